@@ -97,19 +97,19 @@ __device__ __forceinline__ long long local_off_bits(const PassArgs& a, int e, in
     return o;
 }
 
-// LDS position of tile element e.  The tile is stored XOR-swizzled so that the accesses
-// of an op on high tile qubits, whose lanes differ in address bits above the bank
-// period, spread over all banks: complex64 (8-byte elements) XORs element bits 1-4 with
-// bits 4-7 (bit 0 untouched, so the two elements of a 16-byte lane move stay adjacent),
-// complex128 (16 bytes) bits 0-3 with bits 3-6.  The map is a bijection on every range
-// [0, 2^m) and linear over XOR: for disjoint bit sets a | b = a ^ b, so
-// swz(a | b) = swz(a) ^ swz(b), which lets a uniform (scalar) part and a per-lane part be
-// swizzled separately and combined with one XOR.
+// LDS position of tile element e.  The tile is stored XOR-swizzled so that the lanes of an
+// access spread over all banks whichever tile bits they run over: a bank's five (complex64,
+// 8-byte elements) or four (complex128) address bits are the XOR of element bits five or
+// four apart, so any run of consecutive bits, one per bank bit, is free of conflicts.  The
+// map is a bijection on every range [0, 2^m) and linear over XOR: for disjoint bit sets
+// a | b = a ^ b, so swz(a | b) = swz(a) ^ swz(b), which lets a uniform (scalar) part and a
+// per-lane part be swizzled separately and combined with one XOR.  (planner.cpp's
+// tile_slot is the same map.)
 template <typename C>
 __device__ __forceinline__ int swz(int e)
 {
-    if constexpr (sizeof(C) == 8) return e ^ (((e >> 4) & 15) << 1);
-    else return e ^ ((e >> 3) & 15);
+    if constexpr (sizeof(C) == 8) return e ^ ((e >> 5) & 31) ^ (e >> 10);
+    else return e ^ ((e >> 4) & 15) ^ ((e >> 8) & 15);
 }
 
 // Move a tile between HBM and LDS.  Every lane moves 16 bytes at a time: W = 1
@@ -144,13 +144,28 @@ __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restri
     // batches, so the largest tile does not set the kernel's register count
     constexpr int CH = NS < 8 ? NS : 8;
     V v[CH];
-    V* l = reinterpret_cast<V*>(lds);
-    // 16-byte unit u = NT j + tid holds tile elements W u .. W u + W - 1, stored at the
-    // swizzled position of element W u (the swizzle keeps the pair together).  The
-    // swizzle reads element bits below 8 only, which come from tid, and leaves the bits
-    // from j alone, so the position is NT j + swz(W tid) / W: an immediate offset per j.
-    const int ut = swz<C>(W * tid) / W;
-    auto unit = [&](int j) { return (j << LOGT) + ut; };
+    // 16-byte unit u = NT j + tid holds tile elements W u .. W u + W - 1; the positions of
+    // its elements are those of element W tid (+ 1) XOR the compile-time part of j
+    int ut = swz<C>(W * tid);
+    asm volatile("" : "+v"(ut));   // keeps the positions of all j from being held across the tile loop
+    auto put = [&](int j, const V& x) {
+        const int at = ut ^ swz<C>(W * (j << LOGT));
+        if constexpr (W == 2) {
+            lds[at] = C{x.x, x.y};
+            lds[at ^ 1] = C{x.z, x.w};
+        } else {
+            lds[at] = x;
+        }
+    };
+    auto get = [&](int j) {
+        const int at = ut ^ swz<C>(W * (j << LOGT));
+        if constexpr (W == 2) {
+            const C p = lds[at], r = lds[at ^ 1];
+            return V{p.x, p.y, r.x, r.y};
+        } else {
+            return lds[at];
+        }
+    };
     auto off = [&](int j) {
         long long so = 0;
 #pragma unroll
@@ -165,14 +180,81 @@ __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restri
             for (int j = 0; j < CH; ++j)
                 v[j] = __builtin_bit_cast(V, __builtin_nontemporal_load((const NV*)(st + toff + off(j0 + j))));
 #pragma unroll
-            for (int j = 0; j < CH; ++j) l[unit(j0 + j)] = v[j];
+            for (int j = 0; j < CH; ++j) put(j0 + j, v[j]);
         } else {
 #pragma unroll
-            for (int j = 0; j < CH; ++j) v[j] = l[unit(j0 + j)];
+            for (int j = 0; j < CH; ++j) v[j] = get(j0 + j);
 #pragma unroll
             for (int j = 0; j < CH; ++j)
                 __builtin_nontemporal_store(__builtin_bit_cast(NV, v[j]), (NV*)(st + toff + off(j0 + j)));
         }
+    }
+}
+
+// The two halves of a tile load for a kernel that has other work in between: NS 16-byte
+// units per thread from p (the tile's base plus the thread's offset) into registers, and
+// from there to their places in LDS.
+template <typename C, int NS, int W, int NT>
+__device__ __forceinline__ void load_tile(gptr<C> p, const PassArgs& a, floatx4 (&v)[NS])
+{
+    constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        long long o = 0;
+#pragma unroll
+        for (int b = 0; (1 << b) < NS; ++b)
+            if ((j >> b) & 1) o += local_stride(a, LOGT + LW + b);
+        v[j] = __builtin_nontemporal_load((const floatx4*)(p + o));
+    }
+}
+
+template <typename C, int NS, int W, int NT>
+__device__ __forceinline__ void put_tile(C* __restrict__ lds, const floatx4 (&v)[NS])
+{
+    constexpr int LOGT = NT == 512 ? 9 : 8;
+    int ut = swz<C>(W * (int)threadIdx.x);
+    asm volatile("" : "+v"(ut));
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int at = ut ^ swz<C>(W * (j << LOGT));
+        if constexpr (W == 2) {
+            lds[at] = C{v[j].x, v[j].y};
+            lds[at ^ 1] = C{v[j].z, v[j].w};
+        } else {
+            lds[at] = __builtin_bit_cast(C, v[j]);
+        }
+    }
+}
+
+template <typename C, int NS, int W, int NT>
+__device__ __forceinline__ void get_tile(const C* __restrict__ lds, floatx4 (&v)[NS])
+{
+    constexpr int LOGT = NT == 512 ? 9 : 8;
+    int ut = swz<C>(W * (int)threadIdx.x);
+    asm volatile("" : "+v"(ut));
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int at = ut ^ swz<C>(W * (j << LOGT));
+        if constexpr (W == 2) {
+            const C p = lds[at], q = lds[at ^ 1];
+            v[j] = floatx4{p.x, p.y, q.x, q.y};
+        } else {
+            v[j] = __builtin_bit_cast(floatx4, lds[at]);
+        }
+    }
+}
+
+template <typename C, int NS, int W, int NT>
+__device__ __forceinline__ void store_tile(gptr<C> p, const PassArgs& a, const floatx4 (&v)[NS])
+{
+    constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        long long o = 0;
+#pragma unroll
+        for (int b = 0; (1 << b) < NS; ++b)
+            if ((j >> b) & 1) o += local_stride(a, LOGT + LW + b);
+        __builtin_nontemporal_store(v[j], (floatx4*)(p + o));
     }
 }
 
@@ -269,215 +351,302 @@ __device__ void op_dense(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __
     }
 }
 
-// Dense op on matrix cores: FP32 MFMA for complex64, FP64 MFMA for complex128 (the
-// 3-qubit ops; 4-qubit ones take op_dense_mfma_3m below).  The op
-// is the real-embedded 2D x 2D matrix (D = 2^K) times the tile viewed as D x (T / D)
-// complex columns (one column per group of amplitudes that differ only in the op's
-// targets).  A wave takes 16 groups at a time: lane (q, col) = (lane / 16, lane % 16)
-// feeds group `col`, complex input rows 4 j + q (real part, then imaginary part, as two
-// K = 4 steps), and receives output rows 8 rb + 2 q and 8 rb + 2 q + 1 of row block rb
-// (A[i][k] sits in lane i + 16 k and B[k][j] in lane j + 16 k in both precisions; the
-// output rows' order differs between the FP32 and FP64 instructions, which the planner's
-// lanes' choice of A rows absorbs).  The op's complex matrix is staged in LDS once per
-// pass, D x D in the state's precision (half the bytes of its real embedding
-// [[Re, -Im], [Im, Re]]), each row's entries permuted for the LDS banks; each lane reads
-// the complex entries of its A-operand slots
-// once per op and keeps the real-embedded values in registers for the whole op.  All
-// reads of a block precede its writes, so the update is in place; waves own disjoint
-// groups.
+// ---- dense ops on matrix cores
+//
+// A 4-qubit op multiplies a 16 x 16 complex matrix M into the tile viewed as 16 rows (the
+// op's basis states) by columns (the groups).  A wave takes 16 columns at a time, one block
+// of 256 amplitudes: lane (q, c) = (lane / 16, lane % 16) holds four amplitudes of column
+// c, of the rows the planner gave to (q, j), j < 4, and gets back the same four rows'
+// results.  The planner fixes which tile bits the lane, j and the block number run over
+// (planner.cpp, mfma_tables) and stores, per op, the LDS byte offset of each of those bits;
+// the address of an access is one XOR of a lane's and a block's part.  It also stores the
+// matrix in the order the lanes feed it, so an op's set-up is two or four 16-byte loads.
+//
+// Pairs.  Two ops on disjoint targets, one after the other, take one LDS round trip: the
+// matrix instruction contracts the index that lies on (lane / 16, j) and leaves the other
+// on lane % 16, and with the amplitudes as its first operand instead of its second the
+// result comes out transposed: the first op's rows on lane % 16, and the columns, which
+// are the second op's 16 states, on (lane / 16, j), where the second op needs them.
+
+// complex64: the product in bfloat16 matrix instructions (16 x 16 x 32), each FP32 number
+// carried exactly as the sum of three bfloat16 numbers (8 + 8 + 8 significant bits).  Of
+// the nine products of parts the six of relative size 2^-18 and more are summed, in FP32,
+// smallest first; the three left out are below 2^-25 of the term.  A block takes 192
+// matrix-core clocks (FP32 matrix instructions in the three-product form below take 384)
+// and about as many of the VALU for the splits.  30-qubit depth-20 brickwork, per pass:
+// FP32 instructions 4.19 ms, this 4.00 ms, at which the chip is at its power limit (2.0 GHz
+// against 2.4); error of a 22-qubit brickwork state against 64 bits 9.1e-7 and 3.4e-7.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <typename C, int K, int NT = kThreads>
-__device__ void op_dense_mfma(C* __restrict__ lds, int T, const DevOp& op, const float* __restrict__ Araw)
+struct Split8 {
+    bf16x8 h, m, l;
+};
+
+// Two FP32 numbers to bfloat16 (one instruction) and what that leaves of them: one dot
+// product with (-1, 0) or (0, -1) per number subtracts the rounded part, exactly.
+__device__ __forceinline__ bf16x2 split_step(float& a, float& b)
 {
-    using R = typename std::conditional<sizeof(C) == 8, float, double>::type;
-    using Acc = typename std::conditional<sizeof(C) == 8, floatx4, doublex4>::type;
-    const C* __restrict__ Ac = reinterpret_cast<const C*>(Araw);
-    constexpr int D = 1 << K, R2 = 2 * D, RB = R2 / 16, KS = R2 / 4;
-    // the wave index is uniform: saying so keeps the block loop's bookkeeping and each
-    // block's group base on the scalar unit
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int q = lane >> 4, col = lane & 15;
-    // A slot (rb, ks) of this lane is real-embedded entry (row 16 rb + i, column 4 ks + q),
-    // i = lane % 16.  Input column 4 ks + q is the real (ks even) or imaginary (ks odd)
-    // part of complex input 4 (ks / 2) + q, the order in which each lane feeds its complex
-    // inputs.  Rows are arranged so that output element e of lane 16 q + col is (complex
-    // row 8 rb + 2 q + e / 2, real / imaginary e % 2) in both precisions: the FP32
-    // instruction returns row i = 4 q + e there, so row i <-> (i / 2, i % 2); the FP64 one
-    // returns row i = 4 e + q (measured on gfx950), so row i <-> (2 (i % 4) + i / 8,
-    // (i / 4) % 2).  The entry is Re where the row's and column's real / imaginary halves
-    // agree (co == ks % 2), else -Im (co = 0) or +Im (co = 1); slots 2 j and 2 j + 1 share
-    // one complex entry.
-    const int i16 = lane & 15;
-    const int ro = sizeof(C) == 8 ? (i16 >> 1) : 2 * (i16 & 3) + (i16 >> 3);
-    const bool co = sizeof(C) == 8 ? (i16 & 1) : ((i16 >> 2) & 1);
-    // entry (r, c) is staged at r D + (c ^ (r % 8)), so that the eight rows a group of
-    // lanes reads in one access fall in different LDS banks
-    const C* __restrict__ Al = Ac + ro * D;
-    R a[RB][KS];
+    const bf16x2 h = __builtin_convertvector((floatx2{a, b}), bf16x2);
+    // (-1, 0) and (0, -1) in registers: as an inline constant the instruction reads -1.0 as
+    // the other pair
+    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
+    asm("" : "+s"(lo), "+s"(hi));
+    a = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, lo), a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, hi), b, false);
+    return h;
+}
+
+__device__ __forceinline__ Split8 split8(const float (&x)[8])
+{
+    Split8 s;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int j = 0; j < KS / 2; ++j) {
-            const C u = Al[8 * rb * D + ((4 * j + q) ^ ro)];
-            a[rb][2 * j] = co ? u.y : u.x;
-            a[rb][2 * j + 1] = co ? u.x : -u.y;
-        }
-    // this lane's row offsets (the same for every block)
-    // (swizzled LDS positions: the lane's group and row parts are folded into rin / rout)
-    const int bcol = swz<C>(group_base<K>(col, op));
-    int rin[KS / 2], rout[2 * RB];
-#pragma unroll
-    for (int j = 0; j < KS / 2; ++j) rin[j] = swz<C>(row_off<K>(4 * j + q, op)) ^ bcol;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        rout[2 * rb] = swz<C>(row_off<K>(8 * rb + 2 * q, op)) ^ bcol;
-        rout[2 * rb + 1] = swz<C>(row_off<K>(8 * rb + 2 * q + 1, op)) ^ bcol;
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+        const bf16x2 h = split_step(a, b), m = split_step(a, b);
+        const bf16x2 l = __builtin_convertvector((floatx2{a, b}), bf16x2);
+        s.h[2 * i] = h[0]; s.h[2 * i + 1] = h[1];
+        s.m[2 * i] = m[0]; s.m[2 * i + 1] = m[1];
+        s.l[2 * i] = l[0]; s.l[2 * i + 1] = l[1];
     }
-    const int nblk = (T >> K) >> 4;
-    // complex64: two blocks per iteration (blocks blk and blk + waves), their LDS reads
-    // issued together and their accumulation chains interleaved on the matrix pipe;
-    // complex128: one (the FP64 pipe gains nothing from it, and the registers it would
-    // take cost occupancy)
-    constexpr int NW = NT / 64, U = sizeof(C) == 8 ? 2 : 1;
-    for (int blk = wave; blk < nblk; blk += U * NW) {
-        int sb[U];
-        bool live[U];
+    return s;
+}
+
+// The (Re, -Im) operand of an output's real part, turned into (Im, Re) for its
+// imaginary part: halves swapped, the new low half's sign flipped.
+__device__ __forceinline__ bf16x8 imag_operand(bf16x8 v)
+{
+    uintx4 u = __builtin_bit_cast(uintx4, v);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int b = blk + u * NW;
-            live[u] = b < nblk;   // uniform
-            // the block's part of the group base is uniform (scalar unit); the lane's
-            // part was computed once
-            sb[u] = __builtin_amdgcn_readfirstlane(swz<C>(group_base<K>((live[u] ? b : blk) << 4, op)));
-        }
-        C v[U][KS / 2];
+    for (int i = 0; i < 4; ++i) u[i] = __builtin_amdgcn_alignbit(u[i], u[i], 16) ^ 0x8000u;
+    return __builtin_bit_cast(bf16x8, u);
+}
+
+struct Mat64 {
+    Split8 re, im;
+};
+
+// A lane's four complex entries (32 bytes, two 16-byte loads), from LDS or global memory.
+template <typename P>
+__device__ __forceinline__ Mat64 load_mat64(P A, int lane)
+{
+    const floatx4 u = A[lane], v = A[64 + lane];
+    const float x[8] = {u.x, -u.y, u.z, -u.w, v.x, -v.y, v.z, -v.w};
+    Mat64 r;
+    r.re = split8(x);
+    r.im.h = imag_operand(r.re.h);
+    r.im.m = imag_operand(r.re.m);
+    r.im.l = imag_operand(r.re.l);
+    return r;
+}
+
+// SWAP: the amplitudes as the first operand (the transposed result).
+template <bool SWAP>
+__device__ __forceinline__ floatx4 product64(const Split8& a, const Split8& x)
+{
+    auto mm = [](bf16x8 p, bf16x8 v, floatx4 c) {
+        return SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, p, c, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f32_16x16x32_bf16(p, v, c, 0, 0, 0);
+    };
+    floatx4 c = {0, 0, 0, 0};
+    c = mm(a.l, x.h, c);
+    c = mm(a.m, x.m, c);
+    c = mm(a.h, x.l, c);
+    c = mm(a.m, x.h, c);
+    c = mm(a.h, x.m, c);
+    c = mm(a.h, x.h, c);
+    return c;
+}
+
+// complex128: FP64 matrix instructions with three real products instead of four (Gauss's
+// form of a complex product): with M = Ar + i Ai, x = xr + i xi and t = Ar (xr + xi),
+// Re(M x) = t - (Ar + Ai) xi and Im(M x) = t + (Ai - Ar) xr.
+struct Mat128 {
+    double r[4], n[4], s[4];
+};
+
+template <typename P>
+__device__ __forceinline__ Mat128 load_mat128(P A, int lane)
+{
+    Mat128 m;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+    for (int j = 0; j < 4; ++j) {
+        const doublex2 u = A[64 * j + lane];
+        m.r[j] = u.x;
+        m.n[j] = -(u.x + u.y);
+        m.s[j] = u.y - u.x;
+    }
+    return m;
+}
+
+template <bool SWAP>
+__device__ __forceinline__ void product128(const Mat128& a, const double (&xr)[4], const double (&xi)[4],
+                                           doublex4& yr, doublex4& yi)
+{
+    auto mm = [](double p, double v, doublex4 c) {
+        return SWAP ? __builtin_amdgcn_mfma_f64_16x16x4f64(v, p, c, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f64_16x16x4f64(p, v, c, 0, 0, 0);
+    };
+    doublex4 t = {0, 0, 0, 0};
 #pragma unroll
-            for (int j = 0; j < KS / 2; ++j) v[u][j] = lds[sb[u] ^ rin[j]];
-        Acc acc[U][RB];
+    for (int j = 0; j < 4; ++j) t = mm(a.r[j], xr[j] + xi[j], t);
+    yr = yi = t;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[u][rb] = Acc{0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < KS / 2; ++j) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if constexpr (sizeof(C) == 8) {
-                        acc[u][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rb][2 * j], v[u][j].x, acc[u][rb], 0, 0, 0);
-                        acc[u][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rb][2 * j + 1], v[u][j].y, acc[u][rb], 0, 0, 0);
-                    } else {
-                        acc[u][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][2 * j], v[u][j].x, acc[u][rb], 0, 0, 0);
-                        acc[u][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][2 * j + 1], v[u][j].y, acc[u][rb], 0, 0, 0);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!live[u]) continue;
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                C o0, o1;
-                o0.x = acc[u][rb][0];
-                o0.y = acc[u][rb][1];
-                o1.x = acc[u][rb][2];
-                o1.y = acc[u][rb][3];
-                lds[sb[u] ^ rout[2 * rb]] = o0;
-                lds[sb[u] ^ rout[2 * rb + 1]] = o1;
-            }
-        }
+    for (int j = 0; j < 4; ++j) {
+        yr = mm(a.n[j], xi[j], yr);
+        yi = mm(a.s[j], xr[j], yi);
     }
 }
 
-// 4-qubit dense op on matrix cores with three real products instead of the four of
-// the real embedding (Gauss's form of a complex product).  With M = Ar + i Ai and an
-// input column x = xr + i xi, t = Ar (xr + xi) gives Re(M x) = t - (Ar + Ai) xi and
-// Im(M x) = t + (Ai - Ar) xr: per block of 16 groups three 16 x 16 x 16 real products,
-// 12 matrix-core instructions where the real embedding takes 16.  Lane (q, col) =
-// (lane / 16, lane % 16) feeds complex input row 4 j + q of group col at step j and
-// holds row col of each A operand (A[i][k] sits in lane i + 16 k); output element e is
-// complex row 4 q + e (FP32 instruction) or 4 e + q (FP64).  The staged operand is the
-// one op_dense_mfma reads (entry (r, c) at 16 r + (c ^ (r % 8))); each lane forms its
-// three A values per step from one complex entry.
-template <typename C, int NT = kThreads>
-__device__ void op_dense_mfma_3m(C* __restrict__ lds, int T, const DevOp& op, const float* __restrict__ Araw)
+// XOR of the offsets of a number's bits: a block's (uniform, scalar unit) or a lane's.
+__device__ __forceinline__ int packed16(const unsigned* w, int i)
 {
-    using R = typename std::conditional<sizeof(C) == 8, float, double>::type;
-    using Acc = typename std::conditional<sizeof(C) == 8, floatx4, doublex4>::type;
-    constexpr int K = 4, D = 16;
-    const C* __restrict__ Ac = reinterpret_cast<const C*>(Araw);
+    return (w[i >> 1] >> (16 * (i & 1))) & 0xffff;
+}
+
+__device__ __forceinline__ int block_off(int blk, const DevOp& op)
+{
+    int o = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxBlockBits; ++i)
+        if ((blk >> i) & 1) o ^= packed16(op.bbit, i);
+    return __builtin_amdgcn_readfirstlane(o);
+}
+
+__device__ __forceinline__ int lane_off(int lane, const unsigned (&bit)[3])
+{
+    int o = 0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) o ^= __builtin_amdgcn_sbfe(lane, i, 1) & packed16(bit, i);
+    return o;
+}
+
+// The operand of an op: from the pass's LDS block (LDSOP: launches whose operands are all
+// staged), else from the plan's operand array.
+template <typename C, bool LDSOP>
+__device__ __forceinline__ auto load_mat(const DevOp& op, cptr<float> __restrict__ apool, const float* __restrict__ alds,
+                                         int lane)
+{
+    if constexpr (sizeof(C) == 8) {
+        if constexpr (LDSOP) return load_mat64(reinterpret_cast<const floatx4*>(alds + op.aoff), lane);
+        else return load_mat64((cptr<floatx4>)(apool + op.goff), lane);
+    } else {
+        if constexpr (LDSOP) return load_mat128(reinterpret_cast<const doublex2*>(alds + op.aoff), lane);
+        else return load_mat128((cptr<doublex2>)(apool + op.goff), lane);
+    }
+}
+
+// One 4-qubit op, or a pair of them on disjoint targets (op2: the second).
+template <typename C, bool PAIR, bool LDSOP, int NT>
+__device__ __forceinline__ void op_mfma4(C* __restrict__ lds, int T, const DevOp& op, const DevOp& op2,
+                                         cptr<float> __restrict__ apool, const float* __restrict__ alds)
+{
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int q = lane >> 4, col = lane & 15;
-    const C* __restrict__ Al = Ac + col * D;
-    R ar[4], an[4], as[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const C u = Al[(4 * j + q) ^ (col & 7)];
-        ar[j] = u.x;
-        an[j] = -(u.x + u.y);
-        as[j] = u.y - u.x;
-    }
-    const int bcol = swz<C>(group_base<K>(col, op));
-    int rin[4], rout[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        rin[j] = swz<C>(row_off<K>(4 * j + q, op)) ^ bcol;
-        rout[j] = swz<C>(row_off<K>(sizeof(C) == 8 ? 4 * q + j : 4 * j + q, op)) ^ bcol;
-    }
-    const int nblk = (T >> K) >> 4;
-    // blocks per iteration: one for complex64, two for complex128 (the reverse of
-    // op_dense_mfma's choice; each about 1 % faster per pass than the other count)
-    constexpr int NW = NT / 64, U = sizeof(C) == 8 ? 1 : 2;
-    auto mfma = [](R a, R b, Acc c) {
-        if constexpr (sizeof(C) == 8) return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-        else return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    char* __restrict__ base = reinterpret_cast<char*>(lds);
+    const int lin = lane_off(lane, op.lin), lout = PAIR ? lane_off(lane, op2.lin) : lin;
+    auto joff = [](int j, const DevOp& o) {
+        return ((j & 1) ? packed16(&o.jbit, 0) : 0) ^ ((j & 2) ? packed16(&o.jbit, 1) : 0);
     };
-    for (int blk = wave; blk < nblk; blk += U * NW) {
-        int sb[U];
-        bool live[U];
+    const int nblk = T >> 8;
+    constexpr int NW = NT / 64;
+    const auto m1 = load_mat<C, LDSOP>(op, apool, alds, lane);
+    decltype(load_mat<C, LDSOP>(op, apool, alds, lane)) m2;
+    if (PAIR) m2 = load_mat<C, LDSOP>(op2, apool, alds, lane);
+    for (int blk = wave; blk < nblk; blk += NW) {
+        const int sb = block_off(blk, op);
+        C v[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int b = blk + u * NW;
-            live[u] = b < nblk;   // uniform
-            sb[u] = __builtin_amdgcn_readfirstlane(swz<C>(group_base<K>((live[u] ? b : blk) << 4, op)));
-        }
-        C v[U][4];
+        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const C*>(base + ((sb ^ joff(j, op)) ^ lin));
+        if constexpr (sizeof(C) == 8) {
+            float x[8];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+            for (int j = 0; j < 4; ++j) {
+                x[2 * j] = v[j].x;
+                x[2 * j + 1] = v[j].y;
+            }
+            Split8 s = split8(x);
+            floatx4 yr = product64<PAIR>(m1.re, s), yi = product64<PAIR>(m1.im, s);
+            if (PAIR) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[u][j] = lds[sb[u] ^ rin[j]];
-        Acc t[U], yr[U], yi[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) t[u] = Acc{0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int u = 0; u < U; ++u) t[u] = mfma(ar[j], v[u][j].x + v[u][j].y, t[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) yr[u] = yi[u] = t[u];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                yr[u] = mfma(an[j], v[u][j].y, yr[u]);
-                yi[u] = mfma(as[j], v[u][j].x, yi[u]);
+                for (int j = 0; j < 4; ++j) {
+                    x[2 * j] = yr[j];
+                    x[2 * j + 1] = yi[j];
+                }
+                s = split8(x);
+                yr = product64<false>(m2.re, s);
+                yi = product64<false>(m2.im, s);
             }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!live[u]) continue;
+            for (int j = 0; j < 4; ++j) {
+                v[j].x = yr[j];
+                v[j].y = yi[j];
+            }
+        } else {
+            double xr[4], xi[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                C o;
-                o.x = yr[u][e];
-                o.y = yi[u][e];
-                lds[sb[u] ^ rout[e]] = o;
+            for (int j = 0; j < 4; ++j) {
+                xr[j] = v[j].x;
+                xi[j] = v[j].y;
+            }
+            doublex4 yr, yi;
+            product128<PAIR>(m1, xr, xi, yr, yi);
+            if (PAIR) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    xr[j] = yr[j];
+                    xi[j] = yi[j];
+                }
+                product128<false>(m2, xr, xi, yr, yi);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j].x = yr[j];
+                v[j].y = yi[j];
             }
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<C*>(base + ((sb ^ joff(j, PAIR ? op2 : op)) ^ lout)) = v[j];
+    }
+}
+
+// complex128 3-qubit op: its real embedding [[Re, -Im], [Im, Re]], 16 x 16, fills the
+// matrix instruction (three 8 x 8 products would not): lane (q, c) feeds two complex rows
+// of column c, 4 j + q, as four real steps and gets rows 2 q and 2 q + 1 back.
+template <bool LDSOP, int NT>
+__device__ __forceinline__ void op_mfma3(double2* __restrict__ lds, int T, const DevOp& op,
+                                         cptr<float> __restrict__ apool, const float* __restrict__ alds)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    char* __restrict__ base = reinterpret_cast<char*>(lds);
+    doublex2 a0, a1;
+    if constexpr (LDSOP) {
+        const doublex2* A = reinterpret_cast<const doublex2*>(alds + op.aoff);
+        a0 = A[lane];
+        a1 = A[64 + lane];
+    } else {
+        cptr<doublex2> A = (cptr<doublex2>)(apool + op.goff);
+        a0 = A[lane];
+        a1 = A[64 + lane];
+    }
+    // target bits: jbit holds bit 2's offset (rows 4 j + q) and bit 0's (rows 2 q + j)
+    const int r0 = lane_off(lane, op.lin), r1 = r0 ^ packed16(&op.jbit, 0);
+    const int w0 = lane_off(lane, op.lout), w1 = w0 ^ packed16(&op.jbit, 1);
+    const int nblk = T >> 7;
+    constexpr int NW = NT / 64;
+    for (int blk = wave; blk < nblk; blk += NW) {
+        const int sb = block_off(blk, op);
+        const double2 v0 = *reinterpret_cast<const double2*>(base + (sb ^ r0));
+        const double2 v1 = *reinterpret_cast<const double2*>(base + (sb ^ r1));
+        doublex4 y = {0, 0, 0, 0};
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.x, v0.x, y, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.y, v0.y, y, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.x, v1.x, y, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.y, v1.y, y, 0, 0, 0);
+        *reinterpret_cast<double2*>(base + (sb ^ w0)) = double2{y[0], y[1]};
+        *reinterpret_cast<double2*>(base + (sb ^ w1)) = double2{y[2], y[3]};
     }
 }
 
@@ -537,19 +706,27 @@ __device__ __forceinline__ void lds_sync()
 // permutations on 3 or more): the caller launches that variant only for passes without
 // such ops, and its lower register count allows more resident workgroups.  NT is the
 // workgroup size.  Ends with an LDS barrier after the last op.
-template <typename C, bool WIDE = true, int NT = kThreads>
+template <typename C, bool WIDE, bool LDSOP, int NT = kThreads>
 __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp> __restrict__ ops, int op_begin,
                           int op_count, cptr<C> __restrict__ pool, cptr<int> __restrict__ ipool,
-                          const float* __restrict__ alds, long long base)
+                          cptr<float> __restrict__ apool, const float* __restrict__ alds, long long base)
 {
     for (int oi = 0; oi < op_count; ++oi) {
         const DevOp op = ops[op_begin + oi];
         cptr<C> M = pool + op.off;
-        if (op.kind == OP_DENSE && op.aoff >= 0) {
-            // the planner gives matrix cores 3- and 4-qubit ops only (kMaxMfmaK)
-            if (op.k == 3) op_dense_mfma<C, 3, NT>(lds, T, op, alds + op.aoff);
-            else if (op.k == 4) op_dense_mfma_3m<C, NT>(lds, T, op, alds + op.aoff);
-            lds_sync();
+        if (op.kind == OP_DENSE && op.goff >= 0) {
+            // matrix cores: a pair, one 4-qubit op, or (complex128 only) a 3-qubit op
+            if (op.flags) {
+                ++oi;
+                op_mfma4<C, true, LDSOP, NT>(lds, T, op, ops[op_begin + oi], apool, alds);
+            } else if (op.k == 4) {
+                op_mfma4<C, false, LDSOP, NT>(lds, T, op, op, apool, alds);
+            } else {
+                if constexpr (sizeof(C) == 16) op_mfma3<LDSOP, NT>(lds, T, op, apool, alds);
+            }
+            // the next op's waves read only what the same waves wrote: LDS keeps a wave's order
+            if (op.nosync) asm volatile("" ::: "memory");
+            else lds_sync();
             continue;
         }
         if (op.kind == OP_DENSE) {
@@ -578,21 +755,22 @@ __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp
     }
 }
 
-// The pass's MFMA operand block, global -> LDS (once per workgroup, or per work item in
-// batched launches).
+// The pass's staged block (diagonal tables, then matrix operands), global -> LDS: 16 bytes
+// per thread and step; blocks are multiples of 16 bytes.
 template <int NT = kThreads>
-__device__ __forceinline__ void stage_operands(float* __restrict__ alds, cptr<float> __restrict__ apool,
-                                               const PassArgs& a)
+__device__ __forceinline__ void stage_operands(float* __restrict__ alds, cptr<float> __restrict__ apool, int off, int len)
 {
-    for (int i = threadIdx.x; i < a.a_len; i += NT) alds[i] = apool[a.a_off + i];
+    cptr<floatx4> src = (cptr<floatx4>)(apool + off);
+    floatx4* dst = reinterpret_cast<floatx4*>(alds);
+    for (int i = threadIdx.x; i < (len >> 2); i += NT) dst[i] = src[i];
 }
 
 // One tile of one pass: HBM -> LDS, every op of the pass, LDS -> HBM.
-template <typename C, bool WIDE = true, int NT = kThreads>
+template <typename C, bool WIDE, bool LDSOP, int NT = kThreads>
 __device__ __forceinline__ void run_tile(gptr<C> __restrict__ st, C* __restrict__ lds, const PassArgs& a,
                                          long long tile, cptr<DevOp> __restrict__ ops, cptr<C> __restrict__ pool,
-                                         cptr<int> __restrict__ ipool, const float* __restrict__ alds,
-                                         bool from_zero = false)
+                                         cptr<int> __restrict__ ipool, cptr<float> __restrict__ apool,
+                                         const float* __restrict__ alds, bool from_zero = false)
 {
     const long long base = tile_base(a, tile);
     if (from_zero) {
@@ -608,19 +786,37 @@ __device__ __forceinline__ void run_tile(gptr<C> __restrict__ st, C* __restrict_
         move_tile<C, true, NT>(st, lds, a, base);
     }
     __syncthreads();
-    apply_ops<C, WIDE, NT>(lds, 1 << a.m, ops, a.op_begin, a.op_count, pool, ipool, alds, base);
+    apply_ops<C, WIDE, LDSOP, NT>(lds, 1 << a.m, ops, a.op_begin, a.op_count, pool, ipool, apool, alds, base);
     move_tile<C, false, NT>(st, lds, a, base);
 }
 
+// One work-list entry of a pass launch: the state it belongs to and its tile.  Consecutive
+// workgroups run on different XCDs; the map gives each XCD runs of neighbouring tiles, whose
+// 128-byte rows are neighbours in memory (30-qubit passes without ops 3.48 -> 3.42 ms
+// complex64, 28-qubit complex128 1.72 -> 1.65 ms).  It permutes each full stride of the grid
+// (a power of two) and leaves other grids alone.
+__device__ __forceinline__ long long xcd_tile(long long t, unsigned grid, long long ntiles)
+{
+    if ((grid & (grid - 1)) || grid < 64 || ntiles < grid) return t;
+    const unsigned w = (unsigned)t & (grid - 1);
+    return (t - w) + ((w & 7) * (grid >> 3) + (w >> 3));
+}
+
 // WIDE = false: the variant without the register-heavy op paths, for passes free of
-// them (fewer registers, so more resident workgroups when LDS allows).
-template <typename C, bool WIDE, int NT>
-__global__ __launch_bounds__(NT) void k_pass(C* __restrict__ st, C* __restrict__ st2, const PassArgs a,
-                                                   long long ntiles, int from_zero,
-                                                   const DevOp* __restrict__ ops,
-                                                   const C* __restrict__ pool,
-                                                   const int* __restrict__ ipool,
-                                                   const float* __restrict__ apool)
+// them (fewer registers, so more resident workgroups when LDS allows).  PF: tiles of 2^12
+// amplitudes, the next one loaded into registers while the ops run on this one (then no op
+// may wait for a global load of its own, which would wait for the tile's too: operands come
+// from LDS).  Both the moves and the ops of a pass take most of its time alone, and the few
+// workgroups a CU holds (four complex64, two complex128) overlap them only in part; with the
+// loads ahead each counts twice: 30-qubit complex64 passes 4.28 -> 4.00 ms (moves alone
+// 3.46), 28-qubit complex128 2.71 -> 2.43 ms (moves alone 1.72, ops alone 2.03).
+template <typename C, bool WIDE, bool PF, int NT>
+__global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restrict__ st, C* __restrict__ st2,
+                                                                     const PassArgs a, long long ntiles,
+                                                                     int from_zero, const DevOp* __restrict__ ops,
+                                                                     const C* __restrict__ pool,
+                                                                     const int* __restrict__ ipool,
+                                                                     const float* __restrict__ apool)
 {
     // st2 != nullptr: the same pass on a second state of the same shape (tiles ntiles ..
     // 2 ntiles - 1 of the work list), e.g. the adjoint's two vectors.  from_zero: the
@@ -629,14 +825,59 @@ __global__ __launch_bounds__(NT) void k_pass(C* __restrict__ st, C* __restrict__
     extern __shared__ __align__(16) unsigned char smem[];
     C* lds = reinterpret_cast<C*>(smem);
     float* alds = reinterpret_cast<float*>(smem + (sizeof(C) << a.m));
-    stage_operands<NT>(alds, (cptr<float>)apool, a);
+    stage_operands<NT>(alds, (cptr<float>)apool, a.a_off, PF ? a.a_len : a.d_len);
     __syncthreads();
     const long long total = st2 ? 2 * ntiles : ntiles;
-    for (long long t = blockIdx.x; t < total; t += gridDim.x) {
-        const bool second = t >= ntiles;
-        run_tile<C, WIDE, NT>((gptr<C>)(second ? st2 : st), lds, a, second ? t - ntiles : t, (cptr<DevOp>)ops,
-                              (cptr<C>)pool, (cptr<int>)ipool, alds, from_zero != 0);
-        __syncthreads();
+    if constexpr (PF) {
+        constexpr int W = sizeof(C) == 8 ? 2 : 1, NS = 4096 / (NT * W);
+        constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
+        const long long tl = local_off_bits(a, (int)threadIdx.x << LW, LW, LOGT + LW);
+        auto at = [&](long long t, gptr<C>& s) {   // the state of entry t and its tile's base
+            const bool second = t >= ntiles;
+            s = (gptr<C>)(second ? st2 : st);
+            return tile_base(a, xcd_tile(second ? t - ntiles : t, gridDim.x, ntiles));
+        };
+        floatx4 v[NS];
+        long long t = blockIdx.x;
+        gptr<C> s;
+        long long base = at(t, s);
+        load_tile<C, NS, W, NT>(s + base + tl, a, v);
+        put_tile<C, NS, W, NT>(lds, v);
+        lds_sync();
+        for (;;) {
+            const long long tn = t + gridDim.x;
+            gptr<C> sn = s;
+            long long bn = 0;
+            if (tn < total) {
+                bn = at(tn, sn);
+                load_tile<C, NS, W, NT>(sn + bn + tl, a, v);
+            }
+            apply_ops<C, WIDE, true, NT>(lds, 4096, (cptr<DevOp>)ops, a.op_begin, a.op_count, (cptr<C>)pool,
+                                         (cptr<int>)ipool, (cptr<float>)apool, alds, base);
+            if (tn >= total) {
+                move_tile_n<C, false, NS, W, NT>(s, lds, a, base + tl);
+                break;
+            }
+            // the tile to registers, the next one into its place, then the stores: the wait
+            // for the next tile's loads then has no stores behind it to wait for
+            floatx4 r[NS];
+            get_tile<C, NS, W, NT>(lds, r);
+            lds_sync();
+            put_tile<C, NS, W, NT>(lds, v);
+            store_tile<C, NS, W, NT>(s + base + tl, a, r);
+            lds_sync();
+            t = tn;
+            s = sn;
+            base = bn;
+        }
+    } else {
+        for (long long t = blockIdx.x; t < total; t += gridDim.x) {
+            const bool second = t >= ntiles;
+            run_tile<C, WIDE, false, NT>((gptr<C>)(second ? st2 : st), lds, a,
+                                        xcd_tile(second ? t - ntiles : t, gridDim.x, ntiles), (cptr<DevOp>)ops,
+                                        (cptr<C>)pool, (cptr<int>)ipool, (cptr<float>)apool, alds, from_zero != 0);
+            __syncthreads();
+        }
     }
 }
 
@@ -645,7 +886,7 @@ __global__ __launch_bounds__(NT) void k_pass(C* __restrict__ st, C* __restrict__
 // binary search over the items' tile prefix sums; the grid is persistent (fixed size,
 // strided over the work list) so the launch can be captured once and replayed.
 template <typename C, bool WIDE>
-__global__ __launch_bounds__(kThreads) void k_batch_pass(const BatchItem* __restrict__ items,
+__global__ __launch_bounds__(kThreads, sizeof(C) == 8 ? 4 : 2) void k_batch_pass(const BatchItem* __restrict__ items,
                                                          const int* __restrict__ count)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -673,13 +914,13 @@ __global__ __launch_bounds__(kThreads) void k_batch_pass(const BatchItem* __rest
         // pointers read from memory carry no address space: state in global memory
         // (global, not flat, loads and stores), plan tables read-only (scalar loads)
         float* alds = reinterpret_cast<float*>(smem + (sizeof(C) << it.a.m));
-        if (it.a.a_len > 0 && lo != staged) {
-            stage_operands(alds, (cptr<float>)it.apool, it.a);
+        if (it.a.d_len > 0 && lo != staged) {   // diagonal tables only: matrix operands stay in global memory
+            stage_operands(alds, (cptr<float>)it.apool, it.a.a_off, it.a.d_len);
             __syncthreads();
             staged = lo;
         }
-        run_tile<C, WIDE>((gptr<C>)it.state, lds, it.a, tile, (cptr<DevOp>)it.ops, (cptr<C>)it.pool,
-                          (cptr<int>)it.ipool, alds);
+        run_tile<C, WIDE, false>((gptr<C>)it.state, lds, it.a, tile, (cptr<DevOp>)it.ops, (cptr<C>)it.pool,
+                          (cptr<int>)it.ipool, (cptr<float>)it.apool, alds);
         __syncthreads();   // the next work item reuses the LDS tile
     }
 }
@@ -1373,46 +1614,27 @@ static int device_cus()
 
 // Workgroups stride over the tiles (the hardware keeps as many resident as registers and
 // LDS allow; a finished workgroup's slot is refilled at once).
-#ifndef QSV_PASS_THREADS_C64
-#define QSV_PASS_THREADS_C64 256
-#endif
-#ifndef QSV_PASS_THREADS_C128
-#define QSV_PASS_THREADS_C128 256
-#endif
-
-template <typename C, bool WIDE, int NT>
-hipError_t launch_pass_nt(void* st, void* st2, const PassArgs& a, long long ntiles, const DevOp* ops,
-                          const void* pool, const int* ipool, const float* apool, hipStream_t s, bool from_zero)
+template <typename C, bool WIDE, bool PF>
+hipError_t launch_pass_t(void* st, void* st2, const PassArgs& a, long long ntiles, const DevOp* ops,
+                         const void* pool, const int* ipool, const float* apool, hipStream_t s, bool from_zero)
 {
     const long long total = st2 ? 2 * ntiles : ntiles;
     static bool attr_set = false;
     if (!attr_set) {
         // a 64 KiB complex128 tile plus its operand block exceeds the 64 KiB default
-        hipError_t e = hipFuncSetAttribute((const void*)k_pass<C, WIDE, NT>,
+        hipError_t e = hipFuncSetAttribute((const void*)k_pass<C, WIDE, PF, kThreads>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const size_t lds = (sizeof(C) << a.m) + sizeof(float) * (size_t)a.a_len;
+    const size_t lds = (sizeof(C) << a.m) + sizeof(float) * (size_t)(PF ? a.a_len : a.d_len);
     // at most 64 workgroups per CU, each striding over tiles: the operand block is staged
     // once per workgroup rather than once per tile (measured on 2^18-tile passes: 6 %
     // faster for complex64, 10 % for complex128 than one workgroup per tile)
-    const long long grid = std::min<long long>(total, 64ll * device_cus());
-    hipLaunchKernelGGL((k_pass<C, WIDE, NT>), dim3((unsigned)grid), dim3(NT), lds, s, (C*)st, (C*)st2, a, ntiles,
-                       from_zero ? 1 : 0, ops, (const C*)pool, ipool, apool);
+    const long long grid = std::min<long long>(PF ? total / 2 : total, 64ll * device_cus());
+    hipLaunchKernelGGL((k_pass<C, WIDE, PF, kThreads>), dim3((unsigned)grid), dim3(kThreads), lds, s, (C*)st, (C*)st2, a,
+                       ntiles, from_zero ? 1 : 0, ops, (const C*)pool, ipool, apool);
     return hipGetLastError();
-}
-
-template <typename R, bool WIDE>
-hipError_t launch_pass_t(void* st, void* st2, const PassArgs& a, long long ntiles, const DevOp* ops,
-                         const void* pool, const int* ipool, const float* apool, hipStream_t s, bool from_zero)
-{
-    using C = typename CT<R>::T;
-    // workgroup size: NT threads for full tiles, 256 for tiles smaller than NT amplitudes
-    constexpr int NTW = sizeof(C) == 8 ? QSV_PASS_THREADS_C64 : QSV_PASS_THREADS_C128;
-    if (NTW != kThreads && a.m >= (NTW == 512 ? 9 : 8) + (sizeof(C) == 8 ? 1 : 0))
-        return launch_pass_nt<C, WIDE, NTW>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero);
-    return launch_pass_nt<C, WIDE, kThreads>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero);
 }
 
 template <typename C, bool WIDE>
@@ -1452,11 +1674,20 @@ hipError_t launch_pass(int dtype, void* st, const PassArgs& a, long long ntiles,
                        const void* pool, const int* ipool, const float* apool, hipStream_t s, void* st2,
                        bool from_zero, bool wide)
 {
-    if (dtype == 0)
-        return wide ? launch_pass_t<float, true>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero)
-                    : launch_pass_t<float, false>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero);
-    return wide ? launch_pass_t<double, true>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero)
-                : launch_pass_t<double, false>(st, st2, a, ntiles, ops, pool, ipool, apool, s, from_zero);
+    // Loading ahead needs workgroups that take two tiles or more while the device is full
+    // (16 per CU; 25-qubit complex64 passes: 0.139 ms without it, 0.130 with two tiles
+    // per workgroup, 0.136 with four, 0.143 with eight).  complex64 moves pairs of
+    // amplitudes, so qubit 0 must be a tile qubit: it is wherever L >= 1.
+    const bool pf = a.m == 12 && a.L >= 1 && a.staged && !from_zero && (st2 ? 2 : 1) * ntiles >= 32ll * device_cus();
+    auto go = [&](auto c, auto w, auto p) {
+        return launch_pass_t<decltype(c), decltype(w)::value, decltype(p)::value>(st, st2, a, ntiles, ops, pool, ipool,
+                                                                                   apool, s, from_zero);
+    };
+    auto pick = [&](auto c) {
+        if (wide) return pf ? go(c, std::true_type{}, std::true_type{}) : go(c, std::true_type{}, std::false_type{});
+        return pf ? go(c, std::false_type{}, std::true_type{}) : go(c, std::false_type{}, std::false_type{});
+    };
+    return dtype == 0 ? pick(float2{}) : pick(double2{});
 }
 
 static hipError_t launch_fill16(void* st, long long bytes, uint4 first, uint4 rest, hipStream_t s)

@@ -54,9 +54,7 @@ PlanOpts default_opts(int dtype)
         o.mfma_min_k = 3;
         o.fp32_mfma = true;
         o.amp_floats = 2;
-        o.mfma_lds_floats = 2048;  // 8 KiB: room for every 3- and 4-qubit op of a pass on
-                                   // matrix cores (complex entries: 2 KiB per 4-qubit op)
-                                   // with four workgroups per CU (32 KiB tiles)
+        o.stage_floats = 2048;  // 8 KiB (four operands) beside a 32 KiB tile: four workgroups per CU
     } else {            // complex128: 16-byte amplitudes
         o.tile_qubits = 12;
         o.low_qubits = 3;   // 8 contiguous amplitudes: 128-byte runs, as complex64's 16
@@ -65,7 +63,7 @@ PlanOpts default_opts(int dtype)
         o.sigma = 8;
         o.amp_floats = 4;
         o.mfma_min_k = 3;          // FP64 matrix cores: no faster than FP64 VALU in peak,
-        o.mfma_lds_floats = 4096;  // but free of the VALU path's per-row scalar loads
+        o.stage_floats = 4096;  // but free of the VALU path's per-row scalar loads
     }
     return o;
 }
@@ -158,17 +156,15 @@ double op_cost(const FGate& g, const PlanOpts& o)
 {
     const double f = op_fma(g);
     if (mfma_eligible(g, o)) {
-        // matrix cores: complex64 at twice the FP32 VALU rate; a 4-qubit op takes three
-        // real products where its real embedding would take four (priced so only where
-        // a pass can stage four of them)
-        return (o.fp32_mfma ? 0.5 : 1.0) * (g.k == 4 && wide_operand_block(o) ? 0.75 : 1.0) * f;
+        // complex128: the FP64 VALU's rate, a 4-qubit op as three real products where its
+        // embedding would take four.  complex64, per 256 amplitudes and SIMD: a 4-qubit op
+        // takes 192 matrix-core clocks and about 200 of the VALU beside them (the exact
+        // splits, addresses), where 24 FMA per amplitude on the VALU take 384; a 3-qubit op
+        // (run as a 4-qubit one) is priced below that, so that fusion is not driven to
+        // widen every 3-qubit op.
+        return (o.fp32_mfma ? 0.5 : 1.0) * (g.k == 4 ? 0.75 : 1.0) * f;
     }
     return f;
-}
-
-bool wide_operand_block(const PlanOpts& o)
-{
-    return o.mfma_lds_floats >= 4 * (o.amp_floats << 8);
 }
 
 bool mfma_eligible(const FGate& g, const PlanOpts& o)
@@ -654,6 +650,13 @@ std::vector<FGate> fuse_commuting(const std::vector<FGate>& gates, int n, const 
     return out;
 }
 
+// Floats of a matrix-core op's staged operand (a complex64 3-qubit op is run as a 4-qubit
+// one; complex128's real embedding doubles a 3-qubit matrix).
+int operand_floats(int dtype, int k)
+{
+    return dtype == 1 && k == 4 ? 1024 : 512;
+}
+
 // One pass built greedily from the ops not yet done (in their order).  grow: the tile
 // starts as `A0` and takes the qubits of every op that joins, up to m; otherwise the
 // tile is exactly `A0` and only ops inside it (or diagonal ops) join.  An op joins when
@@ -688,15 +691,12 @@ PassPlan build_pass(int n, const std::vector<FGate>& fused, const std::vector<ch
         if ((gm & blocked) || (gm & ~gd & blocked_d)) { defer(gm, gd); continue; }
         const double c = op_cost(g, o) + o.sigma;
         const bool limit_ops = o.max_ops_per_pass > 0 && (int)pp.ops.size() >= o.max_ops_per_pass;
-        // a matrix-core op whose operand no longer fits the pass's block would run on the
-        // VALU at several times its planned cost: it waits for the next pass instead
-        // (diagonal tables are staged too, where they fit).  With a block too small for
-        // four 4-qubit matrices (served complex128 passes) that would cost more passes
-        // than the VALU fallback: there the op stays in the pass.
+        // a matrix-core op whose operand no longer fits the pass's staged block waits for the
+        // next pass: reading it from global memory in the op phase would wait for the next
+        // tile's loads (diagonal tables are staged too, where they fit)
         const bool mf = mfma_eligible(g, o);
-        const int af = mf ? o.amp_floats << (2 * g.k) : g.kind == OP_DIAG ? o.amp_floats << g.k : 0;
-        const bool fits_operands = whole || !mf || !wide_operand_block(o) ||
-                                   ((afl + 3) & ~3) + af <= o.mfma_lds_floats || pp.ops.empty();
+        const int af = mf ? operand_floats(o.fp32_mfma ? 0 : 1, g.k) : g.kind == OP_DIAG ? o.amp_floats << g.k : 0;
+        const bool fits_operands = whole || !mf || ((afl + 3) & ~3) + af <= o.stage_floats || pp.ops.empty();
         const bool fits_budget = whole || o.pass_budget < 0 || c <= budget || pp.ops.empty();
         unsigned long long nA = (g.kind == OP_DIAG) ? A : (A | gm);
         if (grow && pp.ops.empty() && __builtin_popcountll(nA) > m) {
@@ -711,7 +711,7 @@ PassPlan build_pass(int n, const std::vector<FGate>& fused, const std::vector<ch
             pp.ops.push_back(i);
             budget -= c;
             pp.cost += c;
-            if (af > 0 && ((afl + 3) & ~3) + af <= o.mfma_lds_floats) afl = ((afl + 3) & ~3) + af;
+            if (af > 0 && ((afl + 3) & ~3) + af <= o.stage_floats) afl = ((afl + 3) & ~3) + af;
         } else {
             defer(gm, gd);
             if ((blocked & all) == all) break;
@@ -765,6 +765,41 @@ void merge_diagonals(std::vector<FGate>& ops, int kmax)
         if (!is_identity(g)) ops.push_back(std::move(g));
 }
 
+// An op that can be one of a pair (kernels.hip): a 4-qubit matrix-core op, complex64
+// 3-qubit ones too (they are run as 4-qubit ops).
+bool pairable(const FGate& g, const PlanOpts& o)
+{
+    return mfma_eligible(g, o) && (g.k == 4 || o.fp32_mfma);
+}
+
+// Order a pass's ops so that ops which can run as a pair are neighbours: an op moves up
+// behind an earlier one when it shares no qubit with it or with any op in between (then
+// it commutes with each of them exactly).
+void pair_up(const std::vector<FGate>& fused, const PlanOpts& o, PassPlan& pp)
+{
+    std::vector<int> rest(pp.ops), out;
+    while (!rest.empty()) {
+        const FGate& a = fused[(size_t)rest[0]];
+        unsigned long long seen = qubit_mask(a);
+        size_t hit = 0;
+        if (pairable(a, o)) {
+            for (size_t i = 1; i < rest.size() && !hit; ++i) {
+                const FGate& b = fused[(size_t)rest[i]];
+                const unsigned long long qb = qubit_mask(b);
+                if (!(qb & seen) && pairable(b, o)) hit = i;
+                seen |= qb;
+            }
+        }
+        out.push_back(rest[0]);
+        if (hit) {
+            out.push_back(rest[hit]);
+            rest.erase(rest.begin() + (long)hit);
+        }
+        rest.erase(rest.begin());
+    }
+    pp.ops.swap(out);
+}
+
 // Pass scheduling.  Each pass is the best of several greedy candidates: the tile that
 // grows with the ops in their order, and tiles fixed in advance to the low L qubits
 // plus m - L consecutive others (every window position).  The fixed windows follow the
@@ -796,10 +831,218 @@ bool schedule_passes(int n, const std::vector<FGate>& fused, const PlanOpts& o, 
         }
         if (best.ops.empty()) { err = "internal: a gate does not fit any tile"; return false; }
         for (const int i : best.ops) done[i] = 1;
+        pair_up(fused, o, best);
         remaining -= (int)best.ops.size();
         passes.push_back(std::move(best));
     }
     return true;
+}
+
+// ---- operand tables of matrix-core ops (kernels.hip: op_mfma4, op_mfma3)
+
+// LDS position of tile element e (kernels.hip: swz).
+int tile_slot(int dtype, int e)
+{
+    if (dtype == 0) return e ^ ((e >> 5) & 31) ^ (e >> 10);
+    return e ^ ((e >> 4) & 15) ^ ((e >> 8) & 15);
+}
+
+// Rank over XOR of the bank bits of a set of tile bits: lanes that run over independent
+// bits fall in different LDS banks.
+int bank_rank(int dtype, const int* bits, int count)
+{
+    const int mask = dtype == 0 ? 31 : 15;
+    int basis[5] = {0, 0, 0, 0, 0}, rank = 0;
+    for (int i = 0; i < count; ++i) {
+        int v = tile_slot(dtype, 1 << bits[i]) & mask;
+        for (int b = 4; b >= 0 && v; --b) {
+            if (!((v >> b) & 1)) continue;
+            if (!basis[b]) {
+                basis[b] = v;
+                ++rank;
+                v = 0;
+            } else {
+                v ^= basis[b];
+            }
+        }
+    }
+    return rank;
+}
+
+// A 4-qubit op's basis state held by lane group q in its j-th register: which of the op's
+// local bits run over q and over j.
+struct Spread {
+    int q0 = 0, q1 = 1, j0 = 2, j1 = 3;
+    int state(int q, int j) const
+    {
+        return ((q & 1) << q0) | ((q >> 1) << q1) | ((j & 1) << j0) | ((j >> 1) << j1);
+    }
+};
+
+Spread spread_from(int q0)
+{
+    Spread s;
+    int rest[3], k = 0;
+    for (int i = 0; i < 4; ++i)
+        if (i != q0) rest[k++] = i;
+    s.q0 = q0;
+    s.q1 = rest[0];
+    s.j0 = rest[1];
+    s.j1 = rest[2];
+    return s;
+}
+
+// The local bit of `t` that lane group bit 0 runs over, best for the banks with the four
+// tile bits that lane % 16 runs over.
+int best_q0(int dtype, const int* t, const int* lane16)
+{
+    int best = 0, rank = -1;
+    for (int i = 0; i < 4; ++i) {
+        const int bits[5] = {lane16[0], lane16[1], lane16[2], lane16[3], t[i]};
+        const int r = bank_rank(dtype, bits, 5);
+        if (r > rank) { rank = r; best = i; }
+    }
+    return best;
+}
+
+// Appends one 4-qubit operand: lane 16 q + m feeds row row(m) of M, columns col(q, j); its
+// four complex entries in the state's precision, in 16-byte units a wave's lanes apart.
+template <typename Row, typename Col>
+void push_operand(std::vector<float>& out, int dtype, const std::vector<cd>& M, Row row, Col col)
+{
+    const size_t at = out.size();
+    out.resize(at + (dtype == 0 ? 512 : 1024));
+    for (int lane = 0; lane < 64; ++lane)
+        for (int j = 0; j < 4; ++j) {
+            const cd v = M[(size_t)row(lane & 15) * 16 + col(lane >> 4, j)];
+            if (dtype == 0) {
+                const float w[2] = {(float)v.real(), (float)v.imag()};
+                std::memcpy(&out[at + (size_t)((j >> 1) * 64 + lane) * 4 + 2 * (j & 1)], w, 8);
+            } else {
+                const double w[2] = {v.real(), v.imag()};
+                std::memcpy(&out[at + (size_t)(j * 64 + lane) * 4], w, 16);
+            }
+        }
+}
+
+// Operand and offset tables of the matrix-core op d (matrix M over tile bits d.lpos), or of
+// the pair (d, d2), appended to the plan's operand array; m: the tile's bits.
+// wave: the two tile bits that tell the waves apart, none of the targets.
+void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2, const std::vector<cd>* M2,
+                 const int (&wave)[2], std::vector<float>& out)
+{
+    const int eb = dtype == 0 ? 8 : 16;
+    auto off = [&](int e) { return tile_slot(dtype, e) * eb; };
+    // the matrix instruction's result row held by lane group q in register e, and back
+    auto drow = [&](int q, int e) { return dtype == 0 ? 4 * q + e : 4 * e + q; };
+    auto dq = [&](int r) { return dtype == 0 ? r >> 2 : r & 3; };
+    auto de = [&](int r) { return dtype == 0 ? r & 3 : r >> 2; };
+    unsigned used = 0;
+    for (int j = 0; j < d.k; ++j) used |= 1u << d.lpos[j];
+    if (d2)
+        for (int j = 0; j < d2->k; ++j) used |= 1u << d2->lpos[j];
+    int col[4];   // tile bits that lane % 16 runs over in the reads
+    if (d2) {
+        for (int i = 0; i < 4; ++i) col[i] = d2->lpos[i];
+    } else {
+        int nc = 0;   // independent bank bits first, then any; the wave bits only if nothing else is left
+        const unsigned keep = (1u << wave[0]) | (1u << wave[1]);
+        for (int pass = 0; pass < 3; ++pass)
+            for (int b = 0; b < m && nc < 4; ++b) {
+                if ((used >> b) & 1 || (pass < 2 && (keep >> b) & 1)) continue;
+                col[nc] = b;
+                if (pass == 0 && bank_rank(dtype, col, nc + 1) <= nc) continue;
+                used |= 1u << b;
+                ++nc;
+            }
+    }
+    while (out.size() & 3) out.push_back(0.0f);
+    d.goff = (int)out.size();
+    auto bit = [&](int b) { return (unsigned)off(1 << b); };
+    auto pack = [](unsigned* w, int i, unsigned v) { w[i >> 1] |= v << (16 * (i & 1)); };
+    // lane bits 0-3 run over the tile bits c, bits 4-5 and j over the op's local bits in S
+    auto lanes = [&](DevOp& o, const int* c, const Spread& S, const int* t) {
+        for (int i = 0; i < 4; ++i) pack(o.lin, i, bit(c[i]));
+        pack(o.lin, 4, bit(t[S.q0]));
+        pack(o.lin, 5, bit(t[S.q1]));
+        pack(&o.jbit, 0, bit(t[S.j0]));
+        pack(&o.jbit, 1, bit(t[S.j1]));
+    };
+    if (d.k == 3) {
+        // the real embedding: input column 4 ks + q is the real (ks even) or imaginary part
+        // of complex input 4 (ks / 2) + q; matrix row i of the FP64 instruction comes back
+        // as element i / 4 of lane group i % 4, and stands for complex row 2 (i % 4) + i / 8,
+        // real or imaginary by (i / 4) % 2
+        const size_t at = out.size();
+        out.resize(at + 512);
+        for (int lane = 0; lane < 64; ++lane) {
+            const int q = lane >> 4, i = lane & 15, r = 2 * (i & 3) + (i >> 3);
+            for (int j = 0; j < 2; ++j) {
+                const cd u = M[(size_t)r * 8 + 4 * j + q];
+                const double w[2] = {(i >> 2) & 1 ? u.imag() : u.real(), (i >> 2) & 1 ? u.real() : -u.imag()};
+                std::memcpy(&out[at + (size_t)(j * 64 + lane) * 4], w, 16);
+            }
+        }
+        for (int i = 0; i < 4; ++i) {
+            pack(d.lin, i, bit(col[i]));
+            pack(d.lout, i, bit(col[i]));
+        }
+        for (int i = 0; i < 2; ++i) {
+            pack(d.lin, 4 + i, bit(d.lpos[i]));        // rows 4 j + q
+            pack(d.lout, 4 + i, bit(d.lpos[1 + i]));   // rows 2 q + j
+        }
+        pack(&d.jbit, 0, bit(d.lpos[2]));
+        pack(&d.jbit, 1, bit(d.lpos[0]));
+    } else if (!d2) {
+        const Spread S = spread_from(best_q0(dtype, d.lpos, col));
+        push_operand(out, dtype, M, [&](int r) { return S.state(dq(r), de(r)); },
+                     [&](int q, int j) { return S.state(q, j); });
+        lanes(d, col, S, d.lpos);
+    } else {
+        // reads: lane % 16 is the second op's state, (q, j) the first's (S1); after the
+        // first product lane % 16 is the first op's new state and (q, e) the second's,
+        // drow(q, e); after the second (q, e) is its new state by S2
+        const Spread S1 = spread_from(best_q0(dtype, d.lpos, d2->lpos));
+        const Spread S2 = spread_from(best_q0(dtype, d2->lpos, d.lpos));
+        push_operand(out, dtype, M, [&](int r) { return r; }, [&](int q, int j) { return S1.state(q, j); });
+        lanes(d, d2->lpos, S1, d.lpos);
+        d2->goff = (int)out.size();
+        push_operand(out, dtype, *M2, [&](int r) { return S2.state(dq(r), de(r)); },
+                     [&](int q, int j) { return drow(q, j); });
+        lanes(*d2, d.lpos, S2, d2->lpos);
+        d.flags = 1;
+    }
+    // the block number's bits: the tile bits that are left
+    int nb = 0;
+    for (const int b : wave)
+        if (!((used >> b) & 1)) {
+            used |= 1u << b;
+            pack(d.bbit, nb++, bit(b));
+        }
+    for (int b = 0; b < m && nb < kMaxBlockBits; ++b)
+        if (!((used >> b) & 1)) pack(d.bbit, nb++, bit(b));
+}
+
+// The matrix of P.ops[oi] (gate g) as the kernels take it: a complex64 3-qubit op gains
+// one more tile qubit, not in `avoid`, as identity; its descriptor and pool matrix follow.
+std::vector<cd> widen(HostPlan& P, int oi, const FGate& g, const PassPlan& pp, unsigned long long& avoid)
+{
+    DevOp& d = P.ops[(size_t)oi];
+    if (!(P.dtype == 0 && g.k == 3)) return g.m;
+    int Q[4] = {g.q[0], g.q[1], g.q[2], -1};
+    for (const int b : pp.active)
+        if (!((avoid >> b) & 1)) { Q[3] = b; break; }
+    avoid |= 1ull << Q[3];
+    std::sort(Q, Q + 4);
+    std::vector<cd> M = embed(g.m, g.q, 3, Q, 4);
+    d.k = 4;
+    for (int j = 0; j < 4; ++j) {
+        d.gbit[j] = Q[j];
+        d.lpos[j] = (int)(std::find(pp.active.begin(), pp.active.end(), Q[j]) - pp.active.begin());
+    }
+    d.off = (int)P.pool.size();
+    P.pool.insert(P.pool.end(), M.begin(), M.end());
+    return M;
 }
 
 // Device tables of a planned circuit (op descriptors, matrix pools, staged operand
@@ -840,6 +1083,7 @@ void build_device_tables(HostPlan& P)
         a.op_count = (int)pp.ops.size();
         a.a_off = (int)P.apool.size();
         a.a_len = 0;
+        std::vector<int> matrix_ops;   // this pass's matrix-core ops (indices into P.ops)
         for (const int fi : pp.ops) {
             const FGate& g = P.fused[fi];
             DevOp d{};
@@ -853,36 +1097,14 @@ void build_device_tables(HostPlan& P)
             }
             const int dd = 1 << g.k;
             d.off = (int)P.pool.size();
-            d.aoff = -1;
+            d.aoff = d.goff = -1;
             if (g.kind == OP_DENSE) {
                 P.pool.insert(P.pool.end(), g.m.begin(), g.m.end());
                 ++P.dense_ops;
-                // the matrix for the matrix cores: 2^k x 2^k complex entries, entry (r, c) at
-                // r 2^k + (c ^ (r % 8)) (the kernel's reads then spread over the LDS
-                // banks), in the state's precision as raw floats (the kernel forms its
-                // real operands in registers), 16-byte aligned
-                const int per = dtype == 0 ? 2 : 4;
-                const int af = per * dd * dd;
-                const int at = (a.a_len + 3) & ~3;
-                if (o.mfma_min_k > 0 && g.k >= o.mfma_min_k && g.k <= kMaxMfmaK && (1 << (a.m - g.k)) >= 16 &&
-                    at + af <= o.mfma_lds_floats) {
-                    P.apool.resize((size_t)a.a_off + at, 0.0f);
-                    d.aoff = at;
-                    for (int e = 0; e < dd * dd; ++e) {
-                        const int r = e / dd, c = (e % dd) ^ (r & 7);
-                        const cd v = g.m[(size_t)r * dd + c];
-                        if (dtype == 0) {
-                            P.apool.push_back((float)v.real());
-                            P.apool.push_back((float)v.imag());
-                        } else {
-                            const double re = v.real(), im = v.imag();
-                            float w[4];
-                            std::memcpy(w, &re, 8);
-                            std::memcpy(w + 2, &im, 8);
-                            P.apool.insert(P.apool.end(), w, w + 4);
-                        }
-                    }
-                    a.a_len = at + af;
+                // matrix cores need 16 groups per block; complex64 3-qubit ops are run as
+                // 4-qubit ones on one more tile bit
+                if (mfma_eligible(g, o) && a.m >= (dtype == 0 ? 8 : g.k + 4)) {
+                    matrix_ops.push_back((int)P.ops.size());
                     ++P.mfma_ops;
                     P.mfma_fma_per_amp += op_fma(g);
                 }
@@ -893,7 +1115,7 @@ void build_device_tables(HostPlan& P)
                 // in the state's precision as raw floats, 16-byte aligned
                 const int per = dtype == 0 ? 2 : 4;
                 const int at = (a.a_len + 3) & ~3;
-                if (at + per * dd <= o.mfma_lds_floats) {
+                if (at + per * dd <= o.stage_floats) {
                     P.apool.resize((size_t)a.a_off + at, 0.0f);
                     for (int r = 0; r < dd; ++r) {
                         const cd v = g.m[(size_t)r * dd + r];
@@ -928,6 +1150,62 @@ void build_device_tables(HostPlan& P)
             P.fma_per_amp += op_fma(g);
             P.ops.push_back(d);
         }
+        a.d_len = a.a_len;
+        // the matrix-core ops' operands, behind the pass's diagonal tables
+        auto gate_of = [&](int oi) -> const FGate& { return P.fused[(size_t)pp.ops[(size_t)(oi - a.op_begin)]]; };
+        struct Step {   // one op or one pair
+            int oi, oj;
+            std::vector<cd> m1, m2;
+            unsigned bits;   // its tile bits
+        };
+        std::vector<Step> steps;
+        for (size_t i = 0; i < matrix_ops.size(); ++i) {
+            Step st;
+            st.oi = matrix_ops[i];
+            st.oj = -1;
+            const FGate& g = gate_of(st.oi);
+            const int oj = i + 1 < matrix_ops.size() ? matrix_ops[i + 1] : -1;
+            if (oj == st.oi + 1 && pairable(g, o) && pairable(gate_of(oj), o) && !(qubit_mask(g) & qubit_mask(gate_of(oj))))
+                st.oj = oj;
+            unsigned long long avoid = qubit_mask(g) | (st.oj >= 0 ? qubit_mask(gate_of(st.oj)) : 0);
+            st.m1 = widen(P, st.oi, g, pp, avoid);
+            if (st.oj >= 0) {
+                st.m2 = widen(P, st.oj, gate_of(st.oj), pp, avoid);
+                ++i;
+            }
+            st.bits = 0;
+            for (const int x : {st.oi, st.oj})
+                for (int j = 0; x >= 0 && j < P.ops[(size_t)x].k; ++j) st.bits |= 1u << P.ops[(size_t)x].lpos[j];
+            steps.push_back(std::move(st));
+        }
+        // runs of neighbouring steps whose targets leave two tile bits free: those bits tell
+        // the waves apart in all of them, and no barrier is needed inside the run
+        for (size_t i = 0; i < steps.size();) {
+            unsigned bits = steps[i].bits;
+            size_t e = i + 1;
+            auto last = [&](const Step& x) { return x.oj >= 0 ? x.oj : x.oi; };
+            while (e < steps.size() && steps[e].oi == last(steps[e - 1]) + 1 &&
+                   a.m - __builtin_popcount(bits | steps[e].bits) >= 2)
+                bits |= steps[e++].bits;
+            int wave[2] = {0, 0}, nw = 0;   // the two highest free bits: the lanes want the low ones
+            for (int b = a.m - 1; b >= 0 && nw < 2; --b)
+                if (!((bits >> b) & 1)) wave[nw++] = b;
+            for (size_t x = i; x < e; ++x) {
+                Step& st = steps[x];
+                DevOp* d2 = st.oj >= 0 ? &P.ops[(size_t)st.oj] : nullptr;
+                mfma_tables(dtype, a.m, P.ops[(size_t)st.oi], st.m1, d2, d2 ? &st.m2 : nullptr, wave, P.apool);
+                P.ops[(size_t)st.oi].nosync = nw == 2 && a.m >= 10 && x + 1 < e;
+            }
+            i = e;
+        }
+        for (const int oi : matrix_ops) {   // those that fit the staged block, in order
+            DevOp& d = P.ops[(size_t)oi];
+            const int at = d.goff - a.a_off, len = operand_floats(dtype, d.k);
+            if (at + len > o.stage_floats) break;
+            d.aoff = at;
+            a.a_len = at + len;
+        }
+        a.staged = matrix_ops.empty() || P.ops[(size_t)matrix_ops.back()].aoff >= 0;
         {
             bool wide = false;
             for (int i = a.op_begin; i < a.op_begin + a.op_count; ++i) {

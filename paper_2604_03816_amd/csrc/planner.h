@@ -46,10 +46,10 @@ struct PlanOpts {
     double sigma = 8;          // per-op on-chip cost in FMA-per-amplitude units
     int max_ops_per_pass = 0;  // 0: no limit
     int mfma_min_k = 0;        // dense ops with k >= this run on MFMA; 0: never
-    bool fp32_mfma = false;    // complex64: MFMA at twice the VALU rate (cost halved in planning)
-    int mfma_lds_floats = 2048;  // per-pass cap of operand floats staged in LDS (MFMA matrices,
-                                 // diagonal tables)
-    int amp_floats = 2;        // floats per staged complex entry (2: complex64, 4: complex128)
+    bool fp32_mfma = false;    // complex64: matrix-core ops as bfloat16 products of exact FP32 splits
+    int stage_floats = 2048;   // per-pass cap of floats staged in LDS (diagonal tables, then
+                               // matrix operands)
+    int amp_floats = 2;        // floats per complex entry (2: complex64, 4: complex128)
 };
 
 struct PassPlan {
@@ -75,7 +75,8 @@ struct HostPlan {
                                    // >= 3 (the register-heavy paths of the pass kernels)
     std::vector<cd> pool;
     std::vector<int> ipool;
-    std::vector<float> apool;      // MFMA operand blocks, one contiguous block per pass
+    std::vector<float> apool;      // per pass: diagonal tables (staged in LDS), then the matrix-core
+                                   // ops' operand and offset tables
     // stats
     size_t dense_ops = 0, diag_ops = 0, perm_ops = 0, mfma_ops = 0;
     double fma_per_amp = 0, mfma_fma_per_amp = 0;
@@ -92,18 +93,12 @@ bool plan_opts_from(int dtype, const qsv_plan_opts* pub, PlanOpts& o, std::strin
 // or 4 with phases).
 double op_fma(const FGate& g);
 
-// Scheduling cost of one op on chip (excluding sigma): op_fma, halved for complex64 dense
-// ops that run on FP32 MFMA (twice the non-packed VALU rate; FP64 MFMA has the FP64 VALU
-// rate), and times 3/4 for 4-qubit dense ops on matrix cores (three real products per
-// block instead of four) when the pass's operand block holds four of them.
+// Scheduling cost of one op on chip (excluding sigma): op_fma, but for ops on matrix cores
+// their measured share of it.
 double op_cost(const FGate& g, const PlanOpts& o);
 
-// The per-pass operand block holds at least four 4-qubit matrices (the planner's defaults
-// for both dtypes; not served complex128 passes, whose block is capped lower).
-bool wide_operand_block(const PlanOpts& o);
-
-// A dense op of o.mfma_min_k .. kMaxMfmaK qubits: it runs on matrix cores when its
-// operand fits the pass's LDS operand block.
+// A dense op of o.mfma_min_k .. kMaxMfmaK qubits: it runs on matrix cores when its tile
+// holds enough groups.
 bool mfma_eligible(const FGate& g, const PlanOpts& o);
 
 // Physical qubits on which a fused gate is diagonal: target q[j] counts when every entry

@@ -14,6 +14,8 @@ constexpr int kLogThreads = 8;
 constexpr int kMaxTileQubits = 13;  // 2^13 amplitudes: 64 KiB of complex64
 constexpr int kMaxQubits = 34;
 
+constexpr int kMaxBlockBits = 5;    // block-number bits of a matrix-core op: 2^13 amplitudes in blocks of 256
+
 enum OpKind : int { OP_DENSE = 0, OP_DIAG = 1, OP_PERM = 2 };
 
 // One op applied to a tile held on chip.  Targets are listed in the order of the
@@ -25,11 +27,21 @@ struct DevOp {
     int gbit[kMaxK];    // physical qubit of each target
     int off;            // offset into the complex pool: dense 4^k, diagonal 2^k, permutation 2^k phases
     int ioff;           // permutation: offset into the int pool (2^k source rows)
-    int flags;          // permutation: 1 when some phase differs from 1
-    int aoff;           // float offset inside the pass's operand block in LDS, else -1: a dense
-                        // op on matrix cores (its 2^k x 2^k complex matrix in the state's
-                        // precision, entries of row r permuted by c ^ (r % 8)) or a diagonal op
-                        // (its 2^k phases, bit copies of the pool entries)
+    int flags;          // permutation: 1 when some phase differs from 1; matrix-core op: 1 when
+                        // it and the next op of the pass run as one pair
+    int aoff;           // float offset inside the pass's block in LDS, else -1: a diagonal op's 2^k
+                        // phases (bit copies of the pool entries) or a matrix-core op's operand
+    int goff;           // dense op on matrix cores: float offset of its operand in the plan's
+                        // operand array (planner.cpp, mfma_tables); -1: not on matrix cores
+    // matrix-core op: LDS byte offsets of the tile bits that the lane number's six bits, the
+    // two bits of the register number j and the block number's bits run over, two 16-bit
+    // offsets per word (16-bit fields would be read by vector loads).  In a pair the first
+    // op's describe the reads and the second's the writes; a 3-qubit op writes by lout, and
+    // its jbit holds the read's and the write's single bit.
+    // The block number's two lowest bits are the wave's.
+    unsigned lin[3], lout[3], jbit, bbit[3];
+    int nosync;         // matrix-core op (a pair: its first op): the next op is one too and gives each
+                        // wave the same part of the tile, so no barrier is needed between them
 };
 
 // Everything a pass kernel needs to place its tile in the state vector.
@@ -45,8 +57,11 @@ struct PassArgs {
     int op_begin;
     int op_count;
     int nruns;
-    int a_off;          // the pass's MFMA operand block: float offset in the plan's operand array
-    int a_len;          // and its length in floats (staged into LDS behind the tile)
+    int a_off;          // the pass's operand block: float offset in the plan's operand array
+    int a_len;          // the floats of it staged into LDS behind the tile (diagonal tables, then
+                        // matrix operands)
+    int d_len;          // the floats of its diagonal tables
+    int staged;         // every matrix-core op's operand is among the staged floats
     unsigned char phys[kMaxTileQubits];
     unsigned char run_pos[kMaxRuns];
     unsigned char run_len[kMaxRuns];
@@ -133,8 +148,8 @@ struct ZItem {
     long long partial_off;  // first double of this state's partials (13 per chunk)
 };
 
-// MFMA operand floats a served complex64 pass may stage in LDS (the batched launch
-// reserves this much behind the tile).
+// Diagonal-table floats a served pass may stage in LDS (the batched launch reserves this
+// much behind the tile).
 constexpr int kServeOperandFloats = 2048;
 
 // Largest tile (log2 amplitudes) a dtype's pass kernel holds in LDS (64 KiB).

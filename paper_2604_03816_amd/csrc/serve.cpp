@@ -482,7 +482,7 @@ qsv_status qsv_server_submit(qsv_server s, int n, qsv_dtype dtype, const qsv_gat
     const int cap = kServeTileQubits[dtype];
     r->popts.tile_qubits = std::min(r->popts.tile_qubits, cap);
     r->popts.whole_state_max = std::min(r->popts.whole_state_max, cap);
-    r->popts.mfma_lds_floats = std::min(r->popts.mfma_lds_floats, kServeOperandFloats);
+    r->popts.stage_floats = std::min(r->popts.stage_floats, kServeOperandFloats);
     if (r->popts.low_qubits >= r->popts.tile_qubits) r->popts.low_qubits = r->popts.tile_qubits - 1;
     r->gates.resize(n_gates);
     std::string err;
@@ -665,7 +665,7 @@ qsv_status qsv_server_step(qsv_server s, int* n_running, int* n_pending)
             const int cap = kServeTileQubits[QSV_C128];
             q->popts.tile_qubits = std::min(q->popts.tile_qubits, cap);
             q->popts.whole_state_max = std::min(q->popts.whole_state_max, cap);
-            q->popts.mfma_lds_floats = std::min(q->popts.mfma_lds_floats, kServeOperandFloats);
+            q->popts.stage_floats = std::min(q->popts.stage_floats, kServeOperandFloats);
             if (q->popts.low_qubits >= q->popts.tile_qubits) q->popts.low_qubits = q->popts.tile_qubits - 1;
             q->popts.fuse = r->popts.fuse;
             q->popts.commute = r->popts.commute;
