@@ -307,6 +307,8 @@ struct ElemGroup {
     TermArgs ta;
     bool zonly = false;     // every term Z-only: the Z kernel with zt
     ZTermArgs zt;
+    bool rounds = false;    // X/Y supports of at most a round's bits: the register kernel with rd
+    RoundArgs rd;
     long long ntiles;
     int grid;
     std::vector<int> idx;   // term indices
@@ -322,6 +324,55 @@ void set_pauli_weights(TermArgs& t, int i, int q)
     t.kw[i][1] = im[q];
     t.kw[i][2] = -re[q];
     t.kw[i][3] = -im[q];
+}
+
+// Rounds of the register kernel for the terms `idx` on a tile of the qubits `active`: each
+// term joins the first round whose kept bits still take its X/Y support; `idx` comes back
+// ordered by round.
+void plan_rounds(RoundArgs& r, const std::vector<PTerm>& terms, const std::vector<int>& active, int rb,
+                 std::vector<int>& idx)
+{
+    const int m = (int)active.size();
+    auto local = [&](unsigned long long q) {
+        int l = 0;
+        for (int j = 0; j < m; ++j) l |= (int)((q >> active[j]) & 1) << j;
+        return l;
+    };
+    std::vector<int> kept;
+    std::vector<std::vector<int>> in;
+    for (const int i : idx) {
+        const int x = local(terms[i].x);
+        size_t k = 0;
+        while (k < kept.size() && __builtin_popcount(kept[k] | x) > rb) ++k;
+        if (k == kept.size()) {
+            kept.push_back(0);
+            in.push_back({});
+        }
+        kept[k] |= x;
+        in[k].push_back(i);
+    }
+    r = RoundArgs{};
+    idx.clear();
+    for (size_t k = 0; k < kept.size(); ++k) {
+        for (int b = m - 1; b >= 0 && __builtin_popcount(kept[k]) < rb; --b) kept[k] |= 1 << b;
+        int nb = 0;
+        for (int b = 0; b < m; ++b)
+            if ((kept[k] >> b) & 1) r.bits[k] |= b << (4 * nb++);
+        auto by_kept = [&](int l) {
+            int o = 0;
+            for (int b = 0; b < rb; ++b) o |= ((l >> ((r.bits[k] >> (4 * b)) & 15)) & 1) << b;
+            return o;
+        };
+        for (const int i : in[k]) {
+            const int at = (int)idx.size(), z = local(terms[i].z);
+            r.xr[at] = by_kept(local(terms[i].x)) | ((terms[i].ny & 1) << 4);
+            r.zr[at] = by_kept(z);
+            r.zl[at] = z & ~kept[k];
+            idx.push_back(i);
+        }
+        r.end[k] = (int)idx.size();
+    }
+    r.nrounds = (int)kept.size();
 }
 
 bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vector<ElemGroup>& G, size_t& doubles,
@@ -349,33 +400,48 @@ bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vecto
         }
     }
     const size_t zgroups = groups.size();
-    for (size_t i = 0; i < terms.size(); ++i) {
-        const unsigned long long x = terms[i].x;
-        if (zkernel && x == 0) continue;
-        if (__builtin_popcountll(x | lowmask) > m) {
-            err = "Pauli term flips more qubits than one tile holds";
-            return false;
-        }
-        bool placed = false;
-        for (size_t g = zgroups; g < groups.size() && !placed; ++g) {
-            const unsigned long long need = gneed[g] | x;
-            if (groups[g].size() < (size_t)kMaxTermsPerLaunch && __builtin_popcountll(need | lowmask) <= m) {
-                groups[g].push_back((int)i);
-                gneed[g] = need;
-                placed = true;
+    // terms whose X/Y supports fit a round's kept bits go to the register kernel, on tiles of
+    // its own size (imag: the two-state kernel)
+    const int rb = imag ? kRoundBitsTwo : kRoundBits, mr = kLogThreads + rb;
+    const int Lr = std::min(o.low_qubits, mr);
+    const unsigned long long lowr = (1ull << Lr) - 1;
+    auto in_rounds = [&](const PTerm& t) { return n >= mr && t.x && __builtin_popcountll(t.x) <= rb; };
+    auto group = [&](bool reg, int mm, unsigned long long lowm, size_t first) {
+        for (size_t i = 0; i < terms.size(); ++i) {
+            const unsigned long long x = terms[i].x;
+            if ((zkernel && x == 0) || in_rounds(terms[i]) != reg) continue;
+            if (__builtin_popcountll(x | lowm) > mm) return false;
+            bool placed = false;
+            for (size_t g = first; g < groups.size() && !placed; ++g) {
+                const unsigned long long need = gneed[g] | x;
+                if (groups[g].size() < (size_t)kMaxTermsPerLaunch && __builtin_popcountll(need | lowm) <= mm) {
+                    groups[g].push_back((int)i);
+                    gneed[g] = need;
+                    placed = true;
+                }
+            }
+            if (!placed) {
+                groups.push_back({(int)i});
+                gneed.push_back(x);
             }
         }
-        if (!placed) {
-            groups.push_back({(int)i});
-            gneed.push_back(x);
-        }
+        return true;
+    };
+    bool ok = group(true, mr, lowr, zgroups);
+    const size_t rgroups = groups.size();
+    ok = ok && group(false, m, lowmask, rgroups);
+    if (!ok) {
+        err = "Pauli term flips more qubits than one tile holds";
+        return false;
     }
     G.clear();
     doubles = 0;
     for (size_t g = 0; g < groups.size(); ++g) {
         std::vector<int> active;
         ElemGroup E;
-        E.a = tile_args(n, m, L, gneed[g], active);
+        E.rounds = g >= zgroups && g < rgroups;
+        E.a = E.rounds ? tile_args(n, mr, Lr, gneed[g], active) : tile_args(n, m, L, gneed[g], active);
+        if (E.rounds) plan_rounds(E.rd, terms, active, rb, groups[g]);
         E.ta = TermArgs{};
         E.ta.nterms = (int)groups[g].size();
         for (int i = 0; i < E.ta.nterms; ++i) {
@@ -408,8 +474,11 @@ bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vecto
             }
             for (int i = 0; i < E.ta.nterms; ++i) {
                 const int q = E.ta.ny[i] & 3;
-                E.zt.zoff[i] = ((q & 1) ? NS : 0) + (E.ta.zloc[i] >> kLogThreads);
-                E.zt.zlo[i] = E.ta.zloc[i] & (kThreads - 1);
+                const int z = E.ta.zloc[i];
+                const bool pairs = dtype == QSV_C64 && NS >= 2;   // slot bit 0 is local bit 0 (k_expval_z)
+                E.zt.zoff[i] = ((q & 1) ? NS : 0) +
+                               (pairs ? (z & 1) | (z >> (kLogThreads + 1) << 1) : z >> kLogThreads);
+                E.zt.zlo[i] = (pairs ? z >> 1 : z) & (kThreads - 1);
                 if (q == 1 || q == 2) E.zt.neg |= 1u << i;
                 if (q & 1) E.zt.zero |= 1u << i;
                 for (size_t b = 0; b < outside.size(); ++b)
@@ -420,7 +489,9 @@ bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vecto
         // Z-only groups end with a workgroup reduction per term, so fewer workgroups; the
         // X/Y kernel is bound by its per-term LDS work and gains from more of them
         // (measured at 30 qubits; callers that read back many groups ask for fewer)
-        E.grid = (int)std::min<long long>(E.ntiles, E.zonly ? 1024 : xgrid);
+        E.grid = (int)std::min<long long>(E.ntiles, E.rounds && !imag && dtype == QSV_C64 ? 2048
+                                                    : E.zonly || E.rounds       ? 1024
+                                                                                : xgrid);
         E.idx = groups[g];
         E.off = doubles;
         doubles += (size_t)E.grid * E.ta.nterms * 2;
@@ -433,7 +504,9 @@ hipError_t launch_elements(int dtype, const void* sa, const void* sb, const std:
                            double* d_partial, hipStream_t stream)
 {
     for (const ElemGroup& E : G) {
-        const hipError_t e = E.zonly
+        const hipError_t e = E.rounds
+            ? launch_expval_r(dtype, sa, sb, E.a, E.ta, E.rd, E.ntiles, E.grid, d_partial + E.off, stream)
+            : E.zonly
             ? launch_expval_z(dtype, sa, sb, E.a, E.zt, E.ntiles, E.grid, d_partial + E.off, stream)
             : launch_expval(dtype, sa, sb, E.a, E.ta, E.ntiles, E.grid, d_partial + E.off, stream);
         if (e != hipSuccess) return e;

@@ -956,10 +956,8 @@ __device__ __forceinline__ NSum ncombine(NSum a, NSum b)
     return r;
 }
 
-// Fixed-order workgroup reduction of Neumaier pairs: butterfly within each wave,
-// then wave results combined in wave order by thread 0.  Returns the result in
-// thread 0.
-__device__ NSum block_reduce(NSum v, NSum* scratch)
+// Butterfly over a wave's lanes in a fixed order; every lane returns the sum.
+__device__ __forceinline__ NSum wave_reduce(NSum v)
 {
     for (int d = 32; d >= 1; d >>= 1) {
         NSum o;
@@ -967,6 +965,15 @@ __device__ NSum block_reduce(NSum v, NSum* scratch)
         o.c = __shfl_xor(v.c, d);
         v = ((threadIdx.x & d) == 0) ? ncombine(v, o) : ncombine(o, v);
     }
+    return v;
+}
+
+// Fixed-order workgroup reduction of Neumaier pairs: butterfly within each wave,
+// then wave results combined in wave order by thread 0.  Returns the result in
+// thread 0.
+__device__ NSum block_reduce(NSum v, NSum* scratch)
+{
+    v = wave_reduce(v);
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) scratch[w] = v;
     __syncthreads();
@@ -1184,48 +1191,250 @@ __global__ __launch_bounds__(kThreads) void k_expval(const C* __restrict__ sa, c
     }
 }
 
-// Z-only terms: <a|P|b> with P = i^q Z^z sums s(k) i^q conj(a_k) b_k.  As in
-// expval_tiles, a thread's NS elements of a tile are Walsh-transformed over the slice
-// bits, after which a term is one lookup W[zloc >> 8] times signs that are fixed per
-// thread (thread-id bits of z, the phase) or per tile (Z bits outside the tile, a
-// uniform mask built from the tile number's bits).  Each thread reads back only the
-// transform values it wrote, so its LDS slots are private: no barrier, no tile copy.
+// Terms with X/Y factors whose supports hold at most RB qubits (RB = 4 for one state, 3 for
+// two): the tile goes to LDS once, and in each round every thread reads the 2^RB elements
+// that differ in the round's kept bits, so a term pairs registers of one thread: per pair one
+// product and one signed addition instead of two LDS reads, index arithmetic and four
+// conversions.  A round serves every term inside its bits (a field of single X or Y factors
+// on 12 tile qubits takes three rounds).  What bounds it is the read of the state: 30 X terms
+// at 30 qubits complex64 (4 launches) 16.0 -> 9.5 ms.
+constexpr int kRowBits = 8;   // 256 threads
+
+// Sum over one thread's pairs (p, p ^ X) of Re (odd: Im) conj(a[p ^ X]) a[p] with the sign of
+// p's kept Z bits.
+template <int X, int EL>
+__device__ __forceinline__ double pair_sum(const double (&re)[EL], const double (&im)[EL], int zr, bool odd)
+{
+    constexpr int low = X & -X;
+    double s = 0.0;
+    if (!odd) {
+#pragma unroll
+        for (int p = 0; p < EL; ++p)
+            if (!(p & low)) s = fma(re[p ^ X] * re[p] + im[p ^ X] * im[p], (__popc(p & zr) & 1) ? -1.0 : 1.0, s);
+    } else {
+#pragma unroll
+        for (int p = 0; p < EL; ++p)
+            if (!(p & low)) s = fma(re[p ^ X] * im[p] - im[p ^ X] * re[p], (__popc(p & zr) & 1) ? -1.0 : 1.0, s);
+    }
+    return s;
+}
+
+// Two states: the sums of conj(a[p ^ X]) b[p] over the p of even and of odd parity.
+template <int X, int EL>
+__device__ __forceinline__ void pair_sums2(const double (&ar)[EL], const double (&ai)[EL], const double (&br)[EL],
+                                           const double (&bi)[EL], int zr, double (&w)[4])
+{
+#pragma unroll
+    for (int p = 0; p < EL; ++p) {
+        const double wr = ar[p ^ X] * br[p] + ai[p ^ X] * bi[p];
+        const double wi = ar[p ^ X] * bi[p] - ai[p ^ X] * br[p];
+        const double odd = (__popc(p & zr) & 1) ? 1.0 : 0.0, even = 1.0 - odd;
+        w[0] = fma(wr, even, w[0]);
+        w[1] = fma(wi, even, w[1]);
+        w[2] = fma(wr, odd, w[2]);
+        w[3] = fma(wi, odd, w[3]);
+    }
+}
+
+// The value of another lane of the same group of four (CTRL: a quad permutation).
+template <int CTRL>
+__device__ __forceinline__ double quad_swap(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+template <typename C, bool TWO>
+__global__ __launch_bounds__(kThreads) void k_expval_r(const C* __restrict__ sa, const C* __restrict__ sb,
+                                                       const PassArgs a, const TermArgs t, const RoundArgs rd,
+                                                       long long ntiles, double* __restrict__ partial)
+{
+    constexpr int RB = TWO ? kRoundBitsTwo : kRoundBits, EL = 1 << RB, M = kRowBits + RB;
+    constexpr int W = sizeof(C) == 8 ? 2 : 1, LW = W == 2 ? 1 : 0, NS = EL / W;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ TermRow rows[kMaxTermsPerLaunch];
+    __shared__ int rbits[kMaxRounds], rend[kMaxRounds], qn[kMaxTermsPerLaunch];
+    const int tid = threadIdx.x;
+    if (tid < t.nterms) {
+        // x: kept X bits, z: kept Z bits, q: Z bits of the thread's part
+        rows[tid] = TermRow{rd.xr[tid], rd.zr[tid], rd.zl[tid], 0, t.zglob[tid],
+                            {t.kw[tid][0], t.kw[tid][1], t.kw[tid][2], t.kw[tid][3]}};
+        qn[tid] = t.ny[tid] & 3;
+    }
+    if (tid < rd.nrounds) {
+        rbits[tid] = rd.bits[tid];
+        rend[tid] = rd.end[tid];
+    }
+    C* la = reinterpret_cast<C*>(smem);
+    C* lb = la + (1 << M);
+    double* sums = reinterpret_cast<double*>(la + ((TWO ? 2 : 1) << M));   // 64 per term
+    for (int i = tid; i < t.nterms << 6; i += kThreads) sums[i] = 0.0;
+    gptr<C> ga = (gptr<C>)const_cast<C*>(sa), gb = (gptr<C>)const_cast<C*>(sb);
+    const long long tl = local_off_bits(a, tid << LW, LW, kRowBits + LW);
+    __syncthreads();
+    for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const long long base = tile_base(a, tile);
+        move_tile_n<C, true, NS, W>(ga, la, a, base + tl);
+        if (TWO) move_tile_n<C, true, NS, W>(gb, lb, a, base + tl);
+        lds_sync();
+        int i = 0;
+        for (int r = 0; r < rd.nrounds; ++r) {
+            const int bits = __builtin_amdgcn_readfirstlane(rbits[r]);
+            const int end = __builtin_amdgcn_readfirstlane(rend[r]);
+            int tb = tid;   // the thread's element with every kept bit clear
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                const int p = (bits >> (4 * b)) & 15;
+                tb = ((tb >> p) << (p + 1)) | (tb & ((1 << p) - 1));
+            }
+            const int ut = swz<C>(tb);
+            double ar[EL], ai[EL], br[TWO ? EL : 1], bi[TWO ? EL : 1];
+#pragma unroll
+            for (int p = 0; p < EL; ++p) {
+                int o = 0;
+#pragma unroll
+                for (int b = 0; b < RB; ++b)
+                    if ((p >> b) & 1) o |= 1 << ((bits >> (4 * b)) & 15);
+                const int at = ut ^ swz<C>(o);
+                const C v = la[at];
+                ar[p] = v.x;
+                ai[p] = v.y;
+                if constexpr (TWO) {
+                    const C u = lb[at];
+                    br[p] = u.x;
+                    bi[p] = u.y;
+                }
+            }
+            for (; i < end; ++i) {
+                const int x = __builtin_amdgcn_readfirstlane(rows[i].x);
+                const int z = __builtin_amdgcn_readfirstlane(rows[i].z);
+                const int zl = __builtin_amdgcn_readfirstlane(rows[i].q);
+                const bool par = (__popc(tb & zl) + __popcll(base & rows[i].g)) & 1;
+                // (keeps the products of all supports from being formed ahead of the loop)
+#pragma unroll
+                for (int p = 0; p < EL; ++p) asm volatile("" : "+v"(ar[p]), "+v"(ai[p]));
+                double val;
+                if constexpr (!TWO) {
+                    const bool odd = x & 16;
+                    switch (x & 15) {
+                    case 1: val = pair_sum<1>(ar, ai, z, odd); break;
+                    case 2: val = pair_sum<2>(ar, ai, z, odd); break;
+                    case 3: val = pair_sum<3>(ar, ai, z, odd); break;
+                    case 4: val = pair_sum<4>(ar, ai, z, odd); break;
+                    case 5: val = pair_sum<5>(ar, ai, z, odd); break;
+                    case 6: val = pair_sum<6>(ar, ai, z, odd); break;
+                    case 7: val = pair_sum<7>(ar, ai, z, odd); break;
+                    case 8: val = pair_sum<8>(ar, ai, z, odd); break;
+                    case 9: val = pair_sum<9>(ar, ai, z, odd); break;
+                    case 10: val = pair_sum<10>(ar, ai, z, odd); break;
+                    case 11: val = pair_sum<11>(ar, ai, z, odd); break;
+                    case 12: val = pair_sum<12>(ar, ai, z, odd); break;
+                    case 13: val = pair_sum<13>(ar, ai, z, odd); break;
+                    case 14: val = pair_sum<14>(ar, ai, z, odd); break;
+                    default: val = pair_sum<15>(ar, ai, z, odd); break;
+                    }
+                    if (par) val = -val;
+                } else {
+                    double w[4] = {0.0, 0.0, 0.0, 0.0};
+                    switch (x & 7) {
+                    case 1: pair_sums2<1>(ar, ai, br, bi, z, w); break;
+                    case 2: pair_sums2<2>(ar, ai, br, bi, z, w); break;
+                    case 3: pair_sums2<3>(ar, ai, br, bi, z, w); break;
+                    case 4: pair_sums2<4>(ar, ai, br, bi, z, w); break;
+                    case 5: pair_sums2<5>(ar, ai, br, bi, z, w); break;
+                    case 6: pair_sums2<6>(ar, ai, br, bi, z, w); break;
+                    default: pair_sums2<7>(ar, ai, br, bi, z, w); break;
+                    }
+                    const double er = par ? w[2] : w[0], ei = par ? w[3] : w[1];
+                    const double orr = par ? w[0] : w[2], oi = par ? w[1] : w[3];
+                    val = rows[i].k[0] * er - rows[i].k[1] * ei + rows[i].k[2] * orr - rows[i].k[3] * oi;
+                }
+                // four lanes share a sum in LDS: a run-time term number cannot index registers
+                val += quad_swap<0xb1>(val);
+                val += quad_swap<0x4e>(val);
+                if ((tid & 3) == 0) sums[(i << 6) + (tid >> 2)] += val;
+            }
+        }
+        lds_sync();   // the next tile overwrites LDS
+    }
+    // wave w finishes terms w, w + 4, ...: its lanes' 64 sums in a fixed order
+    for (int i = tid >> 6; i < t.nterms; i += kThreads / 64) {
+        const NSum v = wave_reduce(NSum{sums[(i << 6) + (tid & 63)], 0.0});
+        if ((tid & 63) == 0) {
+            double f = 1.0;
+            if (!TWO) {
+                // <a|P|a>: a pair adds 2 Re(i^q w) when |x & z| is even and 2 Re(i^(q+1) Im w)
+                // when it is odd
+                const int q = qn[i];
+                f = (rows[i].x & 16) ? (q == 1 ? -2.0 : q == 3 ? 2.0 : 0.0) : (q == 0 ? 2.0 : q == 2 ? -2.0 : 0.0);
+            }
+            partial[((long long)blockIdx.x * t.nterms + i) * 2] = f * v.s;
+            partial[((long long)blockIdx.x * t.nterms + i) * 2 + 1] = f * v.c;
+        }
+    }
+}
+
+// Z-only terms: <a|P|b> with P = i^q Z^z sums s(k) i^q conj(a_k) b_k.  A thread's NS elements
+// of a tile (the next tile's are loaded, 16 bytes at a time, while this one's are summed) are
+// Walsh-transformed over the tile bits they differ in, after which a term is one lookup of
+// its transform slot times signs that are fixed per thread (thread-id bits of z, the phase)
+// or per tile (Z bits outside the tile, a uniform mask built from the tile number's bits).
+// Each thread reads back only the transform values it wrote, so its LDS slots are private:
+// no barrier, no tile copy.  Slot bits of complex64: local bit 0 (a 16-byte unit's two
+// elements), then bits 9 and up; of complex128: bits 8 and up.
 template <typename C, int NS, bool TWO>
 __device__ __forceinline__ void expval_z_tiles(gptr<C> __restrict__ sa, gptr<C> __restrict__ sb,
                                                double* __restrict__ w, const PassArgs& a, const ZTermArgs& t,
                                                long long ntiles, double (&acc)[kMaxTermsPerLaunch])
 {
-    constexpr int LB = NS >= 8 ? 3 : NS >= 4 ? 2 : NS >= 2 ? 1 : 0;
-    long long hs[LB > 0 ? LB : 1];
-#pragma unroll
-    for (int b = 0; b < LB; ++b) hs[b] = local_stride(a, kLogThreads + b);
+    constexpr int W = sizeof(C) == 8 && NS >= 2 ? 2 : 1, LW = W == 2 ? 1 : 0, NU = NS / W;   // units per thread
+    using V = typename std::conditional<sizeof(C) * W == 16, floatx4, float __attribute__((ext_vector_type(2)))>::type;
     const int tid = threadIdx.x;
-    const long long tl = local_off_bits(a, tid, 0, kLogThreads);
-    auto soff = [&](int j) {
-        long long so = 0;
+    const long long tl = local_off_bits(a, tid << LW, LW, kLogThreads + LW);
+    auto load = [&](gptr<C> s, long long tile, V (&v)[NU]) {
+        const gptr<C> p = s + tile_base(a, tile) + tl;
 #pragma unroll
-        for (int b = 0; b < LB; ++b)
-            if ((j >> b) & 1) so += hs[b];
-        return so;
+        for (int u = 0; u < NU; ++u) {
+            long long o = 0;
+#pragma unroll
+            for (int b = 0; (1 << b) < NU; ++b)
+                if ((u >> b) & 1) o += local_stride(a, kLogThreads + LW + b);
+            v[u] = *(gptr<const V>)(p + o);
+        }
     };
     unsigned tmask = t.neg;   // per-thread signs: the phase and the thread-id bits of z
 #pragma unroll
     for (int i = 0; i < kMaxTermsPerLaunch; ++i)
         if (i < t.nterms) tmask ^= (unsigned)(__popc(tid & t.zlo[i]) & 1) << i;
     double* wt = w + tid;     // this thread's slots: wt[j << 8], j < NS (real), NS + j (imaginary)
+    V va[NU], vb[TWO ? NU : 1];
+    load(sa, blockIdx.x, va);
+    if constexpr (TWO) load(sb, blockIdx.x, vb);
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const long long base = tile_base(a, tile);
         unsigned gm = 0;      // per-tile signs: Z bits outside the tile
 #pragma unroll
         for (int b = 0; b < kMaxTileIndexBits; ++b)
             if ((tile >> b) & 1) gm ^= t.gcol[b];
+        struct E { C c[W]; };
         double re[NS], im[NS];
 #pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            const C av = sa[base + tl + soff(j)];
-            const C bv = TWO ? sb[base + tl + soff(j)] : av;
-            re[j] = (double)av.x * (double)bv.x + (double)av.y * (double)bv.y;
-            im[j] = TWO ? (double)av.x * (double)bv.y - (double)av.y * (double)bv.x : 0.0;
+        for (int u = 0; u < NU; ++u) {
+            const E ea = __builtin_bit_cast(E, va[u]);
+            E eb = ea;
+            if constexpr (TWO) eb = __builtin_bit_cast(E, vb[u]);
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                const int j = W * u + k;
+                const C av = ea.c[k], bv = eb.c[k];
+                re[j] = (double)av.x * (double)bv.x + (double)av.y * (double)bv.y;
+                im[j] = TWO ? (double)av.x * (double)bv.y - (double)av.y * (double)bv.x : 0.0;
+            }
+        }
+        if (tile + gridDim.x < ntiles) {
+            load(sa, tile + gridDim.x, va);
+            if constexpr (TWO) load(sb, tile + gridDim.x, vb);
         }
 #pragma unroll
         for (int h = 1; h < NS; h <<= 1) {
@@ -1264,7 +1473,6 @@ __global__ __launch_bounds__(kThreads) void k_expval_z(const C* __restrict__ sa,
                                                        double* __restrict__ partial)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ NSum scratch[kThreads / 64];
     double* w = reinterpret_cast<double*>(smem);
     double acc[kMaxTermsPerLaunch];
 #pragma unroll
@@ -1276,11 +1484,24 @@ __global__ __launch_bounds__(kThreads) void k_expval_z(const C* __restrict__ sa,
     case 2: expval_z_tiles<C, 4, TWO>(ga, gb, w, a, t, ntiles, acc); break;
     default: expval_z_tiles<C, 8, TWO>(ga, gb, w, a, t, ntiles, acc); break;
     }
+    // the threads' sums, eight terms at a time through LDS; wave w finishes terms w and w + 4
+    // of the eight in a fixed order (a workgroup reduction per term cost two barriers and six
+    // shuffles of every wave each: two 12-qubit complex128 states 19 -> 9 us)
 #pragma unroll
-    for (int i = 0; i < kMaxTermsPerLaunch; ++i) {
-        if (i < t.nterms) {
-            const NSum r = block_reduce(NSum{acc[i], 0.0}, scratch);
-            if (threadIdx.x == 0) {
+    for (int i0 = 0; i0 < kMaxTermsPerLaunch; i0 += 8) {
+        if (i0 >= t.nterms) break;
+        __syncthreads();
+#pragma unroll
+        for (int i = i0; i < i0 + 8; ++i) w[((i - i0) << kLogThreads) + threadIdx.x] = acc[i];
+        __syncthreads();
+        for (int i = i0 + (threadIdx.x >> 6); i < i0 + 8 && i < t.nterms; i += kThreads / 64) {
+            const double* v = w + ((i - i0) << kLogThreads) + (threadIdx.x & 63);
+            NSum r = {v[0], 0.0};
+            nadd(r, v[64]);
+            nadd(r, v[128]);
+            nadd(r, v[192]);
+            r = wave_reduce(r);
+            if ((threadIdx.x & 63) == 0) {
                 partial[((long long)blockIdx.x * t.nterms + i) * 2] = r.s;
                 partial[((long long)blockIdx.x * t.nterms + i) * 2 + 1] = r.c;
             }
@@ -1766,7 +1987,8 @@ hipError_t launch_expval_z(int dtype, const void* sa, const void* sb, const Pass
 {
     const bool two = sb != nullptr && sb != sa;
     if (a.m < kLogThreads || a.m > kExpvalMaxTileQubits) return hipErrorInvalidValue;
-    const size_t lds = ((two ? 2 : 1) * sizeof(double)) << a.m;
+    // the threads' transform slots, and at the end eight terms' sums
+    const size_t lds = std::max<size_t>(((two ? 2 : 1) * sizeof(double)) << a.m, sizeof(double) * 8 * kThreads);
     if (dtype == 0) {
         auto k = two ? k_expval_z<float2, true> : k_expval_z<float2, false>;
         hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const float2*)sa, (const float2*)sb, a, t, ntiles,
@@ -1774,6 +1996,35 @@ hipError_t launch_expval_z(int dtype, const void* sa, const void* sb, const Pass
     } else {
         auto k = two ? k_expval_z<double2, true> : k_expval_z<double2, false>;
         hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const double2*)sa, (const double2*)sb, a, t,
+                           ntiles, partial);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_expval_r(int dtype, const void* sa, const void* sb, const PassArgs& a, const TermArgs& t,
+                           const RoundArgs& r, long long ntiles, int grid, double* partial, hipStream_t s)
+{
+    const bool two = sb != nullptr && sb != sa;
+    if (a.m != kRowBits + (two ? kRoundBitsTwo : kRoundBits) || a.L < 1 || r.nrounds > kMaxRounds)
+        return hipErrorInvalidValue;
+    const size_t lds = (two ? 2 : 1) * ((dtype == 0 ? sizeof(float2) : sizeof(double2)) << a.m) +
+                       sizeof(double) * 64 * (size_t)t.nterms;
+    if (dtype == 0) {
+        auto k = two ? k_expval_r<float2, true> : k_expval_r<float2, false>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const float2*)sa, (const float2*)sb, a, t, r, ntiles,
+                           partial);
+    } else {
+        auto k = two ? k_expval_r<double2, true> : k_expval_r<double2, false>;
+        static const hipError_t raised = [] {   // 64 KiB tiles beside the term rows exceed the default limit
+            hipError_t e = hipFuncSetAttribute((const void*)k_expval_r<double2, true>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 98304);
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void*)k_expval_r<double2, false>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, 98304);
+            return e;
+        }();
+        if (raised != hipSuccess) return raised;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const double2*)sa, (const double2*)sb, a, t, r,
                            ntiles, partial);
     }
     return hipGetLastError();

@@ -87,11 +87,27 @@ struct TermArgs {
     double kw[kMaxTermsPerLaunch][4];
 };
 
+// Rounds of the register kernel for terms with X/Y factors (k_expval_r): in a round each
+// thread holds the tile elements that differ in the round's kept bits, so a term whose
+// X/Y support lies inside them pairs elements of one thread.  Terms are ordered by round.
+constexpr int kRoundBits = 4, kRoundBitsTwo = 3;   // bits kept in a round: one state, two states
+constexpr int kMaxRounds = kMaxTermsPerLaunch;
+struct RoundArgs {
+    int nrounds;
+    int bits[kMaxRounds];            // the round's kept tile bits, ascending, four bits each
+    int end[kMaxRounds];             // one past its last term
+    int xr[kMaxTermsPerLaunch];      // X/Y support by kept-bit index; one state: plus 16 when the term
+                                     // has an odd number of Y factors
+    int zr[kMaxTermsPerLaunch];      // Z/Y support among the kept bits, by kept-bit index
+    int zl[kMaxTermsPerLaunch];      // Z/Y support among the other tile bits
+};
+
 // Work list of the Z-only expectation kernel (every term's X/Y mask is zero).  The
 // host folds each term's phase and global sign into lookups and masks:
-//   zoff[i]   slot of the term in a thread's transform array: (q odd ? NS : 0) + (zloc >> 8)
-//             (q = ny mod 4; odd q selects the imaginary transform)
-//   zlo[i]    the term's Z bits among the thread-id bits (zloc & 255)
+//   zoff[i]   slot of the term in a thread's transform array: (q odd ? NS : 0) plus its Z bits
+//             among the slot bits (k_expval_z; q = ny mod 4: odd q selects the imaginary
+//             transform)
+//   zlo[i]    the term's Z bits among the thread-id bits
 //   neg       bit i: the phase i^q is negative (q = 1 or 2)
 //   zero      bit i: odd q, i.e. the imaginary transform, identically zero when a == b
 //   gcol[b]   bit i: tile-number bit b is a qubit of term i's Z support outside the tile
@@ -184,6 +200,9 @@ hipError_t launch_expval_z(int dtype, const void* sa, const void* sb, const Pass
                            long long ntiles, int grid, double* partial, hipStream_t s);
 hipError_t launch_expval(int dtype, const void* sa, const void* sb, const PassArgs& a, const TermArgs& t,
                          long long ntiles, int grid, double* partial, hipStream_t s);
+// Terms whose X/Y supports fit a round (a.m == 8 + kRoundBits, two states kRoundBitsTwo).
+hipError_t launch_expval_r(int dtype, const void* sa, const void* sb, const PassArgs& a, const TermArgs& t,
+                           const RoundArgs& r, long long ntiles, int grid, double* partial, hipStream_t s);
 hipError_t launch_pauli_apply(int dtype, const void* in, void* out, long long N, const PauliSumArgs& p,
                               int accumulate, hipStream_t s);
 hipError_t launch_probs_full(int dtype, const void* st, long long N, void* out, hipStream_t s);
