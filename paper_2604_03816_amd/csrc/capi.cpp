@@ -1145,28 +1145,36 @@ qsv_status qsv_probs(qsv_state s, const int* qubits, int m, void* out, int out_o
         if (e != hipSuccess) return fail(QSV_E_DEVICE, std::string("probs: ") + hipGetErrorString(e));
         return QSV_OK;
     }
-    MargArgs a{};
-    a.n = n;
+    MargBlocks a{};
     a.m = m;
+    a.cb = std::min(n, kMargBlockBits);
     unsigned long long Q = 0;
     for (int j = 0; j < m; ++j) {
-        a.q[j] = qubits ? qubits[j] : j;
-        Q |= 1ull << a.q[j];
+        const int q = qubits ? qubits[j] : j;
+        Q |= 1ull << q;
+        if (q < a.cb) {
+            a.lq[a.nl] = q;
+            a.lo[a.nl++] = j;
+        } else {
+            a.hq[a.nh] = q;
+            a.ho[a.nh++] = j;
+        }
     }
-    int r = 0;
-    for (int b = 0; b < n; ++b)
-        if (!((Q >> b) & 1)) a.rest[r++] = b;
-    const long long M = 1ll << m, R = 1ll << (n - m);
-    long long nchunks = std::max<long long>(1, (1ll << 20) / M);
-    nchunks = std::min(nchunks, R);
-    a.nchunks = nchunks;
-    a.chunk = R / nchunks;
-    const size_t pbytes = (size_t)(M * nchunks) * 2 * sizeof(double);
+    for (int b = 0, k = 0; b < a.cb; ++b)
+        if (!((Q >> b) & 1)) a.lr[k++] = b;
+    for (int b = a.cb; b < n; ++b)
+        if (!((Q >> b) & 1)) a.rest[a.nr++] = b;
+    // about 2048 workgroups (eight per CU; the partials of at most 2^20 outputs and
+    // workgroups fit 16 MiB), each with a power of two of the blocks
+    const long long M = 1ll << m, H = 1ll << a.nh, U = 1ll << a.nr;
+    a.G = std::max<long long>(1, std::min({2048 / H, U, (1ll << 20) / M}));
+    a.per = U / a.G;
+    const size_t pbytes = a.G == 1 ? 0 : (size_t)(M * a.G) * 2 * sizeof(double);
     const size_t obytes = (size_t)M * sizeof(double);
     if ((st = ensure_work(s, pbytes + (out_on_device ? 0 : obytes))) != QSV_OK) return st;
     double* partial = s->d_work;
     double* dout = out_on_device ? (double*)out : (double*)((char*)s->d_work + pbytes);
-    QSV_HIP(launch_probs_marg(s->dtype, s->buf, a, partial, dout, s->stream));
+    QSV_HIP(launch_marg_blocks(s->dtype, s->buf, a, partial, dout, s->stream));
     if (!out_on_device) QSV_HIP(hipMemcpyAsync(out, dout, obytes, hipMemcpyDeviceToHost, s->stream));
     QSV_HIP(hipStreamSynchronize(s->stream));
     return QSV_OK;
@@ -1431,7 +1439,7 @@ qsv_status qsv_dm_probs(qsv_state s, const int* qubits, int m, double* out)
     if ((st = ensure_work(s, pbytes + obytes)) != QSV_OK) return st;
     double* partial = s->d_work;
     double* dout = (double*)((char*)s->d_work + pbytes);
-    QSV_HIP(launch_probs_marg(s->dtype, s->buf, a, partial, dout, s->stream, true));
+    QSV_HIP(launch_dm_marg(s->dtype, s->buf, a, partial, dout, s->stream));
     QSV_HIP(hipMemcpyAsync(out, dout, obytes, hipMemcpyDeviceToHost, s->stream));
     QSV_HIP(hipStreamSynchronize(s->stream));
     return QSV_OK;

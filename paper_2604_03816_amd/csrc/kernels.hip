@@ -1684,11 +1684,104 @@ __global__ __launch_bounds__(kThreads) void k_probs_full(const C* __restrict__ s
     }
 }
 
-// DM: the buffer holds vec(rho) of an a.n-qubit density matrix (index row + 2^n col)
-// and the probability of basis state k is the diagonal entry Re rho[k, k].
-template <typename C, bool DM>
-__global__ __launch_bounds__(kThreads) void k_probs_marg(const C* __restrict__ st, const MargArgs a,
-                                                         double* __restrict__ partial)
+// Marginal distribution of a state.  A workgroup sums the blocks of 2^cb consecutive
+// amplitudes that share one value of the measured qubits above the block (H values, G
+// workgroups each, `per` blocks a workgroup): every thread keeps a Neumaier pair for each of
+// its places in the block (16-byte loads, the next block's loads ahead of this one's sums),
+// and at the end the block's places that agree on the measured qubits inside it are added
+// in a fixed order.  The state is read once, in order; 5 measured qubits of 27, complex64:
+// 14.3 -> 0.3 ms with the final sum (a thread per output and chunk gathered single
+// amplitudes, and one thread added an output's 32768 chunks).
+template <typename C>
+__global__ __launch_bounds__(kThreads) void k_marg_blocks(const C* __restrict__ st, const MargBlocks a,
+                                                          double* __restrict__ partial, double* __restrict__ out)
+{
+    constexpr int W = 16 / sizeof(C), NU = 16 / W;   // 16-byte units per thread of a full block
+    using V = typename Lane16<C>::T;
+    __shared__ double val[1 << kMargBlockBits];
+    __shared__ NSum part[kThreads];
+    const int tid = threadIdx.x, size = 1 << a.cb;
+    const long long h = blockIdx.x / a.G, g = blockIdx.x % a.G;
+    auto deposit = [](long long v, const int* pos, int k) {
+        long long o = 0;
+        for (int j = 0; j < k; ++j) o |= ((v >> j) & 1) << pos[j];
+        return o;
+    };
+    const long long hbase = deposit(h, a.hq, a.nh);
+    if (size == 1 << kMargBlockBits) {
+        NSum acc[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = NSum{0.0, 0.0};
+        V v[NU];
+        auto load = [&](long long r) {
+            const V* p = reinterpret_cast<const V*>(st + (hbase | deposit(r, a.rest, a.nr))) + tid;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) v[u] = p[u << kLogThreads];
+        };
+        load(g * a.per);
+        for (long long r = g * a.per; r < (g + 1) * a.per; ++r) {
+            double p[16];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                if constexpr (W == 2) {
+                    p[2 * u] = (double)v[u].x * v[u].x + (double)v[u].y * v[u].y;
+                    p[2 * u + 1] = (double)v[u].z * v[u].z + (double)v[u].w * v[u].w;
+                } else {
+                    p[u] = v[u].x * v[u].x + v[u].y * v[u].y;
+                }
+            }
+            if (r + 1 < (g + 1) * a.per) load(r + 1);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) nadd(acc[i], p[i]);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                val[W * ((u << kLogThreads) + tid) + w] = acc[W * u + w].s + acc[W * u + w].c;
+    } else {   // the whole state is one smaller block
+        for (int e = tid; e < size; e += kThreads) {
+            const double x = st[e].x, y = st[e].y;
+            val[e] = x * x + y * y;
+        }
+    }
+    __syncthreads();
+    // output ol of the block: tp threads each add a share of its 2^(cb - nl) places
+    const int nout = 1 << a.nl, places = size >> a.nl;
+    const int tp = nout >= kThreads ? 1 : min(kThreads / nout, places);
+    const long long hout = deposit(h, a.ho, a.nh);
+    const long long M = 1ll << a.m;
+    for (int o0 = 0; o0 < nout; o0 += kThreads / tp) {
+        const int ol = o0 + tid / tp, k0 = tid % tp;
+        NSum s = {0.0, 0.0};
+        if (ol < nout) {
+            const int lb = (int)deposit(ol, a.lq, a.nl);
+            for (int k = k0; k < places; k += tp) nadd(s, val[lb | (int)deposit(k, a.lr, a.cb - a.nl)]);
+        }
+        if (tp > 1) {
+            part[tid] = s;
+            __syncthreads();
+            if (k0 == 0 && ol < nout)
+                for (int k = 1; k < tp; ++k) s = ncombine(s, part[tid + k]);
+        }
+        if (k0 == 0 && ol < nout) {
+            const long long o = hout | deposit(ol, a.lo, a.nl);
+            if (a.G == 1) {
+                out[o] = s.s + s.c;
+            } else {
+                partial[2 * (g * M + o)] = s.s;
+                partial[2 * (g * M + o) + 1] = s.c;
+            }
+        }
+        if (tp > 1) __syncthreads();
+    }
+}
+
+// Marginal of a density matrix's diagonal: the buffer holds vec(rho) of an a.n-qubit density
+// matrix (index row + 2^n col) and the probability of basis state k is Re rho[k, k].
+template <typename C>
+__global__ __launch_bounds__(kThreads) void k_dm_marg(const C* __restrict__ st, const MargArgs a,
+                                                      double* __restrict__ partial)
 {
     const long long M = 1ll << a.m;
     const long long total = M * a.nchunks;
@@ -1703,30 +1796,28 @@ __global__ __launch_bounds__(kThreads) void k_probs_marg(const C* __restrict__ s
     for (long long r = ch * a.chunk; r < (ch + 1) * a.chunk; ++r) {
         long long idx = ob;
         for (int j = 0; j < nr; ++j) idx |= ((r >> j) & 1) << a.rest[j];
-        if (DM) {
-            nadd(s, (double)st[idx + (idx << a.n)].x);
-        } else {
-            const C v = st[idx];
-            const double x = v.x, y = v.y;
-            nadd(s, x * x + y * y);
-        }
+        nadd(s, (double)st[idx + (idx << a.n)].x);
     }
     partial[2 * (ch * M + o)] = s.s;
     partial[2 * (ch * M + o) + 1] = s.c;
 }
 
-// out[o] = Neumaier sum over chunks of partial[(chunk*M + o)] (pairs), fixed order.
+// out[o] = Neumaier sum over chunks of partial[(chunk*M + o)] (pairs), fixed order.  PER: a
+// workgroup per output (many chunks); else a thread per output.
+template <bool PER>
 __global__ __launch_bounds__(kThreads) void k_sum_chunks(const double* __restrict__ partial, long long M,
                                                          long long nchunks, double* __restrict__ out)
 {
-    const long long o = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ NSum scratch[kThreads / 64];
+    const long long o = PER ? (long long)blockIdx.x : (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= M) return;
     NSum s = {0.0, 0.0};
-    for (long long c = 0; c < nchunks; ++c) {
+    for (long long c = PER ? threadIdx.x : 0; c < nchunks; c += PER ? kThreads : 1) {
         nadd(s, partial[2 * (c * M + o)]);
         s.c += partial[2 * (c * M + o) + 1];
     }
-    out[o] = s.s + s.c;
+    if (PER) s = block_reduce(s, scratch);
+    if (!PER || threadIdx.x == 0) out[o] = s.s + s.c;
 }
 
 // Per-qubit <Z_i> and norm of finished served states, batched: work item = one chunk of
@@ -2055,24 +2146,44 @@ hipError_t launch_probs_full(int dtype, const void* st, long long N, void* out, 
     return hipGetLastError();
 }
 
-hipError_t launch_probs_marg(int dtype, const void* st, const MargArgs& a, double* partial, double* out,
-                             hipStream_t s, bool density)
+static hipError_t launch_sum_chunks(const double* partial, long long M, long long nchunks, double* out, hipStream_t s)
+{
+    if (nchunks > 32)
+        hipLaunchKernelGGL(k_sum_chunks<true>, dim3((unsigned)M), dim3(kThreads), 0, s, partial, M, nchunks, out);
+    else
+        hipLaunchKernelGGL(k_sum_chunks<false>, dim3((unsigned)((M + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+                           partial, M, nchunks, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_marg_blocks(int dtype, const void* st, const MargBlocks& a, double* partial, double* out,
+                              hipStream_t s)
+{
+    const long long blocks = a.G << a.nh;
+    if (a.cb > kMargBlockBits || blocks > 0x7fffffffll) return hipErrorInvalidValue;
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_marg_blocks<float2>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const float2*)st, a,
+                           partial, out);
+    else
+        hipLaunchKernelGGL(k_marg_blocks<double2>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const double2*)st, a,
+                           partial, out);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.G == 1) return e;
+    return launch_sum_chunks(partial, 1ll << a.m, a.G, out, s);
+}
+
+hipError_t launch_dm_marg(int dtype, const void* st, const MargArgs& a, double* partial, double* out, hipStream_t s)
 {
     const long long M = 1ll << a.m;
-    const long long total = M * a.nchunks;
-    const long long blocks = (total + kThreads - 1) / kThreads;
-    if (dtype == 0) {
-        auto k = density ? k_probs_marg<float2, true> : k_probs_marg<float2, false>;
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const float2*)st, a, partial);
-    } else {
-        auto k = density ? k_probs_marg<double2, true> : k_probs_marg<double2, false>;
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const double2*)st, a, partial);
-    }
-    hipError_t e = hipGetLastError();
+    const long long blocks = (M * a.nchunks + kThreads - 1) / kThreads;
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_dm_marg<float2>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const float2*)st, a, partial);
+    else
+        hipLaunchKernelGGL(k_dm_marg<double2>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const double2*)st, a,
+                           partial);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((M + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                       (const double*)partial, M, a.nchunks, out);
-    return hipGetLastError();
+    return launch_sum_chunks(partial, M, a.nchunks, out, s);
 }
 
 hipError_t launch_chunk_totals(int src_dtype, const void* src, int chunk_bits, long long nchunks, double* totals,

@@ -131,14 +131,27 @@ struct PauliSumArgs {
     double coeff[kMaxPauliApply];
 };
 
-// Marginal probabilities: thread (o, chunk) sums |alpha|^2 over the indices whose
-// bits at the measured qubits spell o, for the chunk-th range of the other bits.
+// Marginal of a density matrix's diagonal: thread (o, chunk) sums the entries whose bits at
+// the measured qubits spell o, for the chunk-th range of the other bits.
 struct MargArgs {
     int n, m;
     int q[kMaxQubits];      // measured qubits, output bit j <-> q[j]
     int rest[kMaxQubits];   // the other qubits, ascending
     long long chunk;        // rest-values per thread
     long long nchunks;
+};
+
+// Marginal of a state (k_marg_blocks): blocks of 2^cb consecutive amplitudes.
+constexpr int kMargBlockBits = 12;
+struct MargBlocks {
+    int m, cb;
+    int nl, nh, nr;                                 // measured inside / above the block, other qubits above
+    int lq[kMargBlockBits], lo[kMargBlockBits];     // measured qubits inside, and their output bits
+    int lr[kMargBlockBits];                         // the block's other qubits
+    int hq[kMaxQubits], ho[kMaxQubits];             // measured qubits above, and their output bits
+    int rest[kMaxQubits];                           // the other qubits above
+    long long G, per;                               // workgroups per value of the measured qubits above,
+                                                    // blocks per workgroup
 };
 
 // One state's current pass inside a batched launch (continuous batching).
@@ -228,8 +241,10 @@ hipError_t sample_assign(const double* u, const long long* order, long long n, c
                          long long lastnz, double P, double* residual, SampleChunk* list, long long* nruns,
                          void* scratch, size_t scratch_bytes, hipStream_t s);
 hipError_t scatter_outcomes(const long long* order, const long long* got, long long n, long long* out, hipStream_t s);
-hipError_t launch_probs_marg(int dtype, const void* st, const MargArgs& a, double* partial, double* out,
-                             hipStream_t s, bool density = false);
+// partial: 2 G 2^m doubles unless G == 1
+hipError_t launch_marg_blocks(int dtype, const void* st, const MargBlocks& a, double* partial, double* out,
+                              hipStream_t s);
+hipError_t launch_dm_marg(int dtype, const void* st, const MargArgs& a, double* partial, double* out, hipStream_t s);
 hipError_t launch_dm_pauli(int dtype, const void* st, int n, const PauliSumArgs& p, int grid, double* partial,
                            hipStream_t s);
 
