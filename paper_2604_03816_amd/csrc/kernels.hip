@@ -1578,25 +1578,33 @@ __global__ __launch_bounds__(kThreads) void k_pauli_apply(const C* __restrict__ 
 // ------------------------------------------------------------------ sampling
 
 // Probability of entry i: |alpha_i|^2 in FP64 (state sources) or a table entry.
+__device__ __forceinline__ double prob_of(float2 v) { return (double)v.x * v.x + (double)v.y * v.y; }
+__device__ __forceinline__ double prob_of(double2 v) { return v.x * v.x + v.y * v.y; }
+
 template <int SRC>
 __device__ __forceinline__ double prob_at(const void* src, long long i)
 {
     if constexpr (SRC == 0) {
-        const float2 v = reinterpret_cast<const float2*>(src)[i];
-        return (double)v.x * v.x + (double)v.y * v.y;
+        return prob_of(reinterpret_cast<const float2*>(src)[i]);
     } else if constexpr (SRC == 1) {
-        const double2 v = reinterpret_cast<const double2*>(src)[i];
-        return v.x * v.x + v.y * v.y;
+        return prob_of(reinterpret_cast<const double2*>(src)[i]);
     } else {
         return reinterpret_cast<const double*>(src)[i];
     }
 }
 
-// Inclusive prefix sums of one chunk (2^cb entries, cb <= 12) into scan[] in LDS, in a
-// fixed order: each thread sums its run of E consecutive entries sequentially, the
+// Place of a chunk's entry i in LDS: one double of padding per 16, so that the 16 entries a
+// thread sums in order lie 17 doubles from its neighbours' (no bank conflicts).
+__device__ __host__ constexpr int scan_at(int i) { return i + (i >> 4); }
+
+// Inclusive prefix sums of one chunk (2^cb entries, cb <= 12) into scan[scan_at(i)] in LDS, in
+// a fixed order: each thread sums its run of E consecutive entries sequentially, the
 // thread totals are scanned within each wave (shuffles) and across the four waves.
 // Every chunk, in both sampling kernels, goes through this one function, so a chunk's
-// total and its last prefix sum are the same number.
+// total and its last prefix sum are the same number.  Full chunks of a state come in by
+// 16-byte loads of neighbouring lanes and go to the threads' runs through LDS (each thread
+// reading its own run from memory touched a cache line per lane: 2^16 chunks of a 28-qubit
+// complex64 state 1.38 -> 0.55 ms).
 template <int SRC>
 __device__ void chunk_scan(const void* src, long long chunk, int cb, double* scan, double* wsum)
 {
@@ -1604,12 +1612,37 @@ __device__ void chunk_scan(const void* src, long long chunk, int cb, double* sca
     const int E = size > kThreads ? size / kThreads : 1;
     const int tid = threadIdx.x;
     const long long base = chunk << cb;
+    if (SRC != 2 && size >= 2 * kThreads) {
+        constexpr int W = SRC == 0 ? 2 : 1;   // entries per 16 bytes
+        using V = typename std::conditional<SRC == 0, floatx4, doublex2>::type;
+        const V* p = reinterpret_cast<const V*>(src) + base / W;
+        for (int u0 = tid; u0 < size / W; u0 += 8 * kThreads) {
+            V v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (u0 + k * kThreads < size / W) v[k] = p[u0 + k * kThreads];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int u = u0 + k * kThreads;
+                if (u >= size / W) break;
+                if constexpr (SRC == 0) {
+                    scan[scan_at(2 * u)] = prob_of(float2{v[k].x, v[k].y});
+                    scan[scan_at(2 * u + 1)] = prob_of(float2{v[k].z, v[k].w});
+                } else if constexpr (SRC == 1) {
+                    scan[scan_at(u)] = prob_of(double2{v[k].x, v[k].y});
+                }
+            }
+        }
+    } else {
+        for (int i = tid; i < size; i += kThreads) scan[scan_at(i)] = prob_at<SRC>(src, base + i);
+    }
+    __syncthreads();
     double run = 0.0;
     const bool mine = tid * E < size;
     if (mine) {
         for (int i = 0; i < E; ++i) {
-            run += prob_at<SRC>(src, base + tid * E + i);
-            scan[tid * E + i] = run;   // prefix within the thread's run
+            run += scan[scan_at(tid * E + i)];
+            scan[scan_at(tid * E + i)] = run;   // prefix within the thread's run
         }
     }
     // inclusive scan of the thread totals: within the wave, then across waves
@@ -1626,7 +1659,7 @@ __device__ void chunk_scan(const void* src, long long chunk, int cb, double* sca
     for (int i = 0; i < w; ++i) woff += wsum[i];
     const double off = woff + x - (mine ? run : 0.0);   // exclusive offset of this thread
     if (mine) {
-        for (int i = 0; i < E; ++i) scan[tid * E + i] += off;
+        for (int i = 0; i < E; ++i) scan[scan_at(tid * E + i)] += off;
     }
     __syncthreads();
 }
@@ -1639,7 +1672,7 @@ __global__ __launch_bounds__(kThreads) void k_chunk_totals(const void* __restric
     double* scan = reinterpret_cast<double*>(smem);
     __shared__ double wsum[kThreads / 64];
     chunk_scan<SRC>(src, blockIdx.x, cb, scan, wsum);
-    if (threadIdx.x == 0) totals[blockIdx.x] = scan[(1 << cb) - 1];
+    if (threadIdx.x == 0) totals[blockIdx.x] = scan[scan_at((1 << cb) - 1)];
 }
 
 // One workgroup per listed chunk: rebuild the chunk's prefix sums, then every shot of
@@ -1658,7 +1691,7 @@ __global__ __launch_bounds__(kThreads) void k_sample_chunks(const void* __restri
     const SampleChunk c = list[blockIdx.x];
     chunk_scan<SRC>(src, c.chunk, cb, scan, wsum);
     const int size = 1 << cb;
-    const double total = scan[size - 1];
+    const double total = scan[scan_at(size - 1)];
     const double below = nextafter(total, 0.0);
     for (long long i = c.lo + threadIdx.x; i < c.hi; i += kThreads) {
         double r = residual[i];
@@ -1666,7 +1699,7 @@ __global__ __launch_bounds__(kThreads) void k_sample_chunks(const void* __restri
         int lo = 0, hi = size - 1;   // smallest k with r < scan[k]; scan[size - 1] > r
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (r < scan[mid]) hi = mid;
+            if (r < scan[scan_at(mid)]) hi = mid;
             else lo = mid + 1;
         }
         outcome[i] = (c.chunk << cb) + lo;
@@ -2190,7 +2223,7 @@ hipError_t launch_chunk_totals(int src_dtype, const void* src, int chunk_bits, l
                                hipStream_t s)
 {
     if (chunk_bits > kSampleChunkBits || nchunks <= 0) return hipErrorInvalidValue;
-    const size_t lds = sizeof(double) << chunk_bits;
+    const size_t lds = sizeof(double) * scan_at(1 << chunk_bits);
     auto k = src_dtype == 0 ? k_chunk_totals<0> : src_dtype == 1 ? k_chunk_totals<1> : k_chunk_totals<2>;
     hipLaunchKernelGGL(k, dim3((unsigned)nchunks), dim3(kThreads), lds, s, src, chunk_bits, totals);
     return hipGetLastError();
@@ -2201,7 +2234,7 @@ hipError_t launch_sample_chunks(int src_dtype, const void* src, int chunk_bits, 
 {
     if (chunk_bits > kSampleChunkBits) return hipErrorInvalidValue;
     if (nlist <= 0) return hipSuccess;
-    const size_t lds = sizeof(double) << chunk_bits;
+    const size_t lds = sizeof(double) * scan_at(1 << chunk_bits);
     auto k = src_dtype == 0 ? k_sample_chunks<0> : src_dtype == 1 ? k_sample_chunks<1> : k_sample_chunks<2>;
     hipLaunchKernelGGL(k, dim3((unsigned)nlist), dim3(kThreads), lds, s, src, chunk_bits, list, residual, outcome);
     return hipGetLastError();
