@@ -77,10 +77,13 @@ struct qsv_state_s {
         size_t dbytes = 0;
         hipEvent_t ev = nullptr;
         bool pending = false;
+        bool shared = false;   // h and d are parts of the state's tab_block
     };
     static constexpr int kTabSlots = 8;
     TabSlot tab[kTabSlots];
     int tab_next = 0;
+    unsigned char* tab_block_h = nullptr;   // every slot's first blocks in one allocation each
+    unsigned char* tab_block_d = nullptr;   // (reserve_tabs)
 };
 
 struct qsv_plan_s {
@@ -575,6 +578,45 @@ qsv_status pauli_sum_apply(qsv_state s, const void* src, void* dst, const std::v
     return QSV_OK;
 }
 
+// Bytes of a plan's tables in an arena slot, and where each starts.
+struct TableLayout {
+    size_t ops, pool, ipool, apool, total;
+};
+
+TableLayout table_layout(const HostPlan& hp)
+{
+    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    TableLayout t;
+    t.ops = 0;
+    t.pool = t.ops + al(hp.ops.size() * sizeof(DevOp));
+    t.ipool = t.pool + al(hp.pool.size() * elem_bytes(hp.dtype));
+    t.apool = t.ipool + al(hp.ipool.size() * sizeof(int));
+    t.total = std::max<size_t>(t.apool + al(hp.apool.size() * sizeof(float)), 256);
+    return t;
+}
+
+// Gives each of a fresh state's arena slots `bytes` out of one pinned and one device
+// allocation (a call that uses all of them in turn paid for eight of each: pinned ones take
+// about 70 us and 90 us more to free).
+qsv_status reserve_tabs(qsv_state s, size_t bytes)
+{
+    bytes = (bytes + 255) & ~(size_t)255;
+    QSV_HIP(hipHostMalloc((void**)&s->tab_block_h, bytes * qsv_state_s::kTabSlots, hipHostMallocDefault));
+    if (hipMalloc((void**)&s->tab_block_d, bytes * qsv_state_s::kTabSlots) != hipSuccess) {
+        (void)hipGetLastError();
+        s->tab_block_d = nullptr;
+        return fail(QSV_E_OOM, "plan table allocation failed");
+    }
+    for (int i = 0; i < qsv_state_s::kTabSlots; ++i) {
+        qsv_state_s::TabSlot& ts = s->tab[i];
+        ts.h = s->tab_block_h + (size_t)i * bytes;
+        ts.d = s->tab_block_d + (size_t)i * bytes;
+        ts.hbytes = ts.dbytes = bytes;
+        ts.shared = true;
+    }
+    return QSV_OK;
+}
+
 // Enqueues every pass of a host plan on the state's stream, its tables copied into the
 // state's next arena slot: one asynchronous copy, no allocation once the slot is large
 // enough, and no wait for the device unless the passes of the application kTabSlots
@@ -589,13 +631,8 @@ qsv_status enqueue_plan(qsv_state s, const HostPlan& hp, qsv_state s2 = nullptr,
         if (s2) QSV_HIP(launch_init_zero(s2->dtype, s2->buf, 1ll << s2->n, s2->stream));
         return QSV_OK;
     }
-    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t eb = elem_bytes(hp.dtype);
-    const size_t o_ops = 0;
-    const size_t o_pool = o_ops + al(hp.ops.size() * sizeof(DevOp));
-    const size_t o_ipool = o_pool + al(hp.pool.size() * eb);
-    const size_t o_apool = o_ipool + al(hp.ipool.size() * sizeof(int));
-    const size_t total = std::max<size_t>(o_apool + al(hp.apool.size() * sizeof(float)), 256);
+    const TableLayout tl = table_layout(hp);
+    const size_t o_ops = tl.ops, o_pool = tl.pool, o_ipool = tl.ipool, o_apool = tl.apool, total = tl.total;
     qsv_state_s::TabSlot& ts = s->tab[s->tab_next];
     s->tab_next = (s->tab_next + 1) % qsv_state_s::kTabSlots;
     if (ts.pending) {   // the passes that read this slot's tables (and so its copy) are done
@@ -603,6 +640,11 @@ qsv_status enqueue_plan(qsv_state s, const HostPlan& hp, qsv_state s2 = nullptr,
         ts.pending = false;
     }
     if (!ts.ev) QSV_HIP(hipEventCreateWithFlags(&ts.ev, hipEventDisableTiming));
+    if (ts.shared && (total > ts.hbytes || total > ts.dbytes)) {   // outgrown: blocks of its own from here on
+        ts.h = ts.d = nullptr;
+        ts.hbytes = ts.dbytes = 0;
+        ts.shared = false;
+    }
     if (total > ts.hbytes) {
         if (ts.h) QSV_HIP(hipHostFree(ts.h));
         ts.h = nullptr;
@@ -691,10 +733,12 @@ qsv_status qsv_free(qsv_state s)
     if (s->d_work) (void)hipFree(s->d_work);
     if (s->h_work) (void)hipHostFree(s->h_work);
     for (qsv_state_s::TabSlot& ts : s->tab) {
-        if (ts.d) (void)hipFree(ts.d);
-        if (ts.h) (void)hipHostFree(ts.h);
+        if (ts.d && !ts.shared) (void)hipFree(ts.d);
+        if (ts.h && !ts.shared) (void)hipHostFree(ts.h);
         if (ts.ev) (void)hipEventDestroy(ts.ev);
     }
+    if (s->tab_block_d) (void)hipFree(s->tab_block_d);
+    if (s->tab_block_h) (void)hipHostFree(s->tab_block_h);
     delete s;
     return QSV_OK;
 }
@@ -1225,8 +1269,9 @@ qsv_status qsv_sample(qsv_state s, const int* qubits, int m, const double* unifo
     } else if (m != n) {
         return fail(QSV_E_ARG, "qubits == NULL measures all n qubits (m must be n)");
     }
-    for (long long i = 0; i < shots; ++i)
-        if (!(uniforms[i] >= 0.0 && uniforms[i] < 1.0)) return fail(QSV_E_ARG, "uniforms must lie in [0, 1)");
+    bool bad = false;   // (no early exit: the loop runs on vectors)
+    for (long long i = 0; i < shots; ++i) bad |= !(uniforms[i] >= 0.0) | !(uniforms[i] < 1.0);
+    if (bad) return fail(QSV_E_ARG, "uniforms must lie in [0, 1)");
     if (!identity && m > 26) return fail(QSV_E_UNSUPPORTED, "marginal sampling over more than 26 qubits");
     if (shots == 0) return QSV_OK;
     DeviceGuard g(s->device);
@@ -1738,6 +1783,9 @@ qsv_status qsv_adjoint_grad(int n, qsv_dtype dtype, const qsv_op* ops, size_t n_
         if (!undo[li].empty() &&
             !make_plan(n, dtype, gates_of(undo[li], th_generic.data(), true), default_opts(dtype), undo_tmpl[li], err))
             st = fail(QSV_E_ARG, err);
+    size_t tab_bytes = table_layout(fwd_tmpl).total;
+    for (const HostPlan& t : undo_tmpl) tab_bytes = std::max(tab_bytes, table_layout(t).total);
+    for (int p = 0; p < pairs && st == QSV_OK; ++p) st = reserve_tabs(pair[p].phi, tab_bytes);
     // a template refreshed with a vector's gates, or a plan made for them
     auto plan_for = [&](const HostPlan& tmpl, const std::vector<InGate>& g, HostPlan& hp) -> qsv_status {
         hp = tmpl;
@@ -1751,6 +1799,7 @@ qsv_status qsv_adjoint_grad(int n, qsv_dtype dtype, const qsv_op* ops, size_t n_
         if (!n_ops) return QSV_OK;
         return plan_for(fwd_tmpl, gates_of(all_ops, params + (size_t)b * P, false), hp);
     };
+    HostPlan undo_plan;   // one plan's storage for every undo step (its tables are copied when enqueued)
     // enqueue vector b on pair pr: forward, energy, co-state, reverse sweep, partials copy
     auto enqueue_vector = [&](int b, Pair& pr, const HostPlan& fwd) -> qsv_status {
         qsv_state phi = pr.phi, lam = pr.lam;
@@ -1770,7 +1819,7 @@ qsv_status qsv_adjoint_grad(int n, qsv_dtype dtype, const qsv_op* ops, size_t n_
         // one plan applied to both states), then the layer's Im <lambda|P_j|phi>
         for (size_t li = 0; li < layers.size(); ++li) {
             if (!undo[li].empty()) {
-                HostPlan hp;
+                HostPlan& hp = undo_plan;
                 if ((s2 = plan_for(undo_tmpl[li], gates_of(undo[li], th, true), hp)) != QSV_OK) return s2;
                 if ((s2 = enqueue_plan(phi, hp, lam)) != QSV_OK) return s2;   // one launch per pass, both states
             }

@@ -37,6 +37,7 @@
 #include <cmath>
 #include <cstring>
 #include <queue>
+#include <unordered_map>
 
 namespace qsv {
 
@@ -95,37 +96,59 @@ bool plan_opts_from(int dtype, const qsv_plan_opts* pub, PlanOpts& o, std::strin
     return true;
 }
 
-int classify(const std::vector<cd>& m, int k)
+namespace {
+
+bool zero(const cd& v) { return v.real() == 0 && v.imag() == 0; }
+
+// Kind of a matrix and, as local bits, the targets it is not diagonal on, in one look at its
+// nonzero entries.
+int structure(const cd* m, int k, int& off)
 {
     const int d = 1 << k;
-    bool diag = true;
-    for (int r = 0; r < d && diag; ++r)
-        for (int c = 0; c < d; ++c)
-            if (r != c && m[(size_t)r * d + c] != cd(0, 0)) { diag = false; break; }
-    if (diag) return OP_DIAG;
-    std::vector<int> colcount(d, 0);
+    int flips = 0, perm = 1;
+    unsigned cols = 0;
     for (int r = 0; r < d; ++r) {
         int cnt = 0;
-        for (int c = 0; c < d; ++c)
-            if (m[(size_t)r * d + c] != cd(0, 0)) { ++cnt; ++colcount[c]; }
-        if (cnt != 1) return OP_DENSE;
+        const cd* row = m + (size_t)r * d;
+        for (int c = 0; c < d; ++c) {
+            if (zero(row[c])) continue;
+            flips |= r ^ c;
+            ++cnt;
+            if ((cols >> c) & 1) perm = 0;
+            cols |= 1u << c;
+        }
+        if (cnt != 1) perm = 0;
+        if (!perm && flips == d - 1) break;
     }
-    for (int c = 0; c < d; ++c)
-        if (colcount[c] != 1) return OP_DENSE;
-    return OP_PERM;
+    off = flips;
+    return flips == 0 ? OP_DIAG : perm ? OP_PERM : OP_DENSE;
+}
+
+// Sets g's kind and its diagonal qubits from its matrix.
+void inspect(FGate& g)
+{
+    int off = 0;
+    g.kind = structure(g.m.vec().data(), g.k, off);
+    g.dq = 0;
+    for (int j = 0; j < g.k; ++j)
+        if (!((off >> j) & 1)) g.dq |= 1ull << g.q[j];
+}
+
+}  // namespace
+
+int classify(const std::vector<cd>& m, int k)
+{
+    int off = 0;
+    return structure(m.data(), k, off);
 }
 
 unsigned long long diag_qubit_mask(const FGate& g)
 {
-    const int d = 1 << g.k;
+    int off = 0;
+    structure(g.m.vec().data(), g.k, off);
     unsigned long long dq = 0;
-    for (int j = 0; j < g.k; ++j) {
-        bool diag = true;
-        for (int r = 0; r < d && diag; ++r)
-            for (int c = 0; c < d; ++c)
-                if (((r ^ c) >> j) & 1 && g.m[(size_t)r * d + c] != cd(0, 0)) { diag = false; break; }
-        if (diag) dq |= 1ull << g.q[j];
-    }
+    for (int j = 0; j < g.k; ++j)
+        if (!((off >> j) & 1)) dq |= 1ull << g.q[j];
     return dq;
 }
 
@@ -174,12 +197,12 @@ bool mfma_eligible(const FGate& g, const PlanOpts& o)
 
 namespace {
 
-bool is_identity(const FGate& g)
+bool is_identity(const FGate& g)   // (its kind is set)
 {
+    if (g.kind != OP_DIAG) return false;
     const int d = 1 << g.k;
     for (int r = 0; r < d; ++r)
-        for (int c = 0; c < d; ++c)
-            if (g.m[(size_t)r * d + c] != (r == c ? cd(1, 0) : cd(0, 0))) return false;
+        if (g.m[(size_t)r * d + r] != cd(1, 0)) return false;
     return true;
 }
 
@@ -212,38 +235,116 @@ std::vector<cd> embed(const std::vector<cd>& a, const int* qa, int ka, const int
     return e;
 }
 
-// E(v) . B for a dq x dq matrix B over the ascending qubit list Q, without forming E(v):
-// row r of the product mixes the rows of B that differ from r only in v's bits, in
-// ascending order: the sums of the plain product E(v) B, term for term (zero entries
-// of E(v) skipped).
-std::vector<cd> apply_left(const std::vector<cd>& vm, const int* qv, int kv, const int* Q, int kq,
-                           const std::vector<cd>& B)
+// a += w b, the plain product (std::complex's checks for NaN: every entry here is finite)
+inline void madd(cd& a, const cd& w, const cd& b)
 {
-    const int dq = 1 << kq, dv = 1 << kv;
-    int pos[kMaxK], vmask = 0;
-    for (int j = 0; j < kv; ++j) {
-        int p = 0;
-        while (Q[p] != qv[j]) ++p;
-        pos[j] = p;
-        vmask |= 1 << p;
+    a = cd(a.real() + (w.real() * b.real() - w.imag() * b.imag()),
+           a.imag() + (w.real() * b.imag() + w.imag() * b.real()));
+}
+
+// out[b] = sum_t w[t] in[t][b] in ascending t from zero, for an even count of columns: madd's
+// products and sums, on vectors of V / 2 complex numbers held in registers over t
+// ((re, im) * w.re plus (im, re) * (-w.im, w.im)).
+template <typename V>
+__attribute__((always_inline)) inline void mix_rows_v(double* out, const cd* w, const double* const* in, int terms,
+                                                      int count)
+{
+    constexpr int L = sizeof(V) / sizeof(double), U = 4;
+    for (int b = 0; b < 2 * count; b += L * U) {
+        const int nu = std::min(U, (2 * count - b) / L);
+        V acc[U];
+        for (int u = 0; u < U; ++u) acc[u] = V{};
+        for (int t = 0; t < terms; ++t) {
+            V wr, wi;
+            for (int l = 0; l < L; ++l) {
+                wr[l] = w[t].real();
+                wi[l] = (l & 1) ? w[t].imag() : -w[t].imag();
+            }
+            for (int u = 0; u < U; ++u) {
+                if (u >= nu) break;
+                V x;
+                std::memcpy(&x, in[t] + b + u * L, sizeof(V));
+                V y;
+                for (int l = 0; l < L; ++l) y[l] = x[l ^ 1];
+                acc[u] += x * wr + y * wi;
+            }
+        }
+        for (int u = 0; u < nu; ++u) std::memcpy(out + b + u * L, &acc[u], sizeof(V));
     }
-    int spread[1 << kMaxK];
-    for (int a = 0; a < dv; ++a) {
-        int x = 0;
-        for (int j = 0; j < kv; ++j) x |= ((a >> j) & 1) << pos[j];
-        spread[a] = x;
-    }
+}
+
+typedef double v2d __attribute__((vector_size(16)));
+typedef double v4d __attribute__((vector_size(32)));
+
+__attribute__((target("avx2"))) void mix_rows_avx2(double* out, const cd* w, const double* const* in, int terms,
+                                                   int count)
+{
+    mix_rows_v<v4d>(out, w, in, terms, count);
+}
+
+void mix_rows(double* out, const cd* w, const double* const* in, int terms, int count)
+{
+    static const bool avx2 = __builtin_cpu_supports("avx2");
+    if (avx2) mix_rows_avx2(out, w, in, terms, count);
+    else mix_rows_v<v2d>(out, w, in, terms, count);
+}
+
+// E(v) . E(u) over the ascending qubit list Q without forming either embedding: row r of
+// the product mixes the rows of E(u) that differ from r only in v's bits, in ascending
+// order, and such a row has 2^ku entries: the sums of the plain product, term for term
+// (zero entries of either factor's embedding skipped).
+std::vector<cd> embedded_product(const FGate& v, const FGate& u, const int* Q, int kq)
+{
+    const int dq = 1 << kq, dv = 1 << v.k, du = 1 << u.k;
+    int vspread[1 << kMaxK], uspread[1 << kMaxK], vsub[1 << kMaxK], usub[1 << kMaxK];
+    auto lay = [&](const FGate& g, int* spread, int* sub) {   // returns g's bits in Q
+        int pos[kMaxK], mask = 0;
+        for (int j = 0; j < g.k; ++j) {
+            int p = 0;
+            while (Q[p] != g.q[j]) ++p;
+            pos[j] = p;
+            mask |= 1 << p;
+        }
+        for (int a = 0; a < (1 << g.k); ++a) {
+            int x = 0;
+            for (int j = 0; j < g.k; ++j) x |= ((a >> j) & 1) << pos[j];
+            spread[a] = x;
+        }
+        for (int r = 0; r < dq; ++r) {
+            int x = 0;
+            for (int j = 0; j < g.k; ++j) x |= ((r >> pos[j]) & 1) << j;
+            sub[r] = x;
+        }
+        return mask;
+    };
+    const int vmask = lay(v, vspread, vsub), umask = lay(u, uspread, usub);
     std::vector<cd> C((size_t)dq * dq, cd(0, 0));
+    if (v.kind == OP_DIAG && u.kind == OP_DIAG) {
+        for (int r = 0; r < dq; ++r)
+            madd(C[(size_t)r * dq + r], v.m[(size_t)vsub[r] * dv + vsub[r]], u.m[(size_t)usub[r] * du + usub[r]]);
+        return C;
+    }
     for (int r = 0; r < dq; ++r) {
-        int ra = 0;
-        for (int j = 0; j < kv; ++j) ra |= ((r >> pos[j]) & 1) << j;
-        const int base = r & ~vmask;
+        const cd* vrow = &v.m[(size_t)vsub[r] * dv];
         cd* out = &C[(size_t)r * dq];
+        if (du == dq) {   // u spans Q: whole rows
+            cd w[1 << kMaxK];
+            const double* in[1 << kMaxK];
+            int terms = 0;
+            for (int a = 0; a < dv; ++a) {
+                if (zero(vrow[a])) continue;
+                w[terms] = vrow[a];
+                in[terms++] = reinterpret_cast<const double*>(&u.m[(size_t)((r & ~vmask) | vspread[a]) * du]);
+            }
+            mix_rows(reinterpret_cast<double*>(out), w, in, terms, dq);
+            continue;
+        }
         for (int a = 0; a < dv; ++a) {
-            const cd w = vm[(size_t)ra * dv + a];
-            if (w == cd(0, 0)) continue;
-            const cd* in = &B[(size_t)(base | spread[a]) * dq];
-            for (int c = 0; c < dq; ++c) out[c] += w * in[c];
+            const cd w = vrow[a];
+            if (zero(w)) continue;
+            const int ri = (r & ~vmask) | vspread[a], keep = ri & ~umask;
+            const cd* urow = &u.m[(size_t)usub[ri] * du];
+            for (int b = 0; b < du; ++b) madd(out[keep | uspread[b]], w, urow[b]);
         }
     }
     return C;
@@ -264,11 +365,12 @@ FGate canonical(const InGate& g, int index)
         for (int j = 0; j < g.k; ++j) o |= ((r >> j) & 1) << order[j];
         return o;
     };
-    f.m.assign((size_t)d * d, cd(0, 0));
+    std::vector<cd> m((size_t)d * d);
     for (int r = 0; r < d; ++r)
-        for (int c = 0; c < d; ++c) f.m[(size_t)r * d + c] = g.m[(size_t)remap(r) * d + remap(c)];
-    f.kind = classify(f.m, f.k);
-    f.dq = diag_qubit_mask(f);
+        for (int c = 0; c < d; ++c) m[(size_t)r * d + c] = g.m[(size_t)remap(r) * d + remap(c)];
+    f.m = std::move(m);
+    f.id = index;
+    inspect(f);
     f.first = index;
     f.mem.assign(1, index);
     return f;
@@ -329,8 +431,21 @@ std::vector<int> topo_order(const std::vector<Node>& nodes)
     return order;
 }
 
-FGate fuse_pair(const FGate& u, const FGate& v, int kmax, bool& ok)
+// Products formed while a plan is made, by their factors' ids: the planner fuses a circuit
+// twice (on two DAGs) and most merges are the same.
+struct Products {
+    std::unordered_map<unsigned long long, FGate> made;
+    int next = 0;   // id of the next product
+};
+
+FGate fuse_pair(const FGate& u, const FGate& v, int kmax, bool& ok, Products& pr)
 {
+    const unsigned long long key = ((unsigned long long)(unsigned)u.id << 32) | (unsigned)v.id;
+    const auto hit = pr.made.find(key);
+    if (hit != pr.made.end()) {
+        ok = hit->second.k <= kmax;
+        return hit->second;
+    }
     int Q[2 * kMaxK], kq = 0;
     for (int j = 0; j < u.k; ++j) Q[kq++] = u.q[j];
     for (int j = 0; j < v.k; ++j) {
@@ -345,17 +460,19 @@ FGate fuse_pair(const FGate& u, const FGate& v, int kmax, bool& ok)
     f.k = kq;
     for (int j = 0; j < kq; ++j) f.q[j] = Q[j];
     // Eq. 9: U_fused = U_v . U_u (u applied first)
-    f.m = apply_left(v.m, v.q, v.k, Q, kq, embed(u.m, u.q, u.k, Q, kq));
-    f.kind = classify(f.m, kq);
-    f.dq = diag_qubit_mask(f);
+    f.m = embedded_product(v, u, Q, kq);
+    inspect(f);
+    f.id = pr.next++;
     f.first = std::min(u.first, v.first);
     f.members = u.members + v.members;
-    f.mem = u.mem;
+    f.mem.reserve(u.mem.size() + v.mem.size());
+    f.mem.insert(f.mem.end(), u.mem.begin(), u.mem.end());
     f.mem.insert(f.mem.end(), v.mem.begin(), v.mem.end());
+    pr.made.emplace(key, f);
     return f;
 }
 
-void run_fusion(std::vector<Node>& nodes, const PlanOpts& o)
+void run_fusion(std::vector<Node>& nodes, const PlanOpts& o, Products& pr)
 {
     const int N = (int)nodes.size();
     std::vector<int> pos(N, 0);
@@ -414,7 +531,7 @@ void run_fusion(std::vector<Node>& nodes, const PlanOpts& o)
                     }
                 }
                 bool ok = false;
-                FGate f = fuse_pair(U.g, V.g, o.kmax, ok);
+                FGate f = fuse_pair(U.g, V.g, o.kmax, ok, pr);
                 if (!ok) continue;
                 // (5) arithmetic does not grow beyond what the merge saves
                 if (o.cost_aware > 0 && op_cost(f, o) > op_cost(U.g, o) + op_cost(V.g, o) + o.sigma) continue;
@@ -534,7 +651,7 @@ void relink(std::vector<int>& lst, int from, int to)
     }
 }
 
-std::vector<FGate> fuse_commuting(const std::vector<FGate>& gates, int n, const PlanOpts& o, bool diag_only)
+std::vector<FGate> fuse_commuting(std::vector<FGate> gates, int n, const PlanOpts& o, bool diag_only, Products& pr)
 {
     const int G = (int)gates.size();
     std::vector<CNode> N(G);
@@ -542,11 +659,12 @@ std::vector<FGate> fuse_commuting(const std::vector<FGate>& gates, int n, const 
         std::vector<int> last_nd(n, -1);
         std::vector<std::vector<int>> run(n);
         for (int i = 0; i < G; ++i) {
-            N[i].g = gates[i];
-            N[i].qm = qubit_mask(gates[i]);
-            for (int j = 0; j < gates[i].k; ++j) {
-                const int q = gates[i].q[j];
-                if ((gates[i].dq >> q) & 1) {
+            N[i].g = std::move(gates[i]);
+            const FGate& gi = N[i].g;
+            N[i].qm = qubit_mask(gi);
+            for (int j = 0; j < gi.k; ++j) {
+                const int q = gi.q[j];
+                if ((gi.dq >> q) & 1) {
                     add_edge(N, last_nd[q], i);
                     run[q].push_back(i);
                 } else {
@@ -620,7 +738,7 @@ std::vector<FGate> fuse_commuting(const std::vector<FGate>& gates, int n, const 
                     if (op_cost(probe, o) > op_cost(U.g, o) + op_cost(V.g, o) + o.sigma) continue;
                 }
                 bool ok = false;
-                FGate f = fuse_pair(U.g, V.g, o.kmax, ok);
+                FGate f = fuse_pair(U.g, V.g, o.kmax, ok, pr);
                 if (!ok) continue;
                 if (o.cost_aware > 0 && op_cost(f, o) > op_cost(U.g, o) + op_cost(V.g, o) + o.sigma) continue;
                 // merge v into u: u takes v's edges
@@ -646,7 +764,7 @@ std::vector<FGate> fuse_commuting(const std::vector<FGate>& gates, int n, const 
         }
     }
     std::vector<FGate> out;
-    for (const int v : topo_order_dag(N)) out.push_back(N[v].g);
+    for (const int v : topo_order_dag(N)) out.push_back(std::move(N[v].g));
     return out;
 }
 
@@ -662,10 +780,34 @@ int operand_floats(int dtype, int k)
 // tile is exactly `A0` and only ops inside it (or diagonal ops) join.  An op joins when
 // none of its qubits is blocked by an earlier deferred op it may not commute with, the
 // tile holds it and the pass's arithmetic budget allows.
-PassPlan build_pass(int n, const std::vector<FGate>& fused, const std::vector<char>& done, const PlanOpts& o,
+// What scheduling asks of an op.
+struct OpInfo {
+    unsigned long long gm, gd;   // its qubits; those it is diagonal on (commutation-aware plans)
+    double cost;                 // op_cost plus the per-op overhead
+    int floats;                  // operand or diagonal-table floats to stage
+    bool matrix, diag;           // on matrix cores; diagonal
+};
+
+std::vector<OpInfo> op_infos(const std::vector<FGate>& fused, const PlanOpts& o)
+{
+    std::vector<OpInfo> v;
+    v.reserve(fused.size());
+    for (const FGate& g : fused) {
+        OpInfo i;
+        i.gm = qubit_mask(g);
+        i.gd = o.commute ? g.dq : 0;
+        i.cost = op_cost(g, o) + o.sigma;
+        i.matrix = mfma_eligible(g, o);
+        i.diag = g.kind == OP_DIAG;
+        i.floats = i.matrix ? operand_floats(o.fp32_mfma ? 0 : 1, g.k) : i.diag ? o.amp_floats << g.k : 0;
+        v.push_back(i);
+    }
+    return v;
+}
+
+PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int>& todo, const PlanOpts& o,
                     int m, int L, bool whole, unsigned long long A0, bool grow)
 {
-    const int F = (int)fused.size();
     const unsigned long long all = (n >= 64) ? ~0ull : ((1ull << n) - 1);
     PassPlan pp;
     int Lp = L;   // low qubits kept in this pass's tile
@@ -682,23 +824,23 @@ PassPlan build_pass(int n, const std::vector<FGate>& fused, const std::vector<ch
     };
     double budget = o.pass_budget;
     int afl = 0;   // operand floats staged so far, as the device tables stage them
-    for (int i = 0; i < F; ++i) {
-        if (done[i]) continue;
-        const FGate& g = fused[i];
-        unsigned long long gm = 0;
-        for (int j = 0; j < g.k; ++j) gm |= 1ull << g.q[j];
-        const unsigned long long gd = o.commute ? g.dq : 0;
-        if ((gm & blocked) || (gm & ~gd & blocked_d)) { defer(gm, gd); continue; }
-        const double c = op_cost(g, o) + o.sigma;
+    for (const int i : todo) {
+        const OpInfo& g = ops[(size_t)i];
+        const unsigned long long gm = g.gm, gd = g.gd;
+        if ((gm & blocked) || (gm & ~gd & blocked_d)) {
+            defer(gm, gd);
+            if ((blocked & all) == all) break;
+            continue;
+        }
+        const double c = g.cost;
         const bool limit_ops = o.max_ops_per_pass > 0 && (int)pp.ops.size() >= o.max_ops_per_pass;
         // a matrix-core op whose operand no longer fits the pass's staged block waits for the
         // next pass: reading it from global memory in the op phase would wait for the next
         // tile's loads (diagonal tables are staged too, where they fit)
-        const bool mf = mfma_eligible(g, o);
-        const int af = mf ? operand_floats(o.fp32_mfma ? 0 : 1, g.k) : g.kind == OP_DIAG ? o.amp_floats << g.k : 0;
-        const bool fits_operands = whole || !mf || ((afl + 3) & ~3) + af <= o.stage_floats || pp.ops.empty();
+        const int af = g.floats;
+        const bool fits_operands = whole || !g.matrix || ((afl + 3) & ~3) + af <= o.stage_floats || pp.ops.empty();
         const bool fits_budget = whole || o.pass_budget < 0 || c <= budget || pp.ops.empty();
-        unsigned long long nA = (g.kind == OP_DIAG) ? A : (A | gm);
+        unsigned long long nA = g.diag ? A : (A | gm);
         if (grow && pp.ops.empty() && __builtin_popcountll(nA) > m) {
             // a gate wider than the tile's free slots opens a pass with fewer low qubits
             while (Lp > 0 && __builtin_popcountll(gm | ((1ull << Lp) - 1)) > m) --Lp;
@@ -732,7 +874,7 @@ PassPlan build_pass(int n, const std::vector<FGate>& fused, const std::vector<ch
 // op moves back past every op it commutes with to the nearest earlier diagonal op whose
 // union with it stays within the width bound, and the two become one.  Moving it back
 // is exact: it commutes with every op it passes.
-void merge_diagonals(std::vector<FGate>& ops, int kmax)
+void merge_diagonals(std::vector<FGate>& ops, int kmax, Products& pr)
 {
     constexpr int kWindow = 64;   // earlier ops examined per diagonal op
     std::vector<FGate> out;
@@ -751,7 +893,7 @@ void merge_diagonals(std::vector<FGate>& ops, int kmax)
             }
             if (hit >= 0) {
                 bool ok = false;
-                FGate f = fuse_pair(out[(size_t)hit], v, kmax, ok);
+                FGate f = fuse_pair(out[(size_t)hit], v, kmax, ok, pr);
                 if (ok && f.kind == OP_DIAG) {
                     out[(size_t)hit] = std::move(f);
                     continue;
@@ -817,22 +959,24 @@ bool schedule_passes(int n, const std::vector<FGate>& fused, const PlanOpts& o, 
     const int L = std::min(o.low_qubits, m);
     const unsigned long long low = (L >= 64) ? ~0ull : ((1ull << L) - 1);
     const bool windows = !whole && o.fuse == 1 && n > m && m > L;
+    const std::vector<OpInfo> ops = op_infos(fused, o);
+    std::vector<int> todo(F);
+    for (int i = 0; i < F; ++i) todo[i] = i;
     std::vector<char> done(F, 0);
-    int remaining = F;
-    while (remaining > 0) {
-        PassPlan best = build_pass(n, fused, done, o, m, L, whole, low, true);
+    while (!todo.empty()) {
+        PassPlan best = build_pass(n, ops, todo, o, m, L, whole, low, true);
         if (windows) {
             const int w = m - L;
             for (int a = L; a + w <= n; ++a) {
                 const unsigned long long A0 = low | (((1ull << w) - 1) << a);
-                PassPlan c = build_pass(n, fused, done, o, m, L, whole, A0, false);
+                PassPlan c = build_pass(n, ops, todo, o, m, L, whole, A0, false);
                 if (c.cost > best.cost) best = std::move(c);
             }
         }
         if (best.ops.empty()) { err = "internal: a gate does not fit any tile"; return false; }
         for (const int i : best.ops) done[i] = 1;
+        todo.erase(std::remove_if(todo.begin(), todo.end(), [&](int i) { return done[(size_t)i] != 0; }), todo.end());
         pair_up(fused, o, best);
-        remaining -= (int)best.ops.size();
         passes.push_back(std::move(best));
     }
     return true;
@@ -912,17 +1056,25 @@ void push_operand(std::vector<float>& out, int dtype, const std::vector<cd>& M, 
 {
     const size_t at = out.size();
     out.resize(at + (dtype == 0 ? 512 : 1024));
-    for (int lane = 0; lane < 64; ++lane)
-        for (int j = 0; j < 4; ++j) {
-            const cd v = M[(size_t)row(lane & 15) * 16 + col(lane >> 4, j)];
-            if (dtype == 0) {
-                const float w[2] = {(float)v.real(), (float)v.imag()};
-                std::memcpy(&out[at + (size_t)((j >> 1) * 64 + lane) * 4 + 2 * (j & 1)], w, 8);
-            } else {
-                const double w[2] = {v.real(), v.imag()};
-                std::memcpy(&out[at + (size_t)(j * 64 + lane) * 4], w, 16);
+    int cols[4][4];
+    for (int q = 0; q < 4; ++q)
+        for (int j = 0; j < 4; ++j) cols[q][j] = col(q, j);
+    for (int l = 0; l < 16; ++l) {
+        const cd* mrow = &M[(size_t)row(l) * 16];
+        for (int q = 0; q < 4; ++q)
+            for (int j = 0; j < 4; ++j) {
+                const cd& v = mrow[cols[q][j]];
+                const int lane = 16 * q + l;
+                if (dtype == 0) {
+                    float* w = &out[at + (size_t)((j >> 1) * 64 + lane) * 4 + 2 * (j & 1)];
+                    w[0] = (float)v.real();
+                    w[1] = (float)v.imag();
+                } else {
+                    const double w[2] = {v.real(), v.imag()};
+                    std::memcpy(&out[at + (size_t)(j * 64 + lane) * 4], w, 16);
+                }
             }
-        }
+    }
 }
 
 // Operand and offset tables of the matrix-core op d (matrix M over tile bits d.lpos), or of
@@ -1023,18 +1175,19 @@ void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2
         if (!((used >> b) & 1)) pack(d.bbit, nb++, bit(b));
 }
 
-// The matrix of P.ops[oi] (gate g) as the kernels take it: a complex64 3-qubit op gains
-// one more tile qubit, not in `avoid`, as identity; its descriptor and pool matrix follow.
+// A complex64 3-qubit op P.ops[oi] (gate g) gains one more tile qubit, not in `avoid`, as
+// identity: returns its 4-qubit matrix and updates its descriptor and pool matrix.  Other
+// ops: an empty matrix.
 std::vector<cd> widen(HostPlan& P, int oi, const FGate& g, const PassPlan& pp, unsigned long long& avoid)
 {
     DevOp& d = P.ops[(size_t)oi];
-    if (!(P.dtype == 0 && g.k == 3)) return g.m;
+    if (!(P.dtype == 0 && g.k == 3)) return {};
     int Q[4] = {g.q[0], g.q[1], g.q[2], -1};
     for (const int b : pp.active)
         if (!((avoid >> b) & 1)) { Q[3] = b; break; }
     avoid |= 1ull << Q[3];
     std::sort(Q, Q + 4);
-    std::vector<cd> M = embed(g.m, g.q, 3, Q, 4);
+    std::vector<cd> M = embed(g.m.vec(), g.q, 3, Q, 4);
     d.k = 4;
     for (int j = 0; j < 4; ++j) {
         d.gbit[j] = Q[j];
@@ -1099,7 +1252,7 @@ void build_device_tables(HostPlan& P)
             d.off = (int)P.pool.size();
             d.aoff = d.goff = -1;
             if (g.kind == OP_DENSE) {
-                P.pool.insert(P.pool.end(), g.m.begin(), g.m.end());
+                P.pool.insert(P.pool.end(), g.m.vec().begin(), g.m.vec().end());
                 ++P.dense_ops;
                 // matrix cores need 16 groups per block; complex64 3-qubit ops are run as
                 // 4-qubit ones on one more tile bit
@@ -1155,8 +1308,8 @@ void build_device_tables(HostPlan& P)
         auto gate_of = [&](int oi) -> const FGate& { return P.fused[(size_t)pp.ops[(size_t)(oi - a.op_begin)]]; };
         struct Step {   // one op or one pair
             int oi, oj;
-            std::vector<cd> m1, m2;
-            unsigned bits;   // its tile bits
+            std::vector<cd> w1, w2;   // widened matrices (empty: the gate's own)
+            unsigned bits;            // its tile bits
         };
         std::vector<Step> steps;
         for (size_t i = 0; i < matrix_ops.size(); ++i) {
@@ -1168,9 +1321,9 @@ void build_device_tables(HostPlan& P)
             if (oj == st.oi + 1 && pairable(g, o) && pairable(gate_of(oj), o) && !(qubit_mask(g) & qubit_mask(gate_of(oj))))
                 st.oj = oj;
             unsigned long long avoid = qubit_mask(g) | (st.oj >= 0 ? qubit_mask(gate_of(st.oj)) : 0);
-            st.m1 = widen(P, st.oi, g, pp, avoid);
+            st.w1 = widen(P, st.oi, g, pp, avoid);
             if (st.oj >= 0) {
-                st.m2 = widen(P, st.oj, gate_of(st.oj), pp, avoid);
+                st.w2 = widen(P, st.oj, gate_of(st.oj), pp, avoid);
                 ++i;
             }
             st.bits = 0;
@@ -1193,7 +1346,9 @@ void build_device_tables(HostPlan& P)
             for (size_t x = i; x < e; ++x) {
                 Step& st = steps[x];
                 DevOp* d2 = st.oj >= 0 ? &P.ops[(size_t)st.oj] : nullptr;
-                mfma_tables(dtype, a.m, P.ops[(size_t)st.oi], st.m1, d2, d2 ? &st.m2 : nullptr, wave, P.apool);
+                const std::vector<cd>* m2 = !d2 ? nullptr : st.w2.empty() ? &gate_of(st.oj).m.vec() : &st.w2;
+                mfma_tables(dtype, a.m, P.ops[(size_t)st.oi], st.w1.empty() ? gate_of(st.oi).m.vec() : st.w1, d2, m2, wave,
+                            P.apool);
                 P.ops[(size_t)st.oi].nosync = nw == 2 && a.m >= 10 && x + 1 < e;
             }
             i = e;
@@ -1243,9 +1398,15 @@ bool make_plan(int n, int dtype, const std::vector<InGate>& gates, const PlanOpt
     // ---- DAG (Section 5.1): immediate predecessor per qubit
     std::vector<Node> nodes(gates.size());
     std::vector<int> last(n, -1);
+    Products pr;
+    pr.next = (int)gates.size();
+    pr.made.reserve(2 * gates.size());
+    std::vector<FGate> canon;   // kept for the second fusion (the matrices are shared)
+    canon.reserve(gates.size());
     for (size_t i = 0; i < gates.size(); ++i) {
         Node& nd = nodes[i];
         nd.g = canonical(gates[i], (int)i);
+        canon.push_back(nd.g);
         for (int j = 0; j < nd.g.k; ++j) {
             const int x = nd.g.q[j];
             nd.prev[j] = last[x];
@@ -1262,23 +1423,20 @@ bool make_plan(int n, int dtype, const std::vector<InGate>& gates, const PlanOpt
     // merged across the commutation-aware DAG, and the whole fusion is run a second time
     // on that DAG: the plan with fewer passes (then less arithmetic) is kept
     {
-        if (o.fuse == 1) run_fusion(nodes, o);
+        if (o.fuse == 1) run_fusion(nodes, o, pr);
         std::vector<FGate> in;
-        for (const int v : topo_order(nodes)) in.push_back(nodes[v].g);
-        if (o.fuse == 1 && o.commute) in = fuse_commuting(in, n, o, true);
+        for (const int v : topo_order(nodes)) in.push_back(std::move(nodes[v].g));
+        if (o.fuse == 1 && o.commute) in = fuse_commuting(std::move(in), n, o, true, pr);
         for (FGate& g : in)
             if (!is_identity(g)) P.fused.push_back(std::move(g));
-        if (o.fuse == 1 && o.commute) merge_diagonals(P.fused, o.kmax);
+        if (o.fuse == 1 && o.commute) merge_diagonals(P.fused, o.kmax, pr);
     }
     if (!schedule_passes(n, P.fused, o, P.passes, err)) return false;
     if (o.fuse == 1 && o.commute) {
-        std::vector<FGate> in;
-        in.reserve(gates.size());
-        for (size_t i = 0; i < gates.size(); ++i) in.push_back(canonical(gates[i], (int)i));
         std::vector<FGate> alt;
-        for (FGate& g : fuse_commuting(in, n, o, false))
+        for (FGate& g : fuse_commuting(std::move(canon), n, o, false, pr))
             if (!is_identity(g)) alt.push_back(std::move(g));
-        merge_diagonals(alt, o.kmax);
+        merge_diagonals(alt, o.kmax, pr);
         std::vector<PassPlan> alt_passes;
         if (!schedule_passes(n, alt, o, alt_passes, err)) return false;
         auto arith = [&](const std::vector<FGate>& f) {
@@ -1353,12 +1511,11 @@ bool refresh_plan(HostPlan& P, const std::vector<InGate>& gates)
     size_t covered = 0;
     for (const FGate& f : P.fused) covered += f.mem.size();
     if (covered != gates.size()) return false;   // a product was dropped as the identity
-    std::vector<std::vector<cd>> mats(P.fused.size());
+    std::vector<Matrix> mats(P.fused.size());
     for (size_t fi = 0; fi < P.fused.size(); ++fi) {
         const FGate& f = P.fused[fi];
         const int d = 1 << f.k;
-        std::vector<cd>& M = mats[fi];
-        M.assign((size_t)d * d, cd(0, 0));
+        std::vector<cd> M((size_t)d * d, cd(0, 0));
         for (int r = 0; r < d; ++r) M[(size_t)r * d + r] = cd(1, 0);
         for (const int i : f.mem) {
             if (i < 0 || (size_t)i >= gates.size()) return false;
@@ -1377,15 +1534,16 @@ bool refresh_plan(HostPlan& P, const std::vector<InGate>& gates)
         FGate probe;
         probe.k = f.k;
         for (int j = 0; j < f.k; ++j) probe.q[j] = f.q[j];
-        probe.m = M;
+        probe.m = std::move(M);
         if ((diag_qubit_mask(probe) & f.dq) != f.dq) return false;
         if (f.kind == OP_DIAG || f.kind == OP_PERM) {
             for (int r = 0; r < d; ++r)
                 for (int c = 0; c < d; ++c)
-                    if (f.m[(size_t)r * d + c] == cd(0, 0) && M[(size_t)r * d + c] != cd(0, 0)) return false;
+                    if (f.m[(size_t)r * d + c] == cd(0, 0) && probe.m[(size_t)r * d + c] != cd(0, 0)) return false;
         }
+        mats[fi] = probe.m;
     }
-    for (size_t fi = 0; fi < P.fused.size(); ++fi) P.fused[fi].m.swap(mats[fi]);
+    for (size_t fi = 0; fi < P.fused.size(); ++fi) P.fused[fi].m = std::move(mats[fi]);
     build_device_tables(P);
     return true;
 }

@@ -2,6 +2,7 @@
 // DAG gate fusion (Section 5.2, Algorithm 2, Eq. 9) and HBM pass scheduling.
 #pragma once
 #include <complex>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -20,11 +21,25 @@ struct InGate {
     std::vector<cd> m;
 };
 
+// A matrix that copies of a fused gate share (never written once made).
+class Matrix {
+public:
+    Matrix() = default;
+    Matrix(std::vector<cd>&& v) : p_(std::make_shared<const std::vector<cd>>(std::move(v))) {}
+    const std::vector<cd>& vec() const { return *p_; }
+    const cd& operator[](size_t i) const { return (*p_)[i]; }
+    size_t size() const { return p_ ? p_->size() : 0; }
+
+private:
+    std::shared_ptr<const std::vector<cd>> p_;
+};
+
 // A fused gate: targets ascending, dense matrix with local bit j <-> q[j].
 struct FGate {
     int k = 0;
     int q[kMaxK] = {0, 0, 0, 0, 0};
-    std::vector<cd> m;
+    Matrix m;
+    int id = -1;          // names the matrix while a plan is made: equal ids, equal gates
     int kind = OP_DENSE;  // OP_DENSE, OP_DIAG or OP_PERM (classified from the matrix)
     int first = 0;        // smallest circuit index among the fused members
     int members = 1;
