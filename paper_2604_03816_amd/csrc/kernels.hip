@@ -886,14 +886,15 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restri
 // binary search over the items' tile prefix sums; the grid is persistent (fixed size,
 // strided over the work list) so the launch can be captured once and replayed.
 template <typename C, bool WIDE>
-__global__ __launch_bounds__(kThreads, sizeof(C) == 8 ? 4 : 2) void k_batch_pass(const BatchItem* __restrict__ items,
-                                                         const int* __restrict__ count)
+__global__ __launch_bounds__(kThreads, sizeof(C) == 8 ? 4 : 2) void k_batch_pass(const BatchItem* __restrict__ table,
+                                                                                 const BatchList* __restrict__ list)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     C* lds = reinterpret_cast<C*>(smem);
     __shared__ long long ends[kMaxBatchItems];
-    const int nitems = min(*count, kMaxBatchItems);
+    const int nitems = min(list->count, kMaxBatchItems);
     if (nitems <= 0) return;
+    const BatchItem* __restrict__ items = table + list->first;
     for (int i = threadIdx.x; i < nitems; i += kThreads) ends[i] = items[i].tile_end;
     __syncthreads();
     const long long total = ends[nitems - 1];
@@ -920,7 +921,7 @@ __global__ __launch_bounds__(kThreads, sizeof(C) == 8 ? 4 : 2) void k_batch_pass
             staged = lo;
         }
         run_tile<C, WIDE, false>((gptr<C>)it.state, lds, it.a, tile, (cptr<DevOp>)it.ops, (cptr<C>)it.pool,
-                          (cptr<int>)it.ipool, (cptr<float>)it.apool, alds);
+                          (cptr<int>)it.ipool, (cptr<float>)it.apool, alds, it.from_zero != 0);
         __syncthreads();   // the next work item reuses the LDS tile
     }
 }
@@ -1854,20 +1855,26 @@ __global__ __launch_bounds__(kThreads) void k_sum_chunks(const double* __restric
 }
 
 // Per-qubit <Z_i> and norm of finished served states, batched: work item = one chunk of
-// 2^12 consecutive amplitudes of one state.  Each workgroup writes, for its chunk, the
-// chunk's sum of |alpha|^2 and, for the qubits inside the chunk (bits < 12), the sum
-// over amplitudes with that bit set; qubits >= 12 are constant over a chunk and are
+// 2^14 consecutive amplitudes of one state.  Each workgroup writes, for its chunk, the
+// chunk's sum of |alpha|^2 and, for the qubits inside the chunk (bits < 14), the sum
+// over amplitudes with that bit set; qubits >= 14 are constant over a chunk and are
 // resolved on the host from the chunk sum.  Fixed partition and reduction order.
-constexpr int kZChunkQubits = 12;
-
+// A thread's amplitudes e = 256 i + tid share the bits of tid, so it keeps one total and a
+// sum per bit of i (pairwise sums of 16); the bits of tid are sums over threads, taken with
+// the others from one copy of the threads' sums in LDS (a workgroup reduction per qubit of
+// 2^12-amplitude chunks cost 26 barriers and more time than the read, and the host's
+// additions over chunks four times as many).
 template <typename C>
-__global__ __launch_bounds__(kThreads) void k_zsum_batch(const ZItem* __restrict__ items, const int* __restrict__ count,
+__global__ __launch_bounds__(kThreads) void k_zsum_batch(const ZItem* __restrict__ table, const BatchList* __restrict__ list,
                                                          double* __restrict__ partial)
 {
-    __shared__ NSum scratch[kThreads / 64];
-    const int nitems = *count;
+    constexpr int HB = kZChunkQubits - kLogThreads;   // bits of i
+    __shared__ double val[1 + HB][kThreads];
+    const int nitems = list->count;
     if (nitems <= 0) return;
+    const ZItem* __restrict__ items = table + list->first;
     const long long total = items[nitems - 1].chunk_end;
+    const int tid = threadIdx.x;
     for (long long w = blockIdx.x; w < total; w += gridDim.x) {
         int lo = 0, hi = nitems - 1;
         while (lo < hi) {
@@ -1880,25 +1887,66 @@ __global__ __launch_bounds__(kThreads) void k_zsum_batch(const ZItem* __restrict
         const int cq = it.n < kZChunkQubits ? it.n : kZChunkQubits;
         const int len = 1 << cq;
         const C* st = (const C*)it.state + (chunk << cq);
-        double tot = 0.0, bits[kZChunkQubits];
-#pragma unroll
-        for (int b = 0; b < kZChunkQubits; ++b) bits[b] = 0.0;
-        for (int e = threadIdx.x; e < len; e += kThreads) {
+        auto prob = [&](int e) {
             const C v = st[e];
-            const double p = (double)v.x * v.x + (double)v.y * v.y;
-            tot += p;
+            return (double)v.x * v.x + (double)v.y * v.y;
+        };
+        double tot = 0.0, bits[HB];
 #pragma unroll
-            for (int b = 0; b < kZChunkQubits; ++b)
-                if ((e >> b) & 1) bits[b] += p;
+        for (int b = 0; b < HB; ++b) bits[b] = 0.0;
+        if (len >= 16 * kThreads) {
+            for (int s = 0; s < len / (16 * kThreads); ++s) {
+                double p[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) p[i] = prob(((16 * s + i) << kLogThreads) + tid);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {   // p[i] for i < 16 >> b: sums over the bits below b
+                    double odd = 0.0;
+#pragma unroll
+                    for (int i = 0; i < (16 >> b); i += 2) {
+                        odd += p[i + 1];
+                        p[i / 2] = p[i] + p[i + 1];
+                    }
+                    bits[b] += odd;
+                }
+                tot += p[0];
+#pragma unroll
+                for (int b = 4; b < HB; ++b)
+                    if ((s >> (b - 4)) & 1) bits[b] += p[0];
+            }
+        } else {
+            for (int i = 0; (i << kLogThreads) + tid < len; ++i) {
+                const double p = prob((i << kLogThreads) + tid);
+                tot += p;
+#pragma unroll
+                for (int b = 0; b < HB; ++b)
+                    if ((i >> b) & 1) bits[b] += p;
+            }
         }
+        val[0][tid] = tot;
+#pragma unroll
+        for (int b = 0; b < HB; ++b) val[1 + b][tid] = bits[b];
+        __syncthreads();
         double* out = partial + (it.partial_off + chunk * (kZChunkQubits + 1));
-        NSum r = block_reduce(NSum{tot, 0.0}, scratch);
-        if (threadIdx.x == 0) out[0] = r.s + r.c;
-#pragma unroll
-        for (int b = 0; b < kZChunkQubits; ++b) {
-            r = block_reduce(NSum{bits[b], 0.0}, scratch);
-            if (threadIdx.x == 0) out[1 + b] = r.s + r.c;
+        // output o (0: the total, 1 + b: bit b), a wave each: bits of tid from the totals of the
+        // threads that have them set, the others from their own sums of all threads
+        const int lane = tid & 63;
+        for (int o = tid >> 6; o <= kZChunkQubits; o += kThreads / 64) {
+            const int b = o - 1;
+            NSum v = {0.0, 0.0};
+            if (b >= 0 && b < kLogThreads) {
+                for (int t = lane; t < kThreads / 2; t += 64) {
+                    const int j = ((t >> b) << (b + 1)) | (1 << b) | (t & ((1 << b) - 1));
+                    nadd(v, val[0][j]);
+                }
+            } else {
+                const double* src = val[b < 0 ? 0 : 1 + b - kLogThreads];
+                for (int t = lane; t < kThreads; t += 64) nadd(v, src[t]);
+            }
+            v = wave_reduce(v);
+            if (lane == 0) out[o] = v.s + v.c;
         }
+        __syncthreads();   // the next chunk overwrites val
     }
 }
 
@@ -1933,13 +1981,13 @@ __global__ __launch_bounds__(kThreads) void k_dm_pauli(const C* __restrict__ st,
 
 // ------------------------------------------------------------------ launchers
 
-hipError_t launch_zsum_batch(int dtype, const ZItem* items, const int* count, double* partial, int grid,
+hipError_t launch_zsum_batch(int dtype, const ZItem* table, const BatchList* list, double* partial, int grid,
                              hipStream_t s)
 {
     if (dtype == 0)
-        hipLaunchKernelGGL(k_zsum_batch<float2>, dim3(grid), dim3(kThreads), 0, s, items, count, partial);
+        hipLaunchKernelGGL(k_zsum_batch<float2>, dim3(grid), dim3(kThreads), 0, s, table, list, partial);
     else
-        hipLaunchKernelGGL(k_zsum_batch<double2>, dim3(grid), dim3(kThreads), 0, s, items, count, partial);
+        hipLaunchKernelGGL(k_zsum_batch<double2>, dim3(grid), dim3(kThreads), 0, s, table, list, partial);
     return hipGetLastError();
 }
 
@@ -1983,9 +2031,9 @@ hipError_t launch_pass_t(void* st, void* st2, const PassArgs& a, long long ntile
 }
 
 template <typename C, bool WIDE>
-static hipError_t launch_batch_pass_t(const BatchItem* items, const int* count, int grid, size_t lds, hipStream_t s)
+static hipError_t launch_batch_pass_t(const BatchItem* table, const BatchList* list, int grid, size_t lds, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_batch_pass<C, WIDE>), dim3(grid), dim3(kThreads), lds, s, items, count);
+    hipLaunchKernelGGL((k_batch_pass<C, WIDE>), dim3(grid), dim3(kThreads), lds, s, table, list);
     return hipGetLastError();
 }
 
@@ -2002,17 +2050,17 @@ hipError_t prepare_batch_pass()
     return hipSuccess;
 }
 
-hipError_t launch_batch_pass(int dtype, const BatchItem* items, const int* count, int grid, int tile_qubits,
+hipError_t launch_batch_pass(int dtype, const BatchItem* table, const BatchList* list, int grid, int tile_qubits,
                              hipStream_t s, bool wide)
 {
     // tile + the per-pass operand block (MFMA matrices, diagonal tables) of either dtype
     const size_t lds = ((dtype == 0 ? sizeof(float2) : sizeof(double2)) << tile_qubits) +
                        sizeof(float) * kServeOperandFloats;
     if (dtype == 0)
-        return wide ? launch_batch_pass_t<float2, true>(items, count, grid, lds, s)
-                    : launch_batch_pass_t<float2, false>(items, count, grid, lds, s);
-    return wide ? launch_batch_pass_t<double2, true>(items, count, grid, lds, s)
-                : launch_batch_pass_t<double2, false>(items, count, grid, lds, s);
+        return wide ? launch_batch_pass_t<float2, true>(table, list, grid, lds, s)
+                    : launch_batch_pass_t<float2, false>(table, list, grid, lds, s);
+    return wide ? launch_batch_pass_t<double2, true>(table, list, grid, lds, s)
+                : launch_batch_pass_t<double2, false>(table, list, grid, lds, s);
 }
 
 hipError_t launch_pass(int dtype, void* st, const PassArgs& a, long long ntiles, const DevOp* ops,

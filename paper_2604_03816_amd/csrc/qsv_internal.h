@@ -165,6 +165,12 @@ struct BatchItem {
     long long ntiles;     // tiles of this pass
     long long tile_end;   // prefix sum of ntiles over the items up to and including this one
     PassArgs a;
+    int from_zero;        // the request's first pass: |0...0> is built on chip
+};
+
+// A launch's part of the step's item table (items or finished states).
+struct BatchList {
+    int count, first;
 };
 
 // A finished served state whose <Z_i> and norm are reduced in a batched launch.
@@ -172,10 +178,11 @@ struct ZItem {
     const void* state;
     int n;
     int pad;
-    long long nchunks;      // 2^max(0, n - 12) chunks of 2^min(n, 12) amplitudes
+    long long nchunks;      // 2^max(0, n - 14) chunks of 2^min(n, 14) amplitudes
     long long chunk_end;    // prefix sum of nchunks
-    long long partial_off;  // first double of this state's partials (13 per chunk)
+    long long partial_off;  // first double of this state's partials (15 per chunk)
 };
+constexpr int kZChunkQubits = 14;
 
 // Diagonal-table floats a served pass may stage in LDS (the batched launch reserves this
 // much behind the tile).
@@ -193,9 +200,9 @@ size_t sort_uniforms_scratch(long long n);
 hipError_t sort_uniforms(const double* u, long long n, long long* order, void* scratch, size_t scratch_bytes,
                          hipStream_t s);
 hipError_t prepare_batch_pass();   // raises the batched kernels' LDS limit; call before capturing them
-hipError_t launch_batch_pass(int dtype, const BatchItem* items, const int* count, int grid, int tile_qubits,
+hipError_t launch_batch_pass(int dtype, const BatchItem* table, const BatchList* list, int grid, int tile_qubits,
                              hipStream_t s, bool wide);
-hipError_t launch_zsum_batch(int dtype, const ZItem* items, const int* count, double* partial, int grid,
+hipError_t launch_zsum_batch(int dtype, const ZItem* table, const BatchList* list, double* partial, int grid,
                              hipStream_t s);
 // st2 != nullptr applies the same pass to a second state of the same shape in the same
 // launch; from_zero makes the pass read |0...0> instead of the state buffers; wide = false

@@ -41,7 +41,8 @@ bool read_gate_public(const qsv_gate& g, int n, InGate& out, std::string& err);
 
 namespace {
 
-constexpr int kZQ = 12;   // chunk qubits of the batched <Z> reduction (k_zsum_batch)
+constexpr int kZQ = kZChunkQubits;   // chunk qubits of the batched <Z> reduction (k_zsum_batch)
+constexpr int kFootprintChunk = 12;  // footprints count 2^12-amplitude chunks of partials, an upper bound
 constexpr int kServeTileQubits[2] = {12, 12};   // 2^12-amplitude tiles (32 / 64 KiB), as the plain path
 
 struct Req {
@@ -99,13 +100,20 @@ struct qsv_server_s {
     std::unordered_map<long long, std::shared_ptr<Req>> kept;
     size_t capacity = 0, used = 0, pooled = 0;
     std::map<size_t, std::vector<void*>> pool;   // size class -> free device buffers
-    // step work tables: [dtype][j] pass items, [dtype] z items
-    std::vector<BatchItem*> h_items, d_items;
-    std::vector<int*> h_count, d_count;
-    ZItem* h_z[2] = {nullptr, nullptr};
-    ZItem* d_z[2] = {nullptr, nullptr};
-    int* h_zcount = nullptr;   // [2]
-    int* d_zcount = nullptr;
+    // The step's work tables, one pinned block and its device copy (one upload per step): a
+    // BatchList per pass launch and per <Z> launch, then the items of all lists, then the
+    // finished states.
+    unsigned char* h_tab = nullptr;
+    unsigned char* d_tab = nullptr;
+    size_t tab_items = 0, tab_z = 0, tab_bytes = 0;   // offsets of the items and states, size
+    std::vector<std::vector<BatchItem>> lists;        // this step's items per pass launch
+    std::vector<ZItem> zlists[2];
+    // pinned staging of the plan tables of the requests admitted in one step (the step's end
+    // waits for the copies)
+    unsigned char* h_stage = nullptr;
+    size_t stage_bytes = 0, stage_used = 0;
+    hipStream_t stream2 = nullptr;                    // the captured step's complex128 branch
+    hipEvent_t fork = nullptr, join = nullptr;
     double* d_partial = nullptr;
     double* h_partial = nullptr;
     size_t partial_cap = 0;    // doubles
@@ -141,8 +149,8 @@ void worker_loop(qsv_server s)
             r->state_bytes = elem(r->dtype) << r->n;
             r->table_bytes = hp.ops.size() * sizeof(DevOp) + hp.pool.size() * elem(r->dtype) +
                              hp.ipool.size() * sizeof(int) + hp.apool.size() * sizeof(float) + 4 * 256;
-            const long long chunks = 1ll << std::max(0, r->n - kZQ);
-            r->work_bytes = (size_t)chunks * (kZQ + 1) * sizeof(double);
+            const long long chunks = 1ll << std::max(0, r->n - kFootprintChunk);
+            r->work_bytes = (size_t)chunks * (kFootprintChunk + 1) * sizeof(double);
             r->footprint = r->state_bytes + r->table_bytes + r->work_bytes;   // Eq. 14
             if (!r->keep_gates) {
                 r->gates.clear();
@@ -222,24 +230,45 @@ qsv_status admit(qsv_server s, const std::shared_ptr<Req>& r)
     r->d_ipool = (int*)((char*)r->tables + o_ip);
     r->d_apool = (float*)((char*)r->tables + o_ap);
     if (!s->o.dry_run) {
-        std::vector<unsigned char> buf(r->table_cap, 0);
-        if (nops) std::memcpy(buf.data(), hp.ops.data(), nops);
+        if (s->stage_used + r->table_cap > s->stage_bytes) {
+            // the copies that read the block must be done before it is used again or replaced
+            if (hipStreamSynchronize(s->stream) != hipSuccess) return set_error(QSV_E_DEVICE, "admit: synchronise");
+            s->stage_used = 0;
+            if (r->table_cap > s->stage_bytes) {
+                if (s->h_stage) (void)hipHostFree(s->h_stage);
+                s->h_stage = nullptr;
+                s->stage_bytes = 0;
+                const size_t want = std::max<size_t>(round_pow2(r->table_cap), (size_t)8 << 20);
+                if (hipHostMalloc((void**)&s->h_stage, want, hipHostMallocDefault) != hipSuccess) {
+                    (void)hipGetLastError();
+                    s->h_stage = nullptr;
+                    pool_put(s, r->state, r->state_bytes);
+                    pool_put(s, r->tables, r->table_cap);
+                    r->state = r->tables = nullptr;
+                    return set_error(QSV_E_OOM, "admission staging allocation failed");
+                }
+                s->stage_bytes = want;
+            }
+        }
+        unsigned char* buf = s->h_stage + s->stage_used;
+        s->stage_used += (r->table_cap + 255) & ~size_t(255);
+        if (nops) std::memcpy(buf, hp.ops.data(), nops);
         for (size_t i = 0; i < hp.pool.size(); ++i) {
             if (r->dtype == QSV_C64) {
-                float* f = reinterpret_cast<float*>(buf.data() + o_pool) + 2 * i;
+                float* f = reinterpret_cast<float*>(buf + o_pool) + 2 * i;
                 f[0] = (float)hp.pool[i].real();
                 f[1] = (float)hp.pool[i].imag();
             } else {
-                double* f = reinterpret_cast<double*>(buf.data() + o_pool) + 2 * i;
+                double* f = reinterpret_cast<double*>(buf + o_pool) + 2 * i;
                 f[0] = hp.pool[i].real();
                 f[1] = hp.pool[i].imag();
             }
         }
-        if (nip) std::memcpy(buf.data() + o_ip, hp.ipool.data(), nip);
-        if (nap) std::memcpy(buf.data() + o_ap, hp.apool.data(), nap);
-        hipError_t e = hipMemcpyAsync(r->tables, buf.data(), r->table_cap, hipMemcpyHostToDevice, s->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(s->stream);   // buf is pageable and goes out of scope
-        if (e == hipSuccess) e = launch_init_zero(r->dtype, r->state, 1ll << r->n, s->stream);
+        if (nip) std::memcpy(buf + o_ip, hp.ipool.data(), nip);
+        if (nap) std::memcpy(buf + o_ap, hp.apool.data(), nap);
+        hipError_t e = hipMemcpyAsync(r->tables, buf, r->table_cap, hipMemcpyHostToDevice, s->stream);
+        // the first pass builds |0...0> itself; a circuit without passes needs it written
+        if (e == hipSuccess && hp.passes.empty()) e = launch_init_zero(r->dtype, r->state, 1ll << r->n, s->stream);
         if (e != hipSuccess) return set_error(QSV_E_DEVICE, std::string("admit: ") + hipGetErrorString(e));
     }
     s->used += r->footprint;
@@ -273,49 +302,62 @@ qsv_status ensure_partial(qsv_server s, size_t doubles)
     return QSV_OK;
 }
 
-// The step's kernel sequence (captured into the graph, or launched directly).
-hipError_t launch_step(qsv_server s)
+// The step's kernel sequence (captured into the graph, or launched directly on one stream).
+hipError_t launch_step(qsv_server s, bool branch)
 {
     const int P = passes_per_step(s);
     const int grid = s->o.grid > 0 ? s->o.grid : 2048;
-    // work list (wide, dtype, j) at slot (2 wide + dtype) P + j: passes with register-heavy
-    // ops go to the wide kernel variant, the rest to the lighter one
-    for (int j = 0; j < P; ++j)
-        for (int w = 0; w < 2; ++w)
-            for (int dt = 0; dt < 2; ++dt) {
+    const BatchList* heads = (const BatchList*)s->d_tab;
+    const BatchItem* items = (const BatchItem*)(s->d_tab + s->tab_items);
+    const ZItem* states = (const ZItem*)(s->d_tab + s->tab_z);
+    // The precisions' requests are independent: with `branch` (captured steps) complex128 runs
+    // on a branch of its own beside complex64, so that neither waits for the other's last
+    // workgroups.
+    hipError_t e = hipSuccess;
+    if (branch) {
+        if ((e = hipEventRecord(s->fork, s->stream)) != hipSuccess) return e;
+        if ((e = hipStreamWaitEvent(s->stream2, s->fork, 0)) != hipSuccess) return e;
+    }
+    for (int dt = 0; dt < 2; ++dt) {
+        const hipStream_t st = dt && branch ? s->stream2 : s->stream;
+        // work list (wide, dtype, j) at slot (2 wide + dtype) P + j: passes with register-heavy
+        // ops go to the wide kernel variant, the rest to the lighter one
+        for (int j = 0; j < P; ++j)
+            for (int w = 0; w < 2; ++w) {
                 const int slot = (2 * w + dt) * P + j;
-                hipError_t e = launch_batch_pass(dt, s->d_items[slot], s->d_count[slot], grid, kServeTileQubits[dt],
-                                                 s->stream, w != 0);
+                e = launch_batch_pass(dt, items, heads + slot, grid, kServeTileQubits[dt], st, w != 0);
                 if (e != hipSuccess) return e;
             }
-    for (int dt = 0; dt < 2; ++dt) {
-        hipError_t e = launch_zsum_batch(dt, s->d_z[dt], s->d_zcount + dt, s->d_partial, 1024, s->stream);
+        e = launch_zsum_batch(dt, states, heads + 4 * P + dt, s->d_partial, 1024, st);
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (branch) {
+        if ((e = hipEventRecord(s->join, s->stream2)) != hipSuccess) return e;
+        if ((e = hipStreamWaitEvent(s->stream, s->join, 0)) != hipSuccess) return e;
+    }
+    return e;
 }
 
 qsv_status run_step_device(qsv_server s, size_t zdoubles)
 {
     const int P = passes_per_step(s);
-    const int slots = std::max(1, s->o.max_slots);
-    // work tables to the device (outside the graph)
+    // the work tables, packed, to the device in one copy (outside the graph)
+    BatchList* heads = (BatchList*)s->h_tab;
+    BatchItem* items = (BatchItem*)(s->h_tab + s->tab_items);
+    ZItem* states = (ZItem*)(s->h_tab + s->tab_z);
+    int at = 0;
     for (int i = 0; i < 4 * P; ++i) {
-        const int cnt = *s->h_count[i];
-        if (hipMemcpyAsync(s->d_count[i], s->h_count[i], sizeof(int), hipMemcpyHostToDevice, s->stream) != hipSuccess ||
-            (cnt > 0 && hipMemcpyAsync(s->d_items[i], s->h_items[i], cnt * sizeof(BatchItem), hipMemcpyHostToDevice,
-                                       s->stream) != hipSuccess))
-            return set_error(QSV_E_DEVICE, "step table upload failed");
+        heads[i] = BatchList{(int)s->lists[i].size(), at};
+        for (const BatchItem& it : s->lists[i]) items[at++] = it;
     }
+    int zat = 0;
     for (int dt = 0; dt < 2; ++dt) {
-        const int cnt = s->h_zcount[dt];
-        if (cnt > 0 && hipMemcpyAsync(s->d_z[dt], s->h_z[dt], cnt * sizeof(ZItem), hipMemcpyHostToDevice, s->stream) !=
-                           hipSuccess)
-            return set_error(QSV_E_DEVICE, "step table upload failed");
+        heads[4 * P + dt] = BatchList{(int)s->zlists[dt].size(), zat};
+        for (const ZItem& z : s->zlists[dt]) states[zat++] = z;
     }
-    if (hipMemcpyAsync(s->d_zcount, s->h_zcount, 2 * sizeof(int), hipMemcpyHostToDevice, s->stream) != hipSuccess)
+    const size_t used = zat ? s->tab_z + (size_t)zat * sizeof(ZItem) : s->tab_items + (size_t)at * sizeof(BatchItem);
+    if (hipMemcpyAsync(s->d_tab, s->h_tab, used, hipMemcpyHostToDevice, s->stream) != hipSuccess)
         return set_error(QSV_E_DEVICE, "step table upload failed");
-    (void)slots;
     hipError_t e = hipSuccess;
     if (s->o.use_graph) {
         if (s->graph_dirty) {
@@ -327,7 +369,7 @@ qsv_status run_step_device(qsv_server s, size_t zdoubles)
             }
             e = hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal);
             if (e == hipSuccess) {
-                hipError_t le = launch_step(s);
+                hipError_t le = launch_step(s, true);
                 e = hipStreamEndCapture(s->stream, &s->graph);
                 if (le != hipSuccess) e = le;
             }
@@ -338,13 +380,14 @@ qsv_status run_step_device(qsv_server s, size_t zdoubles)
         e = hipGraphLaunch(s->gexec, s->stream);
         ++s->st.graph_replays;
     } else {
-        e = launch_step(s);
+        e = launch_step(s, false);
     }
     if (e == hipSuccess && zdoubles > 0)
         e = hipMemcpyAsync(s->h_partial, s->d_partial, zdoubles * sizeof(double), hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipEventRecord(s->ev, s->stream);
     if (e == hipSuccess) e = hipEventSynchronize(s->ev);
     if (e != hipSuccess) return set_error(QSV_E_DEVICE, std::string("step: ") + hipGetErrorString(e));
+    s->stage_used = 0;   // every admission's copy is done
     return QSV_OK;
 }
 
@@ -393,21 +436,16 @@ qsv_status qsv_server_create(const qsv_server_opts* opts, void* stream, qsv_serv
         }
         s->capacity = s->o.capacity_bytes ? s->o.capacity_bytes : (fr > s->o.reserve_bytes ? fr - s->o.reserve_bytes : 0);
         bool ok = hipEventCreateWithFlags(&s->ev, hipEventDisableTiming) == hipSuccess;
-        s->h_items.assign(4 * P, nullptr);
-        s->d_items.assign(4 * P, nullptr);
-        s->h_count.assign(4 * P, nullptr);
-        s->d_count.assign(4 * P, nullptr);
-        for (int i = 0; ok && i < 4 * P; ++i) {
-            ok = hipHostMalloc((void**)&s->h_items[i], slots * sizeof(BatchItem), hipHostMallocDefault) == hipSuccess &&
-                 hipMalloc((void**)&s->d_items[i], slots * sizeof(BatchItem)) == hipSuccess &&
-                 hipHostMalloc((void**)&s->h_count[i], sizeof(int), hipHostMallocDefault) == hipSuccess &&
-                 hipMalloc((void**)&s->d_count[i], sizeof(int)) == hipSuccess;
-        }
-        for (int dt = 0; ok && dt < 2; ++dt)
-            ok = hipHostMalloc((void**)&s->h_z[dt], slots * sizeof(ZItem), hipHostMallocDefault) == hipSuccess &&
-                 hipMalloc((void**)&s->d_z[dt], slots * sizeof(ZItem)) == hipSuccess;
-        ok = ok && hipHostMalloc((void**)&s->h_zcount, 2 * sizeof(int), hipHostMallocDefault) == hipSuccess &&
-             hipMalloc((void**)&s->d_zcount, 2 * sizeof(int)) == hipSuccess;
+        auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+        s->lists.resize(4 * P);
+        s->tab_items = al((4 * P + 2) * sizeof(BatchList));
+        s->tab_z = s->tab_items + al((size_t)slots * P * sizeof(BatchItem));   // a request has P items a step
+        s->tab_bytes = s->tab_z + al((size_t)slots * sizeof(ZItem));
+        ok = ok && hipHostMalloc((void**)&s->h_tab, s->tab_bytes, hipHostMallocDefault) == hipSuccess &&
+             hipMalloc((void**)&s->d_tab, s->tab_bytes) == hipSuccess &&
+             hipStreamCreateWithFlags(&s->stream2, hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&s->join, hipEventDisableTiming) == hipSuccess;
         if (!ok || ensure_partial(s, 1 << 16) != QSV_OK) {
             (void)hipGetLastError();
             qsv_server_free(s);
@@ -436,18 +474,12 @@ qsv_status qsv_server_free(qsv_server s)
             for (void* p : kv.second) (void)hipFree(p);
         if (s->gexec) (void)hipGraphExecDestroy(s->gexec);
         if (s->graph) (void)hipGraphDestroy(s->graph);
-        for (size_t i = 0; i < s->h_items.size(); ++i) {
-            (void)hipHostFree(s->h_items[i]);
-            (void)hipFree(s->d_items[i]);
-            (void)hipHostFree(s->h_count[i]);
-            (void)hipFree(s->d_count[i]);
-        }
-        for (int dt = 0; dt < 2; ++dt) {
-            (void)hipHostFree(s->h_z[dt]);
-            (void)hipFree(s->d_z[dt]);
-        }
-        (void)hipHostFree(s->h_zcount);
-        (void)hipFree(s->d_zcount);
+        (void)hipHostFree(s->h_tab);
+        (void)hipFree(s->d_tab);
+        (void)hipHostFree(s->h_stage);
+        if (s->fork) (void)hipEventDestroy(s->fork);
+        if (s->join) (void)hipEventDestroy(s->join);
+        if (s->stream2) (void)hipStreamDestroy(s->stream2);
         (void)hipFree(s->d_partial);
         (void)hipHostFree(s->h_partial);
         if (s->ev) (void)hipEventDestroy(s->ev);
@@ -560,8 +592,8 @@ qsv_status qsv_server_step(qsv_server s, int* n_running, int* n_pending)
     std::vector<std::shared_ptr<Req>> finishing;
     size_t zdoubles = 0;
     if (!s->o.dry_run) {
-        for (int i = 0; i < 4 * P; ++i) *s->h_count[i] = 0;
-        s->h_zcount[0] = s->h_zcount[1] = 0;
+        for (auto& l : s->lists) l.clear();
+        for (auto& l : s->zlists) l.clear();
     }
     long long tiles_step = 0;
     for (auto& r : s->running) {
@@ -572,8 +604,8 @@ qsv_status qsv_server_step(qsv_server s, int* n_running, int* n_pending)
             tiles_step += hp.pgrid[pi];
             if (s->o.dry_run) continue;
             const int slot = (2 * (hp.pwide[pi] ? 1 : 0) + r->dtype) * P + j;
-            int& cnt = *s->h_count[slot];
-            BatchItem& it = s->h_items[slot][cnt];
+            std::vector<BatchItem>& list = s->lists[slot];
+            BatchItem it;
             it.state = r->state;
             it.ops = r->d_ops;
             it.pool = r->d_pool;
@@ -581,23 +613,24 @@ qsv_status qsv_server_step(qsv_server s, int* n_running, int* n_pending)
             it.apool = r->d_apool;
             it.a = hp.pargs[pi];
             it.ntiles = hp.pgrid[pi];
-            it.tile_end = (cnt ? s->h_items[slot][cnt - 1].tile_end : 0) + it.ntiles;
-            ++cnt;
+            it.tile_end = (list.empty() ? 0 : list.back().tile_end) + it.ntiles;
+            it.from_zero = pi == 0;
+            list.push_back(it);
         }
         if (r->next_pass + P >= np) {
             finishing.push_back(r);
             if (!s->o.dry_run) {
                 const int dt = r->dtype;
-                int& cnt = s->h_zcount[dt];
-                ZItem& z = s->h_z[dt][cnt];
+                std::vector<ZItem>& list = s->zlists[dt];
+                ZItem z{};
                 z.state = r->state;
                 z.n = r->n;
                 z.nchunks = 1ll << std::max(0, r->n - kZQ);
-                z.chunk_end = (cnt ? s->h_z[dt][cnt - 1].chunk_end : 0) + z.nchunks;
+                z.chunk_end = (list.empty() ? 0 : list.back().chunk_end) + z.nchunks;
                 z.partial_off = (long long)zdoubles;
                 r->z_off = (long long)zdoubles;
                 zdoubles += (size_t)z.nchunks * (kZQ + 1);
-                ++cnt;
+                list.push_back(z);
             }
         }
     }
