@@ -1028,6 +1028,35 @@ __global__ __launch_bounds__(kThreads) void k_norm(const float4* __restrict__ st
     }
 }
 
+// The threads' sums of a launch's terms to one partial each, eight terms at a time through LDS
+// (w: 8 x 256 doubles, free to overwrite); wave w finishes terms w and w + 4 of the eight in a
+// fixed order.  (A workgroup reduction per term cost two barriers and six shuffles of every
+// wave each: two 12-qubit complex128 states 19 -> 9 us.)
+__device__ __forceinline__ void finish_terms(const double (&acc)[kMaxTermsPerLaunch], int nterms, double* w,
+                                             double* __restrict__ partial)
+{
+#pragma unroll
+    for (int i0 = 0; i0 < kMaxTermsPerLaunch; i0 += 8) {
+        if (i0 >= nterms) break;
+        __syncthreads();
+#pragma unroll
+        for (int i = i0; i < i0 + 8; ++i) w[((i - i0) << kLogThreads) + threadIdx.x] = acc[i];
+        __syncthreads();
+        for (int i = i0 + (threadIdx.x >> 6); i < i0 + 8 && i < nterms; i += kThreads / 64) {
+            const double* v = w + ((i - i0) << kLogThreads) + (threadIdx.x & 63);
+            NSum r = {v[0], 0.0};
+            nadd(r, v[64]);
+            nadd(r, v[128]);
+            nadd(r, v[192]);
+            r = wave_reduce(r);
+            if ((threadIdx.x & 63) == 0) {
+                partial[((long long)blockIdx.x * nterms + i) * 2] = r.s;
+                partial[((long long)blockIdx.x * nterms + i) * 2 + 1] = r.c;
+            }
+        }
+    }
+}
+
 // Pauli matrix elements over tiles: value_t = sum_k Re( i^ny conj(a[k xor x]) b[k] ) *
 // (-1)^popcount(k & zy), i.e. Re <a|P_t|b> (ny may carry an extra 3 to give Im instead),
 // for terms with X/Y factors (Z-only terms go to k_expval_z; here they take the generic
@@ -1149,10 +1178,11 @@ __device__ __forceinline__ void expval_tiles(gptr<C> __restrict__ sa, gptr<C> __
     }
 }
 
-// LDS bytes of one k_expval workgroup for a tile of 2^m amplitudes: the tile of a.
+// LDS bytes of one k_expval workgroup for a tile of 2^m amplitudes: the tile of a, and at the
+// end eight terms' sums.
 __host__ __device__ constexpr size_t expval_lds_bytes(size_t elem, int m)
 {
-    return elem << m;
+    return (elem << m) > sizeof(double) * 8 * kThreads ? elem << m : sizeof(double) * 8 * kThreads;
 }
 
 template <typename C, bool TWO>
@@ -1161,7 +1191,6 @@ __global__ __launch_bounds__(kThreads) void k_expval(const C* __restrict__ sa, c
                                                      double* __restrict__ partial)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ NSum scratch[kThreads / 64];
     __shared__ TermRow rows[kMaxTermsPerLaunch];
     if (threadIdx.x < t.nterms) {
         const int i = threadIdx.x;
@@ -1179,17 +1208,7 @@ __global__ __launch_bounds__(kThreads) void k_expval(const C* __restrict__ sa, c
     case 2: expval_tiles<C, 4, TWO>(ga, gb, tla, rows, a, t.nterms, ntiles, acc); break;
     default: expval_tiles<C, 8, TWO>(ga, gb, tla, rows, a, t.nterms, ntiles, acc); break;
     }
-#pragma unroll
-    for (int i = 0; i < kMaxTermsPerLaunch; ++i) {
-        if (i < t.nterms) {
-            NSum v = {acc[i], 0.0};
-            const NSum r = block_reduce(v, scratch);
-            if (threadIdx.x == 0) {
-                partial[((long long)blockIdx.x * t.nterms + i) * 2] = r.s;
-                partial[((long long)blockIdx.x * t.nterms + i) * 2 + 1] = r.c;
-            }
-        }
-    }
+    finish_terms(acc, t.nterms, reinterpret_cast<double*>(smem), partial);
 }
 
 // Terms with X/Y factors whose supports hold at most RB qubits (RB = 4 for one state, 3 for
@@ -1485,48 +1504,25 @@ __global__ __launch_bounds__(kThreads) void k_expval_z(const C* __restrict__ sa,
     case 2: expval_z_tiles<C, 4, TWO>(ga, gb, w, a, t, ntiles, acc); break;
     default: expval_z_tiles<C, 8, TWO>(ga, gb, w, a, t, ntiles, acc); break;
     }
-    // the threads' sums, eight terms at a time through LDS; wave w finishes terms w and w + 4
-    // of the eight in a fixed order (a workgroup reduction per term cost two barriers and six
-    // shuffles of every wave each: two 12-qubit complex128 states 19 -> 9 us)
-#pragma unroll
-    for (int i0 = 0; i0 < kMaxTermsPerLaunch; i0 += 8) {
-        if (i0 >= t.nterms) break;
-        __syncthreads();
-#pragma unroll
-        for (int i = i0; i < i0 + 8; ++i) w[((i - i0) << kLogThreads) + threadIdx.x] = acc[i];
-        __syncthreads();
-        for (int i = i0 + (threadIdx.x >> 6); i < i0 + 8 && i < t.nterms; i += kThreads / 64) {
-            const double* v = w + ((i - i0) << kLogThreads) + (threadIdx.x & 63);
-            NSum r = {v[0], 0.0};
-            nadd(r, v[64]);
-            nadd(r, v[128]);
-            nadd(r, v[192]);
-            r = wave_reduce(r);
-            if ((threadIdx.x & 63) == 0) {
-                partial[((long long)blockIdx.x * t.nterms + i) * 2] = r.s;
-                partial[((long long)blockIdx.x * t.nterms + i) * 2 + 1] = r.c;
-            }
-        }
-    }
+    finish_terms(acc, t.nterms, w, partial);
 }
 
-// Whole states below 256 amplitudes: one workgroup, element per thread, straight from
-// the definition (the tile is the state).
+// Whole states below 256 amplitudes: one workgroup, a wave per term, straight from the
+// definition (the tile is the state).
 template <typename C, bool TWO>
 __global__ __launch_bounds__(kThreads) void k_expval_small(const C* __restrict__ sa, const C* __restrict__ sb,
                                                            int n, const TermArgs t, double* __restrict__ partial)
 {
-    __shared__ NSum scratch[kThreads / 64];
-    const int N = 1 << n;
-    const int e = threadIdx.x;
-    for (int i = 0; i < t.nterms; ++i) {
-        double val = 0.0;
-        if (e < N) {
+    const int N = 1 << n, lane = threadIdx.x & 63;
+    for (int i = threadIdx.x >> 6; i < t.nterms; i += kThreads / 64) {
+        NSum v = {0.0, 0.0};
+        for (int e = lane; e < N; e += 64) {
             const C ap = sa[e ^ t.xloc[i]];
             const C be = TWO ? sb[e] : sa[e];
             const double re = (double)ap.x * (double)be.x + (double)ap.y * (double)be.y;
             const double im = (double)ap.x * (double)be.y - (double)ap.y * (double)be.x;
             const bool odd = __popc(e & t.zloc[i]) & 1;
+            double val;
             if (TWO) {   // the two-state weights (TermArgs::kw)
                 val = (odd ? t.kw[i][2] : t.kw[i][0]) * re - (odd ? t.kw[i][3] : t.kw[i][1]) * im;
             } else {
@@ -1534,11 +1530,12 @@ __global__ __launch_bounds__(kThreads) void k_expval_small(const C* __restrict__
                 val = (q == 0) ? re : (q == 1) ? -im : (q == 2) ? -re : im;
                 if (odd) val = -val;
             }
+            nadd(v, val);
         }
-        const NSum r = block_reduce(NSum{val, 0.0}, scratch);
-        if (threadIdx.x == 0) {
-            partial[(long long)i * 2] = r.s;
-            partial[(long long)i * 2 + 1] = r.c;
+        v = wave_reduce(v);
+        if (lane == 0) {
+            partial[(long long)i * 2] = v.s;
+            partial[(long long)i * 2 + 1] = v.c;
         }
     }
 }
@@ -2113,7 +2110,9 @@ hipError_t launch_zero(int dtype, void* st, long long N, hipStream_t s)
 
 int norm_grid(long long N)
 {
-    return (int)std::min<long long>(1024, std::max<long long>(1, N / kThreads));
+    // eight loads per thread at least: below 2^21 amplitudes more workgroups only add
+    // reductions (18-qubit complex128: 1024 workgroups 18.7 us, 128 11.7 us)
+    return (int)std::min<long long>(1024, std::max<long long>(1, N / (8 * kThreads)));
 }
 
 hipError_t launch_norm(int dtype, const void* st, long long N, double* partial, int grid, hipStream_t s)
