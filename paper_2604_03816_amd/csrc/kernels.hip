@@ -1950,7 +1950,8 @@ __global__ __launch_bounds__(kThreads) void k_zsum_batch(const ZItem* __restrict
 // Tr(rho P_t) for an n-qubit density matrix held as vec(rho) (index row + 2^n col):
 // P|k> = i^ny (-1)^popcount(k & z) |k xor x>, so Tr(rho P) = sum_k rho[k, k xor x] *
 // i^ny (-1)^popcount(k & z).  Only 2^n entries per term are read.  One FP64 Neumaier
-// pair per workgroup and term, combined on the host in a fixed order.
+// pair per workgroup and term (blockIdx.y; one term after another cost a workgroup reduction
+// each: 22 terms of 11 qubits 37 -> 6 us), combined on the host in a fixed order.
 template <typename C>
 __global__ __launch_bounds__(kThreads) void k_dm_pauli(const C* __restrict__ st, int n, const PauliSumArgs p,
                                                        double* __restrict__ partial)
@@ -1958,21 +1959,20 @@ __global__ __launch_bounds__(kThreads) void k_dm_pauli(const C* __restrict__ st,
     __shared__ NSum scratch[kThreads / 64];
     const long long N = 1ll << n;
     const long long stride = (long long)gridDim.x * blockDim.x;
-    for (int t = 0; t < p.nterms; ++t) {
-        const long long x = p.x[t], z = p.z[t];
-        const int q = p.ny[t] & 3;
-        NSum acc = {0.0, 0.0};
-        for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < N; k += stride) {
-            const C v = st[k + ((k ^ x) << n)];
-            double val = (q == 0) ? v.x : (q == 1) ? -v.y : (q == 2) ? -v.x : v.y;   // Re(i^q v)
-            if (__popcll(k & z) & 1) val = -val;
-            nadd(acc, val);
-        }
-        const NSum r = block_reduce(acc, scratch);
-        if (threadIdx.x == 0) {
-            partial[((long long)blockIdx.x * p.nterms + t) * 2] = r.s;
-            partial[((long long)blockIdx.x * p.nterms + t) * 2 + 1] = r.c;
-        }
+    const int t = blockIdx.y;
+    const long long x = p.x[t], z = p.z[t];
+    const int q = p.ny[t] & 3;
+    NSum acc = {0.0, 0.0};
+    for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < N; k += stride) {
+        const C v = st[k + ((k ^ x) << n)];
+        double val = (q == 0) ? v.x : (q == 1) ? -v.y : (q == 2) ? -v.x : v.y;   // Re(i^q v)
+        if (__popcll(k & z) & 1) val = -val;
+        nadd(acc, val);
+    }
+    const NSum r = block_reduce(acc, scratch);
+    if (threadIdx.x == 0) {
+        partial[((long long)blockIdx.x * p.nterms + t) * 2] = r.s;
+        partial[((long long)blockIdx.x * p.nterms + t) * 2 + 1] = r.c;
     }
 }
 
@@ -2291,9 +2291,9 @@ hipError_t launch_dm_pauli(int dtype, const void* st, int n, const PauliSumArgs&
                            hipStream_t s)
 {
     if (dtype == 0)
-        hipLaunchKernelGGL(k_dm_pauli<float2>, dim3(grid), dim3(kThreads), 0, s, (const float2*)st, n, p, partial);
+        hipLaunchKernelGGL(k_dm_pauli<float2>, dim3(grid, p.nterms), dim3(kThreads), 0, s, (const float2*)st, n, p, partial);
     else
-        hipLaunchKernelGGL(k_dm_pauli<double2>, dim3(grid), dim3(kThreads), 0, s, (const double2*)st, n, p, partial);
+        hipLaunchKernelGGL(k_dm_pauli<double2>, dim3(grid, p.nterms), dim3(kThreads), 0, s, (const double2*)st, n, p, partial);
     return hipGetLastError();
 }
 
