@@ -793,13 +793,15 @@ __device__ __forceinline__ void run_tile(gptr<C> __restrict__ st, C* __restrict_
 // One work-list entry of a pass launch: the state it belongs to and its tile.  Consecutive
 // workgroups run on different XCDs; the map gives each XCD runs of neighbouring tiles, whose
 // 128-byte rows are neighbours in memory (30-qubit passes without ops 3.48 -> 3.42 ms
-// complex64, 28-qubit complex128 1.72 -> 1.65 ms).  It permutes each full stride of the grid
+// complex64, 28-qubit complex128 1.72 -> 1.65 ms; with ops 25-qubit complex64 0.131 -> 0.127
+// ms for runs of 16 against one run per XCD).  It permutes each full stride of the grid
 // (a power of two) and leaves other grids alone.
 __device__ __forceinline__ long long xcd_tile(long long t, unsigned grid, long long ntiles)
 {
-    if ((grid & (grid - 1)) || grid < 64 || ntiles < grid) return t;
+    if ((grid & (grid - 1)) || grid < 128 || ntiles < grid) return t;
     const unsigned w = (unsigned)t & (grid - 1);
-    return (t - w) + ((w & 7) * (grid >> 3) + (w >> 3));
+    const unsigned k = w >> 3;
+    return (t - w) + (k & ~15u) * 8 + (w & 7) * 16 + (k & 15);
 }
 
 // WIDE = false: the variant without the register-heavy op paths, for passes free of
