@@ -431,11 +431,15 @@ bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vecto
     }
     const size_t zgroups = groups.size();
     // terms whose X/Y supports fit a round's kept bits go to the register kernel, on tiles of
-    // its own size (imag: the two-state kernel)
+    // its own size (imag: the two-state kernel, which takes one X or Y factor and no further
+    // Z: generators have no other form, and the pairs' parities are then known to the compiler)
     const int rb = imag ? kRoundBitsTwo : kRoundBits, mr = kLogThreads + rb;
     const int Lr = std::min(o.low_qubits, mr);
     const unsigned long long lowr = (1ull << Lr) - 1;
-    auto in_rounds = [&](const PTerm& t) { return n >= mr && t.x && __builtin_popcountll(t.x) <= rb; };
+    auto in_rounds = [&](const PTerm& t) {
+        if (n < mr || !t.x) return false;
+        return imag ? !(t.x & (t.x - 1)) && !(t.z & ~t.x) : __builtin_popcountll(t.x) <= rb;
+    };
     auto group = [&](bool reg, int mm, unsigned long long lowm, size_t first) {
         for (size_t i = 0; i < terms.size(); ++i) {
             const unsigned long long x = terms[i].x;

@@ -1213,13 +1213,17 @@ __global__ __launch_bounds__(kThreads) void k_expval(const C* __restrict__ sa, c
     finish_terms(acc, t.nterms, reinterpret_cast<double*>(smem), partial);
 }
 
-// Terms with X/Y factors whose supports hold at most RB qubits (RB = 4 for one state, 3 for
-// two): the tile goes to LDS once, and in each round every thread reads the 2^RB elements
-// that differ in the round's kept bits, so a term pairs registers of one thread: per pair one
-// product and one signed addition instead of two LDS reads, index arithmetic and four
-// conversions.  A round serves every term inside its bits (a field of single X or Y factors
-// on 12 tile qubits takes three rounds).  What bounds it is the read of the state: 30 X terms
-// at 30 qubits complex64 (4 launches) 16.0 -> 9.5 ms.
+// Terms with X/Y factors on few qubits (one state: at most RB = 4; two states: one qubit, its
+// Z factor the term's only one, as generators have): the tile goes to LDS once, and in each
+// round every thread reads the 2^RB elements that differ in the round's kept bits (RB = 3 for
+// two states), so a term pairs registers of one thread: per pair one product and one signed
+// addition instead of two LDS reads, index arithmetic and four conversions.  A round serves
+// every term inside its bits (a field of single X or Y factors on 12 tile qubits takes three
+// rounds).  The next tile's loads fly during the rounds.  What bounds it on large states is
+// the read of the state, on ones that the last-level cache holds the FP64 arithmetic and the
+// chain of LDS accesses of each term: 30 X terms at 30 qubits complex64 (4 launches) 16.0 ->
+// 9.1 ms; 22 Y terms of two 22-qubit complex64 states (3 launches) 155 -> 90 us, of which
+// the parity of a pair being known at compile time and the loads ahead gave the last 25.
 constexpr int kRowBits = 8;   // 256 threads
 
 // Sum over one thread's pairs (p, p ^ X) of Re (odd: Im) conj(a[p ^ X]) a[p] with the sign of
@@ -1241,20 +1245,19 @@ __device__ __forceinline__ double pair_sum(const double (&re)[EL], const double 
     return s;
 }
 
-// Two states: the sums of conj(a[p ^ X]) b[p] over the p of even and of odd parity.
-template <int X, int EL>
+// Two states: w[0] + i w[1] = the sum of conj(a[p ^ X]) b[p] over the p whose kept Z bits have
+// even parity, w[2] + i w[3] over the odd ones.
+template <int X, int Z, int EL>
 __device__ __forceinline__ void pair_sums2(const double (&ar)[EL], const double (&ai)[EL], const double (&br)[EL],
-                                           const double (&bi)[EL], int zr, double (&w)[4])
+                                           const double (&bi)[EL], double (&w)[4])
 {
 #pragma unroll
     for (int p = 0; p < EL; ++p) {
-        const double wr = ar[p ^ X] * br[p] + ai[p ^ X] * bi[p];
-        const double wi = ar[p ^ X] * bi[p] - ai[p ^ X] * br[p];
-        const double odd = (__popc(p & zr) & 1) ? 1.0 : 0.0, even = 1.0 - odd;
-        w[0] = fma(wr, even, w[0]);
-        w[1] = fma(wi, even, w[1]);
-        w[2] = fma(wr, odd, w[2]);
-        w[3] = fma(wi, odd, w[3]);
+        const int o = (__builtin_popcount(p & Z) & 1) * 2;
+        w[o] = fma(ar[p ^ X], br[p], w[o]);
+        w[o + 1] = fma(ar[p ^ X], bi[p], w[o + 1]);
+        w[o] = fma(ai[p ^ X], bi[p], w[o]);
+        w[o + 1] = fma(-ai[p ^ X], br[p], w[o + 1]);
     }
 }
 
@@ -1295,12 +1298,20 @@ __global__ __launch_bounds__(kThreads) void k_expval_r(const C* __restrict__ sa,
     for (int i = tid; i < t.nterms << 6; i += kThreads) sums[i] = 0.0;
     gptr<C> ga = (gptr<C>)const_cast<C*>(sa), gb = (gptr<C>)const_cast<C*>(sb);
     const long long tl = local_off_bits(a, tid << LW, LW, kRowBits + LW);
+    floatx4 va[NS], vb[TWO ? NS : 1];
+    auto load = [&](long long tile) {
+        const long long o = tile_base(a, tile) + tl;
+        load_tile<C, NS, W, kThreads>(ga + o, a, va);
+        if constexpr (TWO) load_tile<C, NS, W, kThreads>(gb + o, a, vb);
+    };
+    load(blockIdx.x);
     __syncthreads();
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const long long base = tile_base(a, tile);
-        move_tile_n<C, true, NS, W>(ga, la, a, base + tl);
-        if (TWO) move_tile_n<C, true, NS, W>(gb, lb, a, base + tl);
+        put_tile<C, NS, W, kThreads>(la, va);
+        if constexpr (TWO) put_tile<C, NS, W, kThreads>(lb, vb);
         lds_sync();
+        if (tile + gridDim.x < ntiles) load(tile + gridDim.x);
         int i = 0;
         for (int r = 0; r < rd.nrounds; ++r) {
             const int bits = __builtin_amdgcn_readfirstlane(rbits[r]);
@@ -1360,14 +1371,10 @@ __global__ __launch_bounds__(kThreads) void k_expval_r(const C* __restrict__ sa,
                     if (par) val = -val;
                 } else {
                     double w[4] = {0.0, 0.0, 0.0, 0.0};
-                    switch (x & 7) {
-                    case 1: pair_sums2<1>(ar, ai, br, bi, z, w); break;
-                    case 2: pair_sums2<2>(ar, ai, br, bi, z, w); break;
-                    case 3: pair_sums2<3>(ar, ai, br, bi, z, w); break;
-                    case 4: pair_sums2<4>(ar, ai, br, bi, z, w); break;
-                    case 5: pair_sums2<5>(ar, ai, br, bi, z, w); break;
-                    case 6: pair_sums2<6>(ar, ai, br, bi, z, w); break;
-                    default: pair_sums2<7>(ar, ai, br, bi, z, w); break;
+                    switch (x & 7) {   // one kept bit (plan_elements), its Z factor present or not
+                    case 1: z ? pair_sums2<1, 1>(ar, ai, br, bi, w) : pair_sums2<1, 0>(ar, ai, br, bi, w); break;
+                    case 2: z ? pair_sums2<2, 2>(ar, ai, br, bi, w) : pair_sums2<2, 0>(ar, ai, br, bi, w); break;
+                    default: z ? pair_sums2<4, 4>(ar, ai, br, bi, w) : pair_sums2<4, 0>(ar, ai, br, bi, w); break;
                     }
                     const double er = par ? w[2] : w[0], ei = par ? w[3] : w[1];
                     const double orr = par ? w[0] : w[2], oi = par ? w[1] : w[3];
