@@ -24,8 +24,9 @@ steps, on the state's stream) and by the 8 TB/s peak.  Beside it, the ALU fracti
 same launches: algorithmic flops per launch = 2 x (the plan's complex-arithmetic FMA per
 amplitude / passes) x 2^n against a peak that combines the VALU rate for the VALU share
 of the FMA (78.6 TFLOP/s: FP64 vector, and FP32 without packed math) with the
-matrix-core rate for the matrix-core share (FP32 MFMA 157.3 TFLOP/s for complex64, FP64
-MFMA 78.6 TFLOP/s for complex128).  traffic = HBM bytes per launch measured with rocprofv3 counters
+matrix-core rate for the matrix-core share (FP32 MFMA 157.3 TFLOP/s for complex64, whose
+ops run as bfloat16 products of exact FP32 splits but are priced as the FP32 arithmetic
+they stand for; FP64 MFMA 78.6 TFLOP/s for complex128).  traffic = HBM bytes per launch measured with rocprofv3 counters
 (FETCH_SIZE + WRITE_SIZE, scaled by the same counters' reading for a device copy of
 known size), taken from the summary under profiles/ when that summary was made from
 the current kernel source, else null.

@@ -118,12 +118,12 @@ typedef struct {
     int low_qubits;      /* contiguous low qubits kept in every tile, 0 = default */
     double pass_budget;  /* per-pass arithmetic budget (FMA per amplitude: a dense op
                             4 * 2^k, halved on complex64 matrix cores, times 3/4 for a
-                            4-qubit matrix-core op), 0 = default, < 0 = unlimited.  A pass
-                            also ends where its next matrix-core op's operand would not
-                            fit the pass's LDS operand block */
+                            4-qubit matrix-core op), 0 = default, < 0 = unlimited.  A
+                            matrix-core op whose operand no longer fits the pass's LDS
+                            operand block waits for the next pass */
     int matrix_cores;    /* dense ops on >= this many (and at most 4) targets run on matrix
-                            cores (MFMA; FP32 for complex64, FP64 for complex128) when their
-                            operand block fits the pass's LDS budget: 0 = default (3),
+                            cores (MFMA; complex64: bfloat16 products of exact three-way FP32
+                            splits, FP32 accumulation; complex128: FP64): 0 = default (3),
                             -1 = never, 3 or 4 otherwise */
     int commute;         /* fuse = 1 only.  1 (default): commutation-aware DAG -- ops that
                             are diagonal on every qubit they share are left unordered, so
@@ -141,8 +141,8 @@ typedef struct {
     size_t fused_out;      /* fused gates after DAG fusion */
     size_t passes;         /* HBM passes (kernel launches) per application */
     size_t dense_ops, diag_ops, perm_ops;
-    size_t mfma_ops;       /* dense ops run on matrix cores (FP32 MFMA for complex64,
-                              FP64 MFMA for complex128) */
+    size_t mfma_ops;       /* dense ops run on matrix cores (split bfloat16 MFMA for
+                              complex64, FP64 MFMA for complex128) */
     double fma_per_amp;    /* complex-arithmetic cost summed over all passes */
     double hbm_bytes;      /* algorithmic HBM bytes per application = passes * 2 * 2^n * elem */
     double mfma_fma_per_amp;  /* the part of fma_per_amp done by the matrix-core ops */

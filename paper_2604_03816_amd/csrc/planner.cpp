@@ -63,8 +63,9 @@ PlanOpts default_opts(int dtype)
         o.pass_budget = 320;
         o.sigma = 8;
         o.amp_floats = 4;
-        o.mfma_min_k = 3;          // FP64 matrix cores: no faster than FP64 VALU in peak,
-        o.stage_floats = 4096;  // but free of the VALU path's per-row scalar loads
+        o.mfma_min_k = 3;       // FP64 matrix cores: no faster than FP64 VALU in peak, but
+                                // free of the VALU path's per-row scalar loads
+        o.stage_floats = 4096;  // 16 KiB (four operands) beside a 64 KiB tile: two workgroups per CU
     }
     return o;
 }
@@ -775,11 +776,6 @@ int operand_floats(int dtype, int k)
     return dtype == 1 && k == 4 ? 1024 : 512;
 }
 
-// One pass built greedily from the ops not yet done (in their order).  grow: the tile
-// starts as `A0` and takes the qubits of every op that joins, up to m; otherwise the
-// tile is exactly `A0` and only ops inside it (or diagonal ops) join.  An op joins when
-// none of its qubits is blocked by an earlier deferred op it may not commute with, the
-// tile holds it and the pass's arithmetic budget allows.
 // What scheduling asks of an op.
 struct OpInfo {
     unsigned long long gm, gd;   // its qubits; those it is diagonal on (commutation-aware plans)
@@ -805,6 +801,11 @@ std::vector<OpInfo> op_infos(const std::vector<FGate>& fused, const PlanOpts& o)
     return v;
 }
 
+// One pass built greedily from the ops not yet done (in their order).  grow: the tile
+// starts as `A0` and takes the qubits of every op that joins, up to m; otherwise the
+// tile is exactly `A0` and only ops inside it (or diagonal ops) join.  An op joins when
+// none of its qubits is blocked by an earlier deferred op it may not commute with, the
+// tile holds it and the pass's arithmetic budget and staged block allow.
 PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int>& todo, const PlanOpts& o,
                     int m, int L, bool whole, unsigned long long A0, bool grow)
 {
