@@ -824,6 +824,7 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
         blocked_d &= ~blocked;
     };
     double budget = o.pass_budget;
+    const int cap = o.pass_floats > 0 ? o.pass_floats : o.stage_floats;
     int afl = 0;   // operand floats staged so far, as the device tables stage them
     for (const int i : todo) {
         const OpInfo& g = ops[(size_t)i];
@@ -835,11 +836,11 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
         }
         const double c = g.cost;
         const bool limit_ops = o.max_ops_per_pass > 0 && (int)pp.ops.size() >= o.max_ops_per_pass;
-        // a matrix-core op whose operand no longer fits the pass's staged block waits for the
+        // a matrix-core op whose operand no longer fits the pass's block waits for the
         // next pass: reading it from global memory in the op phase would wait for the next
         // tile's loads (diagonal tables are staged too, where they fit)
         const int af = g.floats;
-        const bool fits_operands = whole || !g.matrix || ((afl + 3) & ~3) + af <= o.stage_floats || pp.ops.empty();
+        const bool fits_operands = whole || !g.matrix || ((afl + 3) & ~3) + af <= cap || pp.ops.empty();
         const bool fits_budget = whole || o.pass_budget < 0 || c <= budget || pp.ops.empty();
         unsigned long long nA = g.diag ? A : (A | gm);
         if (grow && pp.ops.empty() && __builtin_popcountll(nA) > m) {
@@ -854,7 +855,7 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
             pp.ops.push_back(i);
             budget -= c;
             pp.cost += c;
-            if (af > 0 && ((afl + 3) & ~3) + af <= o.stage_floats) afl = ((afl + 3) & ~3) + af;
+            if (af > 0 && ((afl + 3) & ~3) + af <= cap) afl = ((afl + 3) & ~3) + af;
         } else {
             defer(gm, gd);
             if ((blocked & all) == all) break;
