@@ -49,6 +49,8 @@ struct FGate {
                                 // matrix applies them
 };
 
+constexpr int kNoPassCap = 1 << 28;   // PlanOpts::pass_floats: as many operands as the budget takes
+
 struct PlanOpts {
     int fuse = 1;
     int commute = 1;           // fuse == 1 only: commutation-aware DAG, fusion and scheduling
@@ -64,7 +66,7 @@ struct PlanOpts {
     bool fp32_mfma = false;    // complex64: matrix-core ops as bfloat16 products of exact FP32 splits
     int stage_floats = 2048;   // per-pass cap of floats staged in LDS (diagonal tables, then
                                // matrix operands)
-    int pass_floats = 0;       // per-pass cap of those floats when scheduling; 0: stage_floats
+    int pass_floats = 0;       // per-pass cap of those floats when scheduling; 0: by the state's size
     int amp_floats = 2;        // floats per complex entry (2: complex64, 4: complex128)
 };
 

@@ -514,9 +514,10 @@ qsv_status qsv_server_submit(qsv_server s, int n, qsv_dtype dtype, const qsv_gat
     const int cap = kServeTileQubits[dtype];
     r->popts.tile_qubits = std::min(r->popts.tile_qubits, cap);
     r->popts.whole_state_max = std::min(r->popts.whole_state_max, cap);
-    // the batched kernels read matrix operands from global memory, so the LDS block (their
-    // diagonal tables) does not limit how many a pass holds: passes as in the plain path
-    r->popts.pass_floats = r->popts.stage_floats;
+    // the batched kernels read matrix operands through L2, so the LDS block (their diagonal
+    // tables) does not limit how many a pass holds (two 4-qubit complex128 ones, as it did:
+    // 392 circuits/s of the 70/30 mix; four: 444; no limit: 464)
+    r->popts.pass_floats = kNoPassCap;
     r->popts.stage_floats = std::min(r->popts.stage_floats, kServeOperandFloats);
     if (r->popts.low_qubits >= r->popts.tile_qubits) r->popts.low_qubits = r->popts.tile_qubits - 1;
     r->gates.resize(n_gates);
@@ -701,7 +702,7 @@ qsv_status qsv_server_step(qsv_server s, int* n_running, int* n_pending)
             const int cap = kServeTileQubits[QSV_C128];
             q->popts.tile_qubits = std::min(q->popts.tile_qubits, cap);
             q->popts.whole_state_max = std::min(q->popts.whole_state_max, cap);
-            q->popts.pass_floats = q->popts.stage_floats;
+            q->popts.pass_floats = kNoPassCap;
             q->popts.stage_floats = std::min(q->popts.stage_floats, kServeOperandFloats);
             if (q->popts.low_qubits >= q->popts.tile_qubits) q->popts.low_qubits = q->popts.tile_qubits - 1;
             q->popts.fuse = r->popts.fuse;
