@@ -1371,10 +1371,15 @@ void build_device_tables(HostPlan& P)
         }
         a.staged = matrix_ops.empty() || P.ops[(size_t)matrix_ops.back()].aoff >= 0;
         {
+            // complex128 passes with operands beyond the LDS block count as wide too: served,
+            // these heavier passes then have a launch of their own (closed loop with the
+            // precision chosen per request 366 against 350 circuits/s; a plain pass takes the
+            // same time in either variant).  complex64 ones are faster in the lighter variant
+            // (22-qubit brickwork 358 and 355 us, 70/30 mix 538 and 549 circuits/s).
             bool wide = false;
             for (int i = a.op_begin; i < a.op_begin + a.op_count; ++i) {
                 const DevOp& d = P.ops[(size_t)i];
-                wide |= (d.kind == OP_DENSE && d.aoff < 0 && d.k >= 4) || (d.kind == OP_PERM && d.k >= 3);
+                wide |= (d.kind == OP_DENSE && (dtype == 0 ? d.goff : d.aoff) < 0 && d.k >= 4) || (d.kind == OP_PERM && d.k >= 3);
             }
             P.pwide.push_back(wide ? 1 : 0);
         }
