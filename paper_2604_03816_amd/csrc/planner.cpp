@@ -433,43 +433,60 @@ std::vector<int> topo_order(const std::vector<Node>& nodes)
 }
 
 // Products formed while a plan is made, by their factors' ids: the planner fuses a circuit
-// twice (on two DAGs) and most merges are the same.
+// twice (on two DAGs) and most merges are the same.  They are kept without their member lists
+// (a chain of G gates on few qubits has G products of up to G members) and up to kKeepBytes
+// of matrices; beyond that they are dropped and later ones formed again.
 struct Products {
+    static constexpr size_t kKeepBytes = 64u << 20;
     std::unordered_map<unsigned long long, FGate> made;
+    size_t bytes = 0;
     int next = 0;   // id of the next product
+
+    void keep(unsigned long long key, const FGate& f)   // (f.mem still empty)
+    {
+        const size_t b = sizeof(FGate) + f.m.size() * sizeof(cd);
+        if (bytes + b > kKeepBytes) {
+            made.clear();
+            bytes = 0;
+        }
+        made.emplace(key, f);
+        bytes += b;
+    }
 };
 
 FGate fuse_pair(const FGate& u, const FGate& v, int kmax, bool& ok, Products& pr)
 {
     const unsigned long long key = ((unsigned long long)(unsigned)u.id << 32) | (unsigned)v.id;
+    FGate f;
     const auto hit = pr.made.find(key);
     if (hit != pr.made.end()) {
         ok = hit->second.k <= kmax;
-        return hit->second;
+        if (!ok) return FGate{};
+        f = hit->second;
+    } else {
+        int Q[2 * kMaxK], kq = 0;
+        for (int j = 0; j < u.k; ++j) Q[kq++] = u.q[j];
+        for (int j = 0; j < v.k; ++j) {
+            bool dup = false;
+            for (int i = 0; i < u.k; ++i) dup |= (u.q[i] == v.q[j]);
+            if (!dup) Q[kq++] = v.q[j];
+        }
+        ok = kq <= kmax;
+        if (!ok) return FGate{};
+        std::sort(Q, Q + kq);
+        f.k = kq;
+        for (int j = 0; j < kq; ++j) f.q[j] = Q[j];
+        // Eq. 9: U_fused = U_v . U_u (u applied first)
+        f.m = embedded_product(v, u, Q, kq);
+        inspect(f);
+        f.id = pr.next++;
+        f.first = std::min(u.first, v.first);
+        f.members = u.members + v.members;
+        pr.keep(key, f);
     }
-    int Q[2 * kMaxK], kq = 0;
-    for (int j = 0; j < u.k; ++j) Q[kq++] = u.q[j];
-    for (int j = 0; j < v.k; ++j) {
-        bool dup = false;
-        for (int i = 0; i < u.k; ++i) dup |= u.q[i] == v.q[j];
-        if (!dup) Q[kq++] = v.q[j];
-    }
-    ok = kq <= kmax;
-    FGate f;
-    if (!ok) return f;
-    std::sort(Q, Q + kq);
-    f.k = kq;
-    for (int j = 0; j < kq; ++j) f.q[j] = Q[j];
-    // Eq. 9: U_fused = U_v . U_u (u applied first)
-    f.m = embedded_product(v, u, Q, kq);
-    inspect(f);
-    f.id = pr.next++;
-    f.first = std::min(u.first, v.first);
-    f.members = u.members + v.members;
     f.mem.reserve(u.mem.size() + v.mem.size());
     f.mem.insert(f.mem.end(), u.mem.begin(), u.mem.end());
     f.mem.insert(f.mem.end(), v.mem.begin(), v.mem.end());
-    pr.made.emplace(key, f);
     return f;
 }
 
