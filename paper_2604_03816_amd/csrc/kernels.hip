@@ -2074,11 +2074,7 @@ hipError_t launch_pass(int dtype, void* st, const PassArgs& a, long long ntiles,
                        const void* pool, const int* ipool, const float* apool, hipStream_t s, void* st2,
                        bool from_zero, bool wide)
 {
-    // Loading ahead needs workgroups that take two tiles or more while the device is full
-    // (16 per CU; 25-qubit complex64 passes: 0.139 ms without it, 0.130 with two tiles
-    // per workgroup, 0.136 with four, 0.143 with eight).  complex64 moves pairs of
-    // amplitudes, so qubit 0 must be a tile qubit: it is wherever L >= 1.
-    const bool pf = a.m == 12 && a.L >= 1 && a.staged && !from_zero && (st2 ? 2 : 1) * ntiles >= 32ll * device_cus();
+    const bool pf = a.staged && !from_zero && loads_ahead(a.m, a.L, (st2 ? 2 : 1) * ntiles, device_cus());
     auto go = [&](auto c, auto w, auto p) {
         return launch_pass_t<decltype(c), decltype(w)::value, decltype(p)::value>(st, st2, a, ntiles, ops, pool, ipool,
                                                                                    apool, s, from_zero);

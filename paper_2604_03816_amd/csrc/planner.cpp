@@ -841,13 +841,15 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
         blocked_d &= ~blocked;
     };
     double budget = o.pass_budget;
-    // Operands need to be in LDS only where a pass loads its next tile during the ops (from
-    // 2^13 tiles of one or two states on); elsewhere they come through L2 and only the
-    // budget ends a pass.  Capped and not, 8-layer ansatz: 22 qubits complex128 12 and 6
-    // passes, 523 and 405 us, complex64 10 and 8, 242 and 223 us; 18 qubits complex128 136
-    // and 124 us.  Complex64 below 20 qubits has few tiles, whose chains of steps grow
-    // (18 qubits 96 and 103 us; brickwork 140 and 128): capped.
-    const bool free_ops = n - o.tile_qubits < 12 && !(o.fp32_mfma && n < 20);
+    // Operands need to be in LDS only where a pass loads its next tile during the ops;
+    // elsewhere they come through L2 and only the budget ends a pass.  A plan does not say
+    // whether its launches cover one state or two (the adjoint's), so the line is where two
+    // would load ahead.  Capped and not, 8-layer ansatz: 22 qubits complex128 12 and 6
+    // passes, 523 and 405 us, complex64 10 and 8, 242 and 223 us; 18 qubits complex128
+    // 136 and 124 us.  Complex64 below 20 qubits has fewer tiles than CUs, whose chains of
+    // steps grow (18 qubits 96 and 103 us; brickwork 140 and 128): capped.
+    const long long tiles = 1ll << (n - m);
+    const bool free_ops = !loads_ahead(m, L, 2 * tiles, kPlanCUs) && !(o.fp32_mfma && tiles < kPlanCUs);
     const int cap = o.pass_floats > 0 ? o.pass_floats : free_ops ? kNoPassCap : o.stage_floats;
     int afl = 0;   // operand floats staged so far, as the device tables stage them
     for (const int i : todo) {

@@ -66,7 +66,8 @@ struct PlanOpts {
     bool fp32_mfma = false;    // complex64: matrix-core ops as bfloat16 products of exact FP32 splits
     int stage_floats = 2048;   // per-pass cap of floats staged in LDS (diagonal tables, then
                                // matrix operands)
-    int pass_floats = 0;       // per-pass cap of those floats when scheduling; 0: by the state's size
+    int pass_floats = 0;       // per-pass cap of those floats when scheduling; 0: stage_floats where
+                               // a pass may load ahead (loads_ahead), else none
     int amp_floats = 2;        // floats per complex entry (2: complex64, 4: complex128)
 };
 

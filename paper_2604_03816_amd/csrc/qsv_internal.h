@@ -188,6 +188,19 @@ constexpr int kZChunkQubits = 14;
 // much behind the tile).
 constexpr int kServeOperandFloats = 2048;
 
+// Whether a pass of `tiles` tiles (of all states that share its launch) loads its next tile
+// during the ops on this one (k_pass), if its matrix operands are all in LDS: tiles of 2^12
+// amplitudes with qubit 0 among their bits (complex64 moves pairs), and workgroups that take
+// two tiles or more while the device is full, 16 per CU (25-qubit complex64 passes 0.139 ms
+// without loads ahead, 0.130 with two tiles per workgroup, 0.136 with four, 0.143 with eight).
+// The planner asks for kPlanCUs, a whole MI355X; the launcher for the device's own.
+constexpr int kAheadTileQubits = 12;
+constexpr int kPlanCUs = 256;
+inline bool loads_ahead(int m, int L, long long tiles, int cus)
+{
+    return m == kAheadTileQubits && L >= 1 && tiles >= 32ll * cus;
+}
+
 // Largest tile (log2 amplitudes) a dtype's pass kernel holds in LDS (64 KiB).
 __host__ __device__ constexpr int kMaxTileQubitsC(int dt) { return dt == 0 ? 13 : 12; }
 

@@ -1,12 +1,50 @@
 """Facts of the planner's results that end results alone would not show (no GPU): memory of a
-plan being made."""
+plan being made, what its passes stage."""
+import ctypes
 import os
 import subprocess
 import sys
 
 import pytest
 
+from paper_2604_03816_amd import build as qsv_build
+from paper_2604_03816_amd import circuits as C
+from paper_2604_03816_amd import qsv
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+class PassFacts(ctypes.Structure):   # plan_facts.cpp
+    _fields_ = [(f, ctypes.c_int) for f in ("tile_qubits", "low_qubits", "ops", "matrix_ops", "staged", "diag_ops",
+                                            "diag_unstaged", "a_len", "d_len")] + [("tiles", ctypes.c_longlong)]
+
+
+@pytest.fixture(scope="module")
+def facts(tmp_path_factory):
+    qsv.lib()
+    so = str(tmp_path_factory.mktemp("plan_facts") / "libplan_facts.so")
+    src = os.path.join(ROOT, "tests", "plan_facts.cpp")
+    cmd = [qsv_build.HIPCC, "--offload-host-only", "-std=c++17", "-O1", "-fPIC", "-shared",
+           "-I" + os.path.join(ROOT, "include"), "-I" + qsv_build.CSRC, "-x", "hip", src, "-o", so,
+           "-L" + qsv_build.OUT_DIR, "-lqsv", "-Wl,-rpath," + qsv_build.OUT_DIR]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return ctypes.CDLL(so)
+
+
+def pass_facts(lib, n, dtype, ops, tile=12):
+    g = qsv.GateList(ops)
+    out = (PassFacts * 4096)()
+    count = lib.plan_facts(n, 0 if dtype == "c64" else 1, tile, g.arr, ctypes.c_size_t(g.n), out, 4096)
+    assert 0 <= count <= 4096
+    return list(out[:count])
+
+
+def circuit(name, n, depth, seed):
+    if name == "hea":
+        return C.bind(C.hea(n, depth), C.hea_params(n, depth, seed))
+    return {"brickwork": lambda: C.brickwork(n, depth, seed), "qft": lambda: C.qft(n),
+            "bricks": lambda: C.h_t_cz_bricks(n, depth, seed), "mix": lambda: C.commuting_mix(n, 25 * depth, seed)}[name]()
 
 
 def run_python(code):
@@ -36,3 +74,15 @@ print(p.stats()["fused_out"], resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
 """)
     assert int(out[0]) == 1
     assert int(out[1]) <= 128 << 10, out
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("tile,n,capped", [(12, 21, False), (12, 23, False), (12, 24, True), (12, 25, True),
+                                           (11, 25, False), (10, 22, False)])
+def test_operands_end_a_pass_only_where_it_may_load_ahead(facts, dtype, tile, n, capped):
+    """A pass on tiles of 2^12 amplitudes whose launch covers 2^13 of them (two states count
+    twice) loads its next tile during the ops if all matrix operands are in LDS, so the planner
+    ends it where they are full; on other tiles and below, one with more operands is as good."""
+    fs = pass_facts(facts, n, dtype, C.brickwork(n, 8, 3), tile)
+    assert all(f.tile_qubits == tile and f.tiles == 1 << (n - tile) for f in fs)
+    assert all(f.staged for f in fs) == capped
