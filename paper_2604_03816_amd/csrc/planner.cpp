@@ -851,7 +851,7 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
     const long long tiles = 1ll << (n - m);
     const bool free_ops = !loads_ahead(m, L, 2 * tiles, kPlanCUs) && !(o.fp32_mfma && tiles < kPlanCUs);
     const int cap = o.pass_floats > 0 ? o.pass_floats : free_ops ? kNoPassCap : o.stage_floats;
-    int afl = 0;   // operand floats staged so far, as the device tables stage them
+    int afl = 0;   // floats of the pass's block so far
     for (const int i : todo) {
         const OpInfo& g = ops[(size_t)i];
         const unsigned long long gm = g.gm, gd = g.gd;
@@ -862,9 +862,9 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
         }
         const double c = g.cost;
         const bool limit_ops = o.max_ops_per_pass > 0 && (int)pp.ops.size() >= o.max_ops_per_pass;
-        // a matrix-core op whose operand no longer fits the pass's block waits for the
-        // next pass: reading it from global memory in the op phase would wait for the next
-        // tile's loads (diagonal tables are staged too, where they fit)
+        // a matrix-core op whose operand no longer fits the pass's block waits for the next
+        // pass: with one operand in global memory the pass could not load ahead.  A diagonal op
+        // joins with its table outside the block if need be (build_device_tables)
         const int af = g.floats;
         const bool fits_operands = whole || !g.matrix || ((afl + 3) & ~3) + af <= cap || pp.ops.empty();
         const bool fits_budget = whole || o.pass_budget < 0 || c <= budget || pp.ops.empty();
@@ -1226,6 +1226,13 @@ std::vector<cd> widen(HostPlan& P, int oi, const FGate& g, const PassPlan& pp, u
     return M;
 }
 
+// Matrix cores need 16 groups per block in a tile of 2^m amplitudes; complex64 3-qubit ops are
+// run as 4-qubit ones on one more tile bit.
+bool on_matrix_cores(const FGate& g, const PlanOpts& o, int dtype, int m)
+{
+    return mfma_eligible(g, o) && m >= (dtype == 0 ? 8 : g.k + 4);
+}
+
 // Device tables of a planned circuit (op descriptors, matrix pools, staged operand
 // blocks, pass arguments) and the arithmetic statistics, from P.fused and P.passes.
 void build_device_tables(HostPlan& P)
@@ -1265,6 +1272,19 @@ void build_device_tables(HostPlan& P)
         a.a_off = (int)P.apool.size();
         a.a_len = 0;
         std::vector<int> matrix_ops;   // this pass's matrix-core ops (indices into P.ops)
+        // The block's floats that diagonal tables may take.  A pass loads ahead only with all
+        // its matrix operands in the block, so where one state's tiles suffice for that they come
+        // first and the tables take what they leave; a table read from global memory waits once
+        // for the next tile's loads (27-qubit complex64 ansatz of 6 layers, five such passes of
+        // ten: 6.00 -> 5.77 ms).  Other passes read their operands through L2, and the tables
+        // have the whole block.
+        int room = o.stage_floats;
+        if (o.pass_floats == 0 && loads_ahead(a.m, a.L, 1ll << (n - a.m), kPlanCUs)) {
+            int need = 0;
+            for (const int fi : pp.ops)
+                if (on_matrix_cores(P.fused[fi], o, dtype, a.m)) need += operand_floats(dtype, P.fused[fi].k);
+            if (need <= room) room -= need;
+        }
         for (const int fi : pp.ops) {
             const FGate& g = P.fused[fi];
             DevOp d{};
@@ -1282,9 +1302,7 @@ void build_device_tables(HostPlan& P)
             if (g.kind == OP_DENSE) {
                 P.pool.insert(P.pool.end(), g.m.vec().begin(), g.m.vec().end());
                 ++P.dense_ops;
-                // matrix cores need 16 groups per block; complex64 3-qubit ops are run as
-                // 4-qubit ones on one more tile bit
-                if (mfma_eligible(g, o) && a.m >= (dtype == 0 ? 8 : g.k + 4)) {
+                if (on_matrix_cores(g, o, dtype, a.m)) {
                     matrix_ops.push_back((int)P.ops.size());
                     ++P.mfma_ops;
                     P.mfma_fma_per_amp += op_fma(g);
@@ -1296,7 +1314,7 @@ void build_device_tables(HostPlan& P)
                 // in the state's precision as raw floats, 16-byte aligned
                 const int per = dtype == 0 ? 2 : 4;
                 const int at = (a.a_len + 3) & ~3;
-                if (at + per * dd <= o.stage_floats) {
+                if (at + per * dd <= room) {
                     P.apool.resize((size_t)a.a_off + at, 0.0f);
                     for (int r = 0; r < dd; ++r) {
                         const cd v = g.m[(size_t)r * dd + r];

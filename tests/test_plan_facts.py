@@ -86,3 +86,13 @@ def test_operands_end_a_pass_only_where_it_may_load_ahead(facts, dtype, tile, n,
     fs = pass_facts(facts, n, dtype, C.brickwork(n, 8, 3), tile)
     assert all(f.tile_qubits == tile and f.tiles == 1 << (n - tile) for f in fs)
     assert all(f.staged for f in fs) == capped
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("name,depth", [("hea", 6), ("hea", 12), ("qft", 1), ("bricks", 12), ("mix", 12), ("brickwork", 8)])
+def test_passes_that_load_ahead_have_their_matrix_operands_staged(facts, name, depth, dtype):
+    """Whatever diagonal tables share the pass's block in LDS."""
+    for n in range(25, 31):
+        for p, f in enumerate(pass_facts(facts, n, dtype, circuit(name, n, depth, 1))):
+            assert f.staged, (n, p, f.matrix_ops, f.diag_ops, f.a_len)
+            assert f.d_len <= f.a_len <= (2048 if dtype == "c64" else 4096)
