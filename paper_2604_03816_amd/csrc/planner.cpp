@@ -845,12 +845,11 @@ PassPlan build_pass(int n, const std::vector<OpInfo>& ops, const std::vector<int
     // elsewhere they come through L2 and only the budget ends a pass.  A plan does not say
     // whether its launches cover one state or two (the adjoint's), so the line is where two
     // would load ahead.  Capped and not, 8-layer ansatz: 22 qubits complex128 12 and 6
-    // passes, 523 and 405 us, complex64 10 and 8, 242 and 223 us; 18 qubits complex128
-    // 136 and 124 us.  Complex64 below 20 qubits has fewer tiles than CUs, whose chains of
-    // steps grow (18 qubits 96 and 103 us; brickwork 140 and 128): capped.
-    const long long tiles = 1ll << (n - m);
-    const bool free_ops = !loads_ahead(m, L, 2 * tiles, kPlanCUs) && !(o.fp32_mfma && tiles < kPlanCUs);
-    const int cap = o.pass_floats > 0 ? o.pass_floats : free_ops ? kNoPassCap : o.stage_floats;
+    // passes, 523 and 405 us, complex64 10 and 8, 242 and 223 us; 18 qubits complex128 136
+    // and 123 us; complex64 at 14, 16 and 19 qubits 66 and 55, 79 and 71, 109 and 98 us (12
+    // layers of brickwork 58 and 54, 75 and 70, 97 and 100).
+    const bool ahead = loads_ahead(m, L, 2ll << (n - m), kPlanCUs);
+    const int cap = o.pass_floats > 0 ? o.pass_floats : ahead ? o.stage_floats : kNoPassCap;
     int afl = 0;   // floats of the pass's block so far
     for (const int i : todo) {
         const OpInfo& g = ops[(size_t)i];
@@ -1495,8 +1494,15 @@ bool make_plan(int n, int dtype, const std::vector<InGate>& gates, const PlanOpt
             for (const FGate& g : f) a += op_cost(g, o);
             return a;
         };
-        if (alt_passes.size() < P.passes.size() ||
-            (alt_passes.size() == P.passes.size() && arith(alt) < arith(P.fused))) {
+        // Complex64 with fewer tiles than CUs: a step (an LDS round trip of every tile) takes
+        // about half of what a pass adds, and the second fusion buys passes with diagonal
+        // steps (8-layer ansatz, by passes alone and so: 15 qubits 77 and 67 us, 16 qubits 84
+        // and 71, 18 qubits 100 and 95).  Elsewhere passes alone (20-qubit complex128 mix 562
+        // and 588 us, 22-qubit complex64 mix 757 and 776) and served (many states a launch).
+        const bool few = o.fp32_mfma && o.pass_floats == 0 && 1ll << std::max(0, n - o.tile_qubits) < kPlanCUs;
+        const size_t now = 2 * P.passes.size() + (few ? P.fused.size() : 0);
+        const size_t then = 2 * alt_passes.size() + (few ? alt.size() : 0);
+        if (then < now || (then == now && arith(alt) < arith(P.fused))) {
             P.fused.swap(alt);
             P.passes.swap(alt_passes);
         }

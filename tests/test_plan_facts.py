@@ -77,7 +77,7 @@ print(p.stats()["fused_out"], resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
 
 
 @pytest.mark.parametrize("dtype", ["c64", "c128"])
-@pytest.mark.parametrize("tile,n,capped", [(12, 21, False), (12, 23, False), (12, 24, True), (12, 25, True),
+@pytest.mark.parametrize("tile,n,capped", [(12, 15, False), (12, 19, False), (12, 21, False), (12, 23, False), (12, 24, True), (12, 25, True),
                                            (11, 25, False), (10, 22, False)])
 def test_operands_end_a_pass_only_where_it_may_load_ahead(facts, dtype, tile, n, capped):
     """A pass on tiles of 2^12 amplitudes whose launch covers 2^13 of them (two states count
@@ -96,3 +96,11 @@ def test_passes_that_load_ahead_have_their_matrix_operands_staged(facts, name, d
         for p, f in enumerate(pass_facts(facts, n, dtype, circuit(name, n, depth, 1))):
             assert f.staged, (n, p, f.matrix_ops, f.diag_ops, f.a_len)
             assert f.d_len <= f.a_len <= (2048 if dtype == "c64" else 4096)
+
+
+@pytest.mark.parametrize("n,steps", [(14, 28), (15, 28), (16, 30), (17, 34), (18, 36), (19, 38)])
+def test_few_tiles_save_passes_and_steps(facts, n, steps):
+    """complex64 states with fewer tiles than CUs: the 8-layer ansatz needs no more passes than
+    with its operands capped (6 to 9), and no diagonal steps bought with them."""
+    fs = pass_facts(facts, n, "c64", circuit("hea", n, 8, 1))
+    assert len(fs) <= n // 2 - 1 and sum(f.ops for f in fs) <= steps
