@@ -997,7 +997,8 @@ qsv_status qsv_plan_pass_ops(qsv_plan p, size_t i, int* fused_idx)
 
 // Host re-enactment of the pass kernel over the device tables (tile placement from the
 // free-bit runs, local offsets from the tile strides, ops by local bit positions), in
-// FP64.  Lets host tests check the tables the GPU consumes without a GPU.
+// FP64.  Lets host tests check the tables the GPU consumes without a GPU.  (Matrix-core ops
+// with their gates' matrices: the tables hold them in the state's precision.)
 qsv_status qsv_plan_emulate(qsv_plan p, double* state)
 {
     if (!p || !state) return fail(QSV_E_ARG, "null argument");
@@ -1030,6 +1031,9 @@ qsv_status qsv_plan_emulate(qsv_plan p, double* state)
                         if ((r >> j) & 1) o += 1 << op.lpos[j];
                     return o;
                 };
+                const cd* M = op.kind == OP_DENSE && op.goff >= 0
+                                  ? hp.fused[(size_t)hp.passes[pi].ops[(size_t)oi]].m.vec().data()
+                                  : hp.pool.data() + op.off;
                 if (op.kind == OP_DIAG) {
                     int gfix = 0;
                     for (int j = 0; j < K; ++j)
@@ -1038,7 +1042,7 @@ qsv_status qsv_plan_emulate(qsv_plan p, double* state)
                         int idx = gfix;
                         for (int j = 0; j < K; ++j)
                             if (op.lpos[j] >= 0) idx |= ((e >> op.lpos[j]) & 1) << j;
-                        lds[e] *= hp.pool[op.off + idx];
+                        lds[e] *= M[idx];
                     }
                     continue;
                 }
@@ -1055,12 +1059,12 @@ qsv_status qsv_plan_emulate(qsv_plan p, double* state)
                         for (int r = 0; r < D; ++r) v[r] = lds[b + roff(r)];
                         for (int r = 0; r < D; ++r) {
                             cd acc = 0;
-                            for (int c = 0; c < D; ++c) acc += hp.pool[op.off + r * D + c] * v[c];
+                            for (int c = 0; c < D; ++c) acc += M[r * D + c] * v[c];
                             w[r] = acc;
                         }
                     } else {
                         for (int r = 0; r < D; ++r) v[r] = lds[b + roff(hp.ipool[op.ioff + r])];
-                        for (int r = 0; r < D; ++r) w[r] = op.flags ? hp.pool[op.off + r] * v[r] : v[r];
+                        for (int r = 0; r < D; ++r) w[r] = op.flags ? M[r] * v[r] : v[r];
                     }
                     for (int r = 0; r < D; ++r) lds[b + roff(r)] = w[r];
                 }

@@ -720,7 +720,7 @@ __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp
             if (op.flags) {
                 ++oi;
                 op_mfma4<C, true, LDSOP, NT>(lds, T, op, ops[op_begin + oi], apool, alds);
-            } else if (op.k == 4) {
+            } else if (sizeof(C) == 8 || op.k == 4) {   // (complex64 3-qubit ops: widened operands)
                 op_mfma4<C, false, LDSOP, NT>(lds, T, op, op, apool, alds);
             } else {
                 if constexpr (sizeof(C) == 16) op_mfma3<LDSOP, NT>(lds, T, op, apool, alds);

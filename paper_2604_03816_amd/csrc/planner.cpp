@@ -1104,25 +1104,60 @@ void push_operand(std::vector<float>& out, int dtype, const std::vector<cd>& M, 
     }
 }
 
-// Operand and offset tables of the matrix-core op d (matrix M over tile bits d.lpos), or of
-// the pair (d, d2), appended to the plan's operand array; m: the tile's bits.
-// wave: the two tile bits that tell the waves apart, none of the targets.
-void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2, const std::vector<cd>* M2,
-                 const int (&wave)[2], std::vector<float>& out)
+// What a matrix-core op multiplies: its matrix over the tile bits lpos.
+struct Operand {
+    int k = 0, lpos[4];
+    std::vector<cd> own;             // a widened matrix
+    const std::vector<cd>* m = nullptr;
+
+    const std::vector<cd>& matrix() const { return m ? *m : own; }
+    unsigned bits() const
+    {
+        unsigned b = 0;
+        for (int j = 0; j < k; ++j) b |= 1u << lpos[j];
+        return b;
+    }
+};
+
+// The operand of gate g in pass pp.  A complex64 3-qubit one gains one more tile qubit, not in
+// `avoid` (and put there), as identity.
+Operand operand_of(int dtype, const FGate& g, const PassPlan& pp, unsigned long long& avoid)
 {
+    Operand o;
+    o.k = g.k;
+    int Q[4] = {g.q[0], g.q[1], g.q[2], g.q[3]};
+    if (dtype == 0 && g.k == 3) {
+        for (const int b : pp.active)
+            if (!((avoid >> b) & 1)) { Q[3] = b; break; }
+        avoid |= 1ull << Q[3];
+        std::sort(Q, Q + 4);
+        o.k = 4;
+        o.own = embed(g.m.vec(), g.q, 3, Q, 4);
+    } else {
+        o.m = &g.m.vec();
+    }
+    for (int j = 0; j < o.k; ++j)
+        o.lpos[j] = (int)(std::find(pp.active.begin(), pp.active.end(), Q[j]) - pp.active.begin());
+    return o;
+}
+
+// Operand and offset tables of the matrix-core op d (operand u), or of the pair (d, d2) of
+// operands u and u2, appended to the plan's operand array; m: the tile's bits.
+// wave: the two tile bits that tell the waves apart, none of the targets.
+void mfma_tables(int dtype, int m, DevOp& d, const Operand& u, DevOp* d2, const Operand* u2, const int (&wave)[2],
+                 std::vector<float>& out)
+{
+    const std::vector<cd>& M = u.matrix();
     const int eb = dtype == 0 ? 8 : 16;
     auto off = [&](int e) { return tile_slot(dtype, e) * eb; };
     // the matrix instruction's result row held by lane group q in register e, and back
     auto drow = [&](int q, int e) { return dtype == 0 ? 4 * q + e : 4 * e + q; };
     auto dq = [&](int r) { return dtype == 0 ? r >> 2 : r & 3; };
     auto de = [&](int r) { return dtype == 0 ? r & 3 : r >> 2; };
-    unsigned used = 0;
-    for (int j = 0; j < d.k; ++j) used |= 1u << d.lpos[j];
-    if (d2)
-        for (int j = 0; j < d2->k; ++j) used |= 1u << d2->lpos[j];
+    unsigned used = u.bits() | (d2 ? u2->bits() : 0);
     int col[4];   // tile bits that lane % 16 runs over in the reads
     if (d2) {
-        for (int i = 0; i < 4; ++i) col[i] = d2->lpos[i];
+        for (int i = 0; i < 4; ++i) col[i] = u2->lpos[i];
     } else {
         int nc = 0;   // independent bank bits first, then any; the wave bits only if nothing else is left
         const unsigned keep = (1u << wave[0]) | (1u << wave[1]);
@@ -1147,7 +1182,7 @@ void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2
         pack(&o.jbit, 0, bit(t[S.j0]));
         pack(&o.jbit, 1, bit(t[S.j1]));
     };
-    if (d.k == 3) {
+    if (u.k == 3) {
         // the real embedding: input column 4 ks + q is the real (ks even) or imaginary part
         // of complex input 4 (ks / 2) + q; matrix row i of the FP64 instruction comes back
         // as element i / 4 of lane group i % 4, and stands for complex row 2 (i % 4) + i / 8,
@@ -1167,28 +1202,28 @@ void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2
             pack(d.lout, i, bit(col[i]));
         }
         for (int i = 0; i < 2; ++i) {
-            pack(d.lin, 4 + i, bit(d.lpos[i]));        // rows 4 j + q
-            pack(d.lout, 4 + i, bit(d.lpos[1 + i]));   // rows 2 q + j
+            pack(d.lin, 4 + i, bit(u.lpos[i]));        // rows 4 j + q
+            pack(d.lout, 4 + i, bit(u.lpos[1 + i]));   // rows 2 q + j
         }
-        pack(&d.jbit, 0, bit(d.lpos[2]));
-        pack(&d.jbit, 1, bit(d.lpos[0]));
+        pack(&d.jbit, 0, bit(u.lpos[2]));
+        pack(&d.jbit, 1, bit(u.lpos[0]));
     } else if (!d2) {
-        const Spread S = spread_from(best_q0(dtype, d.lpos, col));
+        const Spread S = spread_from(best_q0(dtype, u.lpos, col));
         push_operand(out, dtype, M, [&](int r) { return S.state(dq(r), de(r)); },
                      [&](int q, int j) { return S.state(q, j); });
-        lanes(d, col, S, d.lpos);
+        lanes(d, col, S, u.lpos);
     } else {
         // reads: lane % 16 is the second op's state, (q, j) the first's (S1); after the
         // first product lane % 16 is the first op's new state and (q, e) the second's,
         // drow(q, e); after the second (q, e) is its new state by S2
-        const Spread S1 = spread_from(best_q0(dtype, d.lpos, d2->lpos));
-        const Spread S2 = spread_from(best_q0(dtype, d2->lpos, d.lpos));
+        const Spread S1 = spread_from(best_q0(dtype, u.lpos, u2->lpos));
+        const Spread S2 = spread_from(best_q0(dtype, u2->lpos, u.lpos));
         push_operand(out, dtype, M, [&](int r) { return r; }, [&](int q, int j) { return S1.state(q, j); });
-        lanes(d, d2->lpos, S1, d.lpos);
+        lanes(d, u2->lpos, S1, u.lpos);
         d2->goff = (int)out.size();
-        push_operand(out, dtype, *M2, [&](int r) { return S2.state(dq(r), de(r)); },
+        push_operand(out, dtype, u2->matrix(), [&](int r) { return S2.state(dq(r), de(r)); },
                      [&](int q, int j) { return drow(q, j); });
-        lanes(*d2, d.lpos, S2, d2->lpos);
+        lanes(*d2, u.lpos, S2, u2->lpos);
         d.flags = 1;
     }
     // the block number's bits: the tile bits that are left
@@ -1200,29 +1235,6 @@ void mfma_tables(int dtype, int m, DevOp& d, const std::vector<cd>& M, DevOp* d2
         }
     for (int b = 0; b < m && nb < kMaxBlockBits; ++b)
         if (!((used >> b) & 1)) pack(d.bbit, nb++, bit(b));
-}
-
-// A complex64 3-qubit op P.ops[oi] (gate g) gains one more tile qubit, not in `avoid`, as
-// identity: returns its 4-qubit matrix and updates its descriptor and pool matrix.  Other
-// ops: an empty matrix.
-std::vector<cd> widen(HostPlan& P, int oi, const FGate& g, const PassPlan& pp, unsigned long long& avoid)
-{
-    DevOp& d = P.ops[(size_t)oi];
-    if (!(P.dtype == 0 && g.k == 3)) return {};
-    int Q[4] = {g.q[0], g.q[1], g.q[2], -1};
-    for (const int b : pp.active)
-        if (!((avoid >> b) & 1)) { Q[3] = b; break; }
-    avoid |= 1ull << Q[3];
-    std::sort(Q, Q + 4);
-    std::vector<cd> M = embed(g.m.vec(), g.q, 3, Q, 4);
-    d.k = 4;
-    for (int j = 0; j < 4; ++j) {
-        d.gbit[j] = Q[j];
-        d.lpos[j] = (int)(std::find(pp.active.begin(), pp.active.end(), Q[j]) - pp.active.begin());
-    }
-    d.off = (int)P.pool.size();
-    P.pool.insert(P.pool.end(), M.begin(), M.end());
-    return M;
 }
 
 // Matrix cores need 16 groups per block in a tile of 2^m amplitudes; complex64 3-qubit ops are
@@ -1299,12 +1311,13 @@ void build_device_tables(HostPlan& P)
             d.off = (int)P.pool.size();
             d.aoff = d.goff = -1;
             if (g.kind == OP_DENSE) {
-                P.pool.insert(P.pool.end(), g.m.vec().begin(), g.m.vec().end());
                 ++P.dense_ops;
-                if (on_matrix_cores(g, o, dtype, a.m)) {
+                if (on_matrix_cores(g, o, dtype, a.m)) {   // its operand is all it reads
                     matrix_ops.push_back((int)P.ops.size());
                     ++P.mfma_ops;
                     P.mfma_fma_per_amp += op_fma(g);
+                } else {
+                    P.pool.insert(P.pool.end(), g.m.vec().begin(), g.m.vec().end());
                 }
             } else if (g.kind == OP_DIAG) {
                 for (int r = 0; r < dd; ++r) P.pool.push_back(g.m[(size_t)r * dd + r]);
@@ -1353,8 +1366,8 @@ void build_device_tables(HostPlan& P)
         auto gate_of = [&](int oi) -> const FGate& { return P.fused[(size_t)pp.ops[(size_t)(oi - a.op_begin)]]; };
         struct Step {   // one op or one pair
             int oi, oj;
-            std::vector<cd> w1, w2;   // widened matrices (empty: the gate's own)
-            unsigned bits;            // its tile bits
+            Operand u, u2;
+            unsigned bits() const { return u.bits() | u2.bits(); }
         };
         std::vector<Step> steps;
         for (size_t i = 0; i < matrix_ops.size(); ++i) {
@@ -1366,34 +1379,29 @@ void build_device_tables(HostPlan& P)
             if (oj == st.oi + 1 && pairable(g, o) && pairable(gate_of(oj), o) && !(qubit_mask(g) & qubit_mask(gate_of(oj))))
                 st.oj = oj;
             unsigned long long avoid = qubit_mask(g) | (st.oj >= 0 ? qubit_mask(gate_of(st.oj)) : 0);
-            st.w1 = widen(P, st.oi, g, pp, avoid);
+            st.u = operand_of(dtype, g, pp, avoid);
             if (st.oj >= 0) {
-                st.w2 = widen(P, st.oj, gate_of(st.oj), pp, avoid);
+                st.u2 = operand_of(dtype, gate_of(st.oj), pp, avoid);
                 ++i;
             }
-            st.bits = 0;
-            for (const int x : {st.oi, st.oj})
-                for (int j = 0; x >= 0 && j < P.ops[(size_t)x].k; ++j) st.bits |= 1u << P.ops[(size_t)x].lpos[j];
             steps.push_back(std::move(st));
         }
         // runs of neighbouring steps whose targets leave two tile bits free: those bits tell
         // the waves apart in all of them, and no barrier is needed inside the run
         for (size_t i = 0; i < steps.size();) {
-            unsigned bits = steps[i].bits;
+            unsigned bits = steps[i].bits();
             size_t e = i + 1;
             auto last = [&](const Step& x) { return x.oj >= 0 ? x.oj : x.oi; };
             while (e < steps.size() && steps[e].oi == last(steps[e - 1]) + 1 &&
-                   a.m - __builtin_popcount(bits | steps[e].bits) >= 2)
-                bits |= steps[e++].bits;
+                   a.m - __builtin_popcount(bits | steps[e].bits()) >= 2)
+                bits |= steps[e++].bits();
             int wave[2] = {0, 0}, nw = 0;   // the two highest free bits: the lanes want the low ones
             for (int b = a.m - 1; b >= 0 && nw < 2; --b)
                 if (!((bits >> b) & 1)) wave[nw++] = b;
             for (size_t x = i; x < e; ++x) {
                 Step& st = steps[x];
                 DevOp* d2 = st.oj >= 0 ? &P.ops[(size_t)st.oj] : nullptr;
-                const std::vector<cd>* m2 = !d2 ? nullptr : st.w2.empty() ? &gate_of(st.oj).m.vec() : &st.w2;
-                mfma_tables(dtype, a.m, P.ops[(size_t)st.oi], st.w1.empty() ? gate_of(st.oi).m.vec() : st.w1, d2, m2, wave,
-                            P.apool);
+                mfma_tables(dtype, a.m, P.ops[(size_t)st.oi], st.u, d2, d2 ? &st.u2 : nullptr, wave, P.apool);
                 P.ops[(size_t)st.oi].nosync = nw == 2 && a.m >= 10 && x + 1 < e;
             }
             i = e;

@@ -25,7 +25,8 @@ struct DevOp {
     int k;
     int lpos[kMaxK];    // tile-local bit of each target, or -1 (diagonal op, qubit outside the tile)
     int gbit[kMaxK];    // physical qubit of each target
-    int off;            // offset into the complex pool: dense 4^k, diagonal 2^k, permutation 2^k phases
+    int off;            // offset into the complex pool: dense 4^k (not on matrix cores), diagonal 2^k,
+                        // permutation 2^k phases
     int ioff;           // permutation: offset into the int pool (2^k source rows)
     int flags;          // permutation: 1 when some phase differs from 1; matrix-core op: 1 when
                         // it and the next op of the pass run as one pair

@@ -12,7 +12,8 @@ extern "C" {
 // One pass of a plan, as its launch sees it.
 struct PassFacts {
     int tile_qubits, low_qubits, ops, matrix_ops, staged, diag_ops, diag_unstaged, a_len, d_len;
-    long long tiles;
+    int pool;   // complex pool entries the pass's ops read
+    long long tiles, pool_total;
 };
 
 // Plans the circuit with the defaults of `dtype` on tiles of 2^tile amplitudes; the facts of
@@ -30,11 +31,12 @@ int plan_facts(int n, int dtype, int tile, const qsv_gate* gates, size_t count, 
     if (!make_plan(n, dtype, in, o, P, err)) return -1;
     for (size_t p = 0; p < P.pargs.size() && (int)p < max; ++p) {
         const PassArgs& a = P.pargs[p];
-        PassFacts f{a.m, a.L, a.op_count, 0, a.staged, 0, 0, a.a_len, a.d_len, P.pgrid[p]};
+        PassFacts f{a.m, a.L, a.op_count, 0, a.staged, 0, 0, a.a_len, a.d_len, 0, P.pgrid[p], (long long)P.pool.size()};
         for (int i = a.op_begin; i < a.op_begin + a.op_count; ++i) {
             const DevOp& d = P.ops[(size_t)i];
             f.matrix_ops += d.kind == OP_DENSE && d.goff >= 0;
             f.diag_ops += d.kind == OP_DIAG;
+            f.pool += d.kind != OP_DENSE ? 1 << d.k : d.goff < 0 ? 1 << (2 * d.k) : 0;
             f.diag_unstaged += d.kind == OP_DIAG && d.aoff < 0;
         }
         out[p] = f;

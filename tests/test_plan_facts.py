@@ -16,7 +16,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 class PassFacts(ctypes.Structure):   # plan_facts.cpp
     _fields_ = [(f, ctypes.c_int) for f in ("tile_qubits", "low_qubits", "ops", "matrix_ops", "staged", "diag_ops",
-                                            "diag_unstaged", "a_len", "d_len")] + [("tiles", ctypes.c_longlong)]
+                                            "diag_unstaged", "a_len", "d_len", "pool")] + [("tiles", ctypes.c_longlong),
+                                                                                           ("pool_total", ctypes.c_longlong)]
 
 
 @pytest.fixture(scope="module")
@@ -104,3 +105,11 @@ def test_few_tiles_save_passes_and_steps(facts, n, steps):
     with its operands capped (6 to 9), and no diagonal steps bought with them."""
     fs = pass_facts(facts, n, "c64", circuit("hea", n, 8, 1))
     assert len(fs) <= n // 2 - 1 and sum(f.ops for f in fs) <= steps
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("name,n,depth", [("brickwork", 20, 8), ("hea", 18, 6), ("mix", 16, 12), ("brickwork", 6, 4)])
+def test_the_pool_holds_what_ops_read_and_no_more(facts, name, n, depth, dtype):
+    """Matrix-core ops read their operands; their matrices are not carried a second time."""
+    fs = pass_facts(facts, n, dtype, circuit(name, n, depth, 2))
+    assert sum(f.pool for f in fs) == fs[0].pool_total
