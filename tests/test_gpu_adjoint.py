@@ -140,6 +140,43 @@ def test_generators_under_rz_and_layer_orders(qsv, dtype):
         assert rel(G[b], g_ref) <= REL[dtype], rel(G[b], g_ref)
 
 
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [11, 12, 13])
+def test_single_factor_generators_in_registers(qsv, n, dtype):
+    """From 11 qubits on, X and Y generators are summed by the register kernel: on every qubit
+    (each kept bit of a round, low, middle and high), RX alone (no Z factor), RY (its own), and
+    both conjugated by the RZ that follows, against the oracle's parameter shift."""
+    tpl, p = [C.Op("H", (q,)) for q in range(n)], 0
+
+    def layer(kind):
+        nonlocal p
+        for q in range(n):
+            tpl.append(C.Op(kind[q % len(kind)], (q,), param=p))
+            p += 1
+
+    layer(["RX"])
+    tpl += [C.Op("CZ", (q, (q + 1) % n)) for q in range(n)]
+    layer(["RX"])             # RX before RZ: generators conjugated by it
+    layer(["RZ"])
+    tpl += [C.Op("CNOT", (q, q + 1)) for q in range(0, n - 1, 2)]
+    layer(["RY", "RX"])       # both kinds in one layer, half of them under an RZ
+    for q in range(0, n, 2):
+        tpl.append(C.Op("RZ", (q,), param=p))
+        p += 1
+    tpl += [C.Op("CZ", (0, n - 1)), C.Op("H", (n // 2,))]
+    layer(["RX", "RX", "RY"])
+    terms = C.tfim_terms(n) + [(0.4, ((1, "Y"), (n - 1, "Z"))), (-0.7, ((0, "X"), (n // 2, "X")))]
+    params = np.random.default_rng(40 + n).uniform(-np.pi, np.pi, size=(2, p))
+    E, G = qsv.adjoint_grad(n, tpl, params, terms, dtype)
+    for b in range(2):
+        e_ref = oracle.energy(n, tpl, params[b], terms)
+        g_ref = oracle.param_shift_grad(n, tpl, params[b], terms)
+        assert abs(E[b] - e_ref) <= (1e-12 if dtype == "c128" else 1e-4) * max(1.0, abs(e_ref))
+        assert rel(G[b], g_ref) <= REL[dtype], rel(G[b], g_ref)
+        # entry by entry, of the size of the largest
+        assert np.max(np.abs(G[b] - g_ref)) <= REL[dtype] * np.max(np.abs(g_ref))
+
+
 def test_autograd_function(qsv):
     import torch
     from paper_2604_03816_amd.autograd import AdjointExpval
