@@ -122,9 +122,14 @@ typedef struct {
                             matrix-core op whose operand no longer fits the pass's LDS
                             operand block waits for the next pass */
     int matrix_cores;    /* dense ops on >= this many (and at most 4) targets run on matrix
-                            cores (MFMA; complex64: bfloat16 products of exact three-way FP32
+                            cores (MFMA; complex64: bfloat16 products of three-way FP32
                             splits, FP32 accumulation; complex128: FP64): 0 = default (3),
-                            -1 = never, 3 or 4 otherwise */
+                            -1 = never, 3 or 4 otherwise.  A split is exact from 2^-110 to
+                            below 2^128 - 2^119; smaller parts of amplitudes keep fewer than
+                            24 bits, larger ones give NaN, and a non-finite one reaches all
+                            16 amplitudes that share a product with it (a 3-qubit op's
+                            too).  complex64 states beyond that range take -1: FP32
+                            vector arithmetic */
     int commute;         /* fuse = 1 only.  1 (default): commutation-aware DAG -- ops that
                             are diagonal on every qubit they share are left unordered, so
                             fusion may merge them across one another and a pass may take

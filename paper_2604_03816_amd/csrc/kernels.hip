@@ -370,13 +370,17 @@ __device__ void op_dense(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __
 // are the second op's 16 states, on (lane / 16, j), where the second op needs them.
 
 // complex64: the product in bfloat16 matrix instructions (16 x 16 x 32), each FP32 number
-// carried exactly as the sum of three bfloat16 numbers (8 + 8 + 8 significant bits).  Of
-// the nine products of parts the six of relative size 2^-18 and more are summed, in FP32,
-// smallest first; the three left out are below 2^-25 of the term.  A block takes 192
-// matrix-core clocks (FP32 matrix instructions in the three-product form below take 384)
-// and about as many of the VALU for the splits.  30-qubit depth-20 brickwork, per pass:
-// FP32 instructions 4.19 ms, this 4.00 ms, at which the chip is at its power limit (2.0 GHz
-// against 2.4); error of a 22-qubit brickwork state against 64 bits 9.1e-7 and 3.4e-7.
+// carried as the sum of three bfloat16 numbers (8 + 8 + 8 significant bits).  Of the nine
+// products of parts the six of relative size 2^-18 and more are summed, in FP32, smallest
+// first; the three left out are each below 2^-25 of the term, at most 2^-24 together.  The
+// sum is exact from 2^-110 (below, the third part is under bfloat16's smallest) to 2^128 -
+// 2^119 (from there on the first part is infinite); plans with matrix_cores = -1 take such
+// values.  A block takes 192 matrix-core clocks (FP32 matrix instructions in the
+// three-product form below take 384) and about as many of the VALU for the splits.
+// 30-qubit depth-20 brickwork, per pass: FP32 instructions 4.19 ms, this 4.00 ms, at which the
+// chip is at its power limit (2.0 GHz against 2.4); error of a 22-qubit brickwork state
+// against 64 bits 9.1e-7 and 3.4e-7.  Tiles scaled into the range and done again in FP32
+// where a result is NaN cost 0.4 % there and 4 % where diagonal ops and permutations prevail.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));

@@ -87,3 +87,38 @@ def test_split_products_keep_small_and_large_amplitudes():
     # eight products of rounded entries (2^-24) summed in FP32: well below 2^-19 of the largest
     assert np.max(np.abs(got[small] - ref[small])) <= 2.0 ** -19 * scale
     s.free()
+
+
+@pytest.mark.parametrize("k,targets", [(4, (2, 3, 4, 5)), (3, (1, 5, 9))])
+def test_the_range_of_split_products(k, targets):
+    """complex64 states of sizes over the range in which splits are exact, and beyond it (and
+    with an infinity) with matrix_cores = -1.  The bound is the one above: 2^-19 of the largest."""
+    from paper_2604_03816_amd import qsv
+    n = 12
+    rng = np.random.default_rng(5)
+    u = C.haar_unitary(rng, 1 << k)
+    psi0 = rng.normal(size=1 << n) + 1j * rng.normal(size=1 << n)
+    psi0 /= 2 * np.abs(psi0).max()
+    s = qsv.State(n, "c64")
+    for e, opts in ((0, {}), (-60, {}), (-100, {}), (100, {}), (125, {}), (-118, {"matrix_cores": -1}),
+                    (125, {"matrix_cores": -1})):
+        psi = (psi0 * 2.0 ** e).astype(np.complex64)
+        s.set(psi)
+        s.apply([C.Op("U", targets, matrix=u)], kmax=4, **opts)
+        ref = psi.astype(np.complex128)
+        oracle.apply(ref, u, targets)
+        assert np.max(np.abs(s.get() - ref)) <= 2.0 ** -19 * np.abs(ref).max(), (e, opts)
+    psi = psi0.astype(np.complex64)
+    psi[77] = np.inf
+    bits = sum(1 << t for t in targets)
+    group = (np.arange(1 << n) & ~bits) == 77 & ~bits
+    for opts, most in (({}, 16), ({"matrix_cores": -1}, 1 << k)):
+        s.set(psi)
+        s.apply([C.Op("U", targets, matrix=u)], kmax=4, **opts)
+        got = s.get()
+        bad = ~np.isfinite(got)
+        assert np.all(bad[group]) and bad.sum() <= most
+        ref = np.where(group, 0, psi).astype(np.complex128)
+        oracle.apply(ref, u, targets)
+        assert np.max(np.abs(got[~bad] - ref[~bad])) <= 2.0 ** -19
+    s.free()
