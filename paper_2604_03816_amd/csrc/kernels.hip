@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <type_traits>
 
@@ -2016,6 +2017,23 @@ static int device_cus()
     return cus[dev];
 }
 
+// Raises the dynamic LDS limit of kernels on the current device (a function's attributes are
+// each device's own), once per device and `done`.
+template <typename... K>
+static hipError_t raise_lds_limit(std::atomic<unsigned long long>& done, int bytes, K... kernels)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return once_per_device(done, dev, [&] {
+        for (const void* k : {(const void*)kernels...}) {
+            e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    });
+}
+
 // Workgroups stride over the tiles (the hardware keeps as many resident as registers and
 // LDS allow; a finished workgroup's slot is refilled at once).
 template <typename C, bool WIDE, bool PF>
@@ -2023,14 +2041,10 @@ hipError_t launch_pass_t(void* st, void* st2, const PassArgs& a, long long ntile
                          const void* pool, const int* ipool, const float* apool, hipStream_t s, bool from_zero)
 {
     const long long total = st2 ? 2 * ntiles : ntiles;
-    static bool attr_set = false;
-    if (!attr_set) {
-        // a 64 KiB complex128 tile plus its operand block exceeds the 64 KiB default
-        hipError_t e = hipFuncSetAttribute((const void*)k_pass<C, WIDE, PF, kThreads>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    // a 64 KiB complex128 tile plus its operand block exceeds the 64 KiB default
+    static std::atomic<unsigned long long> raised{0};
+    const hipError_t e = raise_lds_limit(raised, 163840, k_pass<C, WIDE, PF, kThreads>);
+    if (e != hipSuccess) return e;
     const size_t lds = (sizeof(C) << a.m) + sizeof(float) * (size_t)(PF ? a.a_len : a.d_len);
     // at most 64 workgroups per CU, each striding over tiles: the operand block is staged
     // once per workgroup rather than once per tile (measured on 2^18-tile passes: 6 %
@@ -2052,13 +2066,9 @@ static hipError_t launch_batch_pass_t(const BatchItem* table, const BatchList* l
 // limit is raised once, outside any stream capture (the server's step is captured).
 hipError_t prepare_batch_pass()
 {
-    const void* fns[4] = {(const void*)k_batch_pass<float2, true>, (const void*)k_batch_pass<float2, false>,
-                          (const void*)k_batch_pass<double2, true>, (const void*)k_batch_pass<double2, false>};
-    for (const void* f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 98304);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    static std::atomic<unsigned long long> raised{0};
+    return raise_lds_limit(raised, 98304, k_batch_pass<float2, true>, k_batch_pass<float2, false>,
+                           k_batch_pass<double2, true>, k_batch_pass<double2, false>);
 }
 
 hipError_t launch_batch_pass(int dtype, const BatchItem* table, const BatchList* list, int grid, int tile_qubits,
@@ -2196,15 +2206,10 @@ hipError_t launch_expval_r(int dtype, const void* sa, const void* sb, const Pass
                            partial);
     } else {
         auto k = two ? k_expval_r<double2, true> : k_expval_r<double2, false>;
-        static const hipError_t raised = [] {   // 64 KiB tiles beside the term rows exceed the default limit
-            hipError_t e = hipFuncSetAttribute((const void*)k_expval_r<double2, true>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 98304);
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute((const void*)k_expval_r<double2, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 98304);
-            return e;
-        }();
-        if (raised != hipSuccess) return raised;
+        // 64 KiB tiles beside the terms' sums exceed the default limit
+        static std::atomic<unsigned long long> raised{0};
+        const hipError_t e = raise_lds_limit(raised, 98304, k_expval_r<double2, true>, k_expval_r<double2, false>);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const double2*)sa, (const double2*)sb, a, t, r,
                            ntiles, partial);
     }

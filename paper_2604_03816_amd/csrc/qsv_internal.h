@@ -2,6 +2,7 @@
 // HIP kernels of libqsv.so.  Not part of the public ABI.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <cstdint>
 
 namespace qsv {
@@ -200,6 +201,18 @@ constexpr int kPlanCUs = 256;
 inline bool loads_ahead(int m, int L, long long tiles, int cus)
 {
     return m == kAheadTileQubits && L >= 1 && tiles >= 32ll * cus;
+}
+
+// Runs `f` for device `dev` unless it has succeeded there before (done: a bit per device; from
+// the 65th on it runs every time).  Threads that come together may both run it.
+template <typename F>
+hipError_t once_per_device(std::atomic<unsigned long long>& done, int dev, F f)
+{
+    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+    const hipError_t e = f();
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
 }
 
 // Largest tile (log2 amplitudes) a dtype's pass kernel holds in LDS (64 KiB).

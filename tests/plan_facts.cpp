@@ -44,4 +44,20 @@ int plan_facts(int n, int dtype, int tile, const qsv_gate* gates, size_t count, 
     return (int)P.pargs.size();
 }
 
+// Runs of a per-device step over the calls' devices; call `failing` (if it runs it) fails.
+int runs_per_device(const int* devices, int calls, int failing, int* ran)
+{
+    std::atomic<unsigned long long> done{0};
+    int failures = 0;
+    for (int c = 0; c < calls; ++c) {
+        ran[c] = 0;
+        const hipError_t e = qsv::once_per_device(done, devices[c], [&] {
+            ran[c] = 1;
+            return c == failing ? hipErrorInvalidValue : hipSuccess;
+        });
+        failures += e != hipSuccess;
+    }
+    return failures;
+}
+
 }  // extern "C"

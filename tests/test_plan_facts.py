@@ -1,5 +1,5 @@
 """Facts of the planner's results that end results alone would not show (no GPU): memory of a
-plan being made, what its passes stage."""
+plan being made, what its passes stage, launch limits per device."""
 import ctypes
 import os
 import subprocess
@@ -113,3 +113,12 @@ def test_the_pool_holds_what_ops_read_and_no_more(facts, name, n, depth, dtype):
     """Matrix-core ops read their operands; their matrices are not carried a second time."""
     fs = pass_facts(facts, n, dtype, circuit(name, n, depth, 2))
     assert sum(f.pool for f in fs) == fs[0].pool_total
+
+
+def test_launch_limits_are_raised_once_on_each_device(facts):
+    """A kernel's dynamic LDS limit belongs to a device: the step runs once on each, again where
+    it failed, and always beyond the 64 devices that are kept apart."""
+    devices = [0, 0, 1, 1, 0, 2, 1, 63, 63, 64, 64]
+    ran = (ctypes.c_int * len(devices))()
+    assert facts.runs_per_device((ctypes.c_int * len(devices))(*devices), len(devices), 2, ran) == 1
+    assert list(ran) == [1, 0, 1, 1, 0, 1, 0, 1, 0, 1, 1]
