@@ -82,7 +82,7 @@ struct qsv_state_s {
     static constexpr int kTabSlots = 8;
     TabSlot tab[kTabSlots];
     int tab_next = 0;
-    unsigned char* tab_block_h = nullptr;   // every slot's first blocks in one allocation each
+    unsigned char* tab_block_h = nullptr;   // slots' first blocks in one allocation each
     unsigned char* tab_block_d = nullptr;   // (reserve_tabs)
 };
 
@@ -625,26 +625,30 @@ TableLayout table_layout(const HostPlan& hp)
     return t;
 }
 
-// Gives each of a fresh state's arena slots `bytes` out of one pinned and one device
-// allocation (a call that uses all of them in turn paid for eight of each: pinned ones take
-// about 70 us and 90 us more to free).
-qsv_status reserve_tabs(qsv_state s, size_t bytes)
+// Gives a fresh state's first arena slots their space out of one pinned and one device
+// allocation (a call that uses eight in turn paid for eight of each: pinned ones take about
+// 70 us and 90 us more to free).  Where that fails the slots grow as they are needed.
+void reserve_tabs(qsv_state s, const TabReserve& r)
 {
-    bytes = (bytes + 255) & ~(size_t)255;
-    QSV_HIP(hipHostMalloc((void**)&s->tab_block_h, bytes * qsv_state_s::kTabSlots, hipHostMallocDefault));
-    if (hipMalloc((void**)&s->tab_block_d, bytes * qsv_state_s::kTabSlots) != hipSuccess) {
+    if (!r.slots) return;
+    if (hipHostMalloc((void**)&s->tab_block_h, r.bytes * (size_t)r.slots, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        s->tab_block_d = nullptr;
-        return fail(QSV_E_OOM, "plan table allocation failed");
+        s->tab_block_h = nullptr;
+        return;
     }
-    for (int i = 0; i < qsv_state_s::kTabSlots; ++i) {
+    if (hipMalloc((void**)&s->tab_block_d, r.bytes * (size_t)r.slots) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(s->tab_block_h);
+        s->tab_block_h = s->tab_block_d = nullptr;
+        return;
+    }
+    for (int i = 0; i < r.slots; ++i) {
         qsv_state_s::TabSlot& ts = s->tab[i];
-        ts.h = s->tab_block_h + (size_t)i * bytes;
-        ts.d = s->tab_block_d + (size_t)i * bytes;
-        ts.hbytes = ts.dbytes = bytes;
+        ts.h = s->tab_block_h + (size_t)i * r.bytes;
+        ts.d = s->tab_block_d + (size_t)i * r.bytes;
+        ts.hbytes = ts.dbytes = r.bytes;
         ts.shared = true;
     }
-    return QSV_OK;
 }
 
 // Enqueues every pass of a host plan on the state's stream, its tables copied into the
@@ -1815,9 +1819,15 @@ qsv_status qsv_adjoint_grad(int n, qsv_dtype dtype, const qsv_op* ops, size_t n_
         if (!undo[li].empty() &&
             !make_plan(n, dtype, gates_of(undo[li], th_generic.data(), true), default_opts(dtype), undo_tmpl[li], err))
             st = fail(QSV_E_ARG, err);
-    size_t tab_bytes = table_layout(fwd_tmpl).total;
-    for (const HostPlan& t : undo_tmpl) tab_bytes = std::max(tab_bytes, table_layout(t).total);
-    for (int p = 0; p < pairs && st == QSV_OK; ++p) st = reserve_tabs(pair[p].phi, tab_bytes);
+    size_t undo_bytes = 0, plans = n_ops ? 1 : 0;   // plans a vector enqueues
+    for (size_t li = 0; li < layers.size(); ++li) {
+        if (undo[li].empty()) continue;
+        undo_bytes = std::max(undo_bytes, table_layout(undo_tmpl[li]).total);
+        ++plans;
+    }
+    for (int p = 0; p < pairs && st == QSV_OK; ++p)
+        reserve_tabs(pair[p].phi, tab_reserve(n_ops ? table_layout(fwd_tmpl).total : 0, undo_bytes,
+                                              plans * (size_t)((B - p + pairs - 1) / pairs), qsv_state_s::kTabSlots));
     // a template refreshed with a vector's gates, or a plan made for them
     auto plan_for = [&](const HostPlan& tmpl, const std::vector<InGate>& g, HostPlan& hp) -> qsv_status {
         hp = tmpl;

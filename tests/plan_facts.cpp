@@ -44,6 +44,13 @@ int plan_facts(int n, int dtype, int tile, const qsv_gate* gates, size_t count, 
     return (int)P.pargs.size();
 }
 
+int reserved_slots(size_t forward, size_t undo, size_t plans, int slots, size_t* bytes)
+{
+    const qsv::TabReserve r = qsv::tab_reserve(forward, undo, plans, slots);
+    *bytes = r.bytes;
+    return r.slots;
+}
+
 // Runs of a per-device step over the calls' devices; call `failing` (if it runs it) fails.
 int runs_per_device(const int* devices, int calls, int failing, int* ran)
 {

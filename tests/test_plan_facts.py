@@ -122,3 +122,16 @@ def test_launch_limits_are_raised_once_on_each_device(facts):
     ran = (ctypes.c_int * len(devices))()
     assert facts.runs_per_device((ctypes.c_int * len(devices))(*devices), len(devices), 2, ran) == 1
     assert list(ran) == [1, 0, 1, 1, 0, 1, 0, 1, 0, 1, 1]
+
+
+@pytest.mark.parametrize("forward,undo,plans,want", [
+    (100 << 10, 30 << 10, 72, (8, 100 << 10)),      # many plans: every slot
+    (100 << 10, 30 << 10, 3, (3, 100 << 10)),       # a short circuit, one vector
+    (100 << 10, 0, 1, (0, 0)),                      # one plan: its slot grows when it comes
+    (2 << 20, 1 << 10, 80, (8, 2 << 20)), ((2 << 20) + 1, 1 << 10, 80, (8, 1 << 10)),   # a deep circuit
+    (40 << 20, 3 << 20, 80, (0, 0)), (40 << 20, 3 << 20, 5, (5, 3 << 20)), (1000, 999, 2, (2, 1024))])
+def test_a_gradient_call_reserves_what_its_plans_take(facts, forward, undo, plans, want):
+    b = ctypes.c_size_t()
+    facts.reserved_slots.argtypes = [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]
+    got = facts.reserved_slots(forward, undo, plans, 8, ctypes.byref(b))
+    assert (got, b.value) == want
