@@ -42,7 +42,6 @@ bool read_gate_public(const qsv_gate& g, int n, InGate& out, std::string& err);
 namespace {
 
 constexpr int kZQ = kZChunkQubits;   // chunk qubits of the batched <Z> reduction (k_zsum_batch)
-constexpr int kFootprintChunk = 12;  // footprints count 2^12-amplitude chunks of partials, an upper bound
 constexpr int kServeTileQubits[2] = {12, 12};   // 2^12-amplitude tiles (32 / 64 KiB), as the plain path
 
 struct Req {
@@ -149,8 +148,8 @@ void worker_loop(qsv_server s)
             r->state_bytes = elem(r->dtype) << r->n;
             r->table_bytes = hp.ops.size() * sizeof(DevOp) + hp.pool.size() * elem(r->dtype) +
                              hp.ipool.size() * sizeof(int) + hp.apool.size() * sizeof(float) + 4 * 256;
-            const long long chunks = 1ll << std::max(0, r->n - kFootprintChunk);
-            r->work_bytes = (size_t)chunks * (kFootprintChunk + 1) * sizeof(double);
+            const long long chunks = 1ll << std::max(0, r->n - kZQ);   // the final <Z> reduction's partials
+            r->work_bytes = (size_t)chunks * (kZQ + 1) * sizeof(double);
             r->footprint = r->state_bytes + r->table_bytes + r->work_bytes;   // Eq. 14
             if (!r->keep_gates) {
                 r->gates.clear();

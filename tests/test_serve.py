@@ -52,6 +52,17 @@ def test_requests_that_can_never_fit_are_rejected_not_blocking():
     sv.close()
 
 
+@pytest.mark.parametrize("n", [3, 12, 13, 14, 17])
+def test_the_footprint_counts_the_partials_the_step_uses(n):
+    """State, tables (no ops: alignment only) and, per 2^14 amplitudes, the 15 doubles of the
+    final <Z> reduction."""
+    sv = Server(max_slots=1, dry_run=True)
+    sv.submit(n, "c128", [])
+    drain(sv)
+    assert sv.stats()["peak_used_bytes"] == (16 << n) + 4 * 256 + 15 * 8 * (1 << max(0, n - 14))
+    sv.close()
+
+
 def test_passes_match_the_plan():
     sv = Server(max_slots=16, dry_run=True)
     ids = {}
