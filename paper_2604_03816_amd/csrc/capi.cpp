@@ -520,12 +520,12 @@ bool plan_elements(int n, const std::vector<PTerm>& terms, bool imag, std::vecto
             }
         }
         E.ntiles = 1ll << (n - E.a.m);
-        // Z-only groups end with a workgroup reduction per term, so fewer workgroups; the
-        // X/Y kernel is bound by its per-term LDS work and gains from more of them
-        // (measured at 30 qubits; callers that read back many groups ask for fewer)
-        E.grid = (int)std::min<long long>(E.ntiles, E.rounds && !imag && dtype == QSV_C64 ? 2048
-                                                    : E.zonly || E.rounds       ? 1024
-                                                                                : xgrid);
+        // Z-only and register groups are bound by the read of the state and end with sums over
+        // the workgroups' terms, so fewer workgroups; the general X/Y kernel is bound by its
+        // per-term LDS work and gains from more of them (measured at 30 qubits).  Callers that
+        // read back many groups ask for fewer (xgrid)
+        const int most = E.rounds && !imag && dtype == QSV_C64 ? 2048 : E.zonly || E.rounds ? 1024 : xgrid;
+        E.grid = (int)std::min<long long>(E.ntiles, std::min(most, xgrid));
         E.idx = groups[g];
         E.off = doubles;
         doubles += (size_t)E.grid * E.ta.nterms * 2;
