@@ -118,9 +118,11 @@ typedef struct {
     int low_qubits;      /* contiguous low qubits kept in every tile, 0 = default */
     double pass_budget;  /* per-pass arithmetic budget (FMA per amplitude: a dense op
                             4 * 2^k, halved on complex64 matrix cores, times 3/4 for a
-                            4-qubit matrix-core op), 0 = default, < 0 = unlimited.  A
+                            4-qubit matrix-core op), 0 = default, < 0 = unlimited.  On
+                            states large enough for passes to load their next tile during
+                            the ops (24 qubits and more on 2^12-amplitude tiles) a
                             matrix-core op whose operand no longer fits the pass's LDS
-                            operand block waits for the next pass */
+                            operand block also waits for the next pass, unless served */
     int matrix_cores;    /* dense ops on >= this many (and at most 4) targets run on matrix
                             cores (MFMA; complex64: bfloat16 products of three-way FP32
                             splits, FP32 accumulation; complex128: FP64): 0 = default (3),
