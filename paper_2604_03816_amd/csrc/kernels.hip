@@ -125,11 +125,10 @@ __device__ __forceinline__ long long local_stride(const PassArgs& a, int i)
     return 1ll << a.phys[i];   // i is a compile-time constant at every call site
 }
 
-template <typename C, bool LOAD, int NS, int W, int NT = kThreads>
+template <typename C, bool LOAD, int NS, int W>
 __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restrict__ lds, const PassArgs& a,
                                             long long toff)
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8;
     static_assert(W == 1 || (W == 2 && sizeof(C) == 8), "16-byte lanes");
     using V = typename std::conditional<W == 2, floatx4, C>::type;
     // the state streams through once per pass: nontemporal loads and stores (measured
@@ -139,18 +138,18 @@ __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restri
     constexpr int LB = NS >= 32 ? 5 : NS >= 16 ? 4 : NS >= 8 ? 3 : NS >= 4 ? 2 : NS >= 2 ? 1 : 0;
     long long hs[LB > 0 ? LB : 1];
 #pragma unroll
-    for (int b = 0; b < LB; ++b) hs[b] = local_stride(a, LOGT + LW + b);
+    for (int b = 0; b < LB; ++b) hs[b] = local_stride(a, kLogThreads + LW + b);
     const int tid = threadIdx.x;
     // at most CH 16-byte units in registers at a time: wider tiles move in several
     // batches, so the largest tile does not set the kernel's register count
     constexpr int CH = NS < 8 ? NS : 8;
     V v[CH];
-    // 16-byte unit u = NT j + tid holds tile elements W u .. W u + W - 1; the positions of
+    // 16-byte unit u = 256 j + tid holds tile elements W u .. W u + W - 1; the positions of
     // its elements are those of element W tid (+ 1) XOR the compile-time part of j
     int ut = swz<C>(W * tid);
     asm volatile("" : "+v"(ut));   // keeps the positions of all j from being held across the tile loop
     auto put = [&](int j, const V& x) {
-        const int at = ut ^ swz<C>(W * (j << LOGT));
+        const int at = ut ^ swz<C>(W * (j << kLogThreads));
         if constexpr (W == 2) {
             lds[at] = C{x.x, x.y};
             lds[at ^ 1] = C{x.z, x.w};
@@ -159,7 +158,7 @@ __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restri
         }
     };
     auto get = [&](int j) {
-        const int at = ut ^ swz<C>(W * (j << LOGT));
+        const int at = ut ^ swz<C>(W * (j << kLogThreads));
         if constexpr (W == 2) {
             const C p = lds[at], r = lds[at ^ 1];
             return V{p.x, p.y, r.x, r.y};
@@ -195,29 +194,28 @@ __device__ __forceinline__ void move_tile_n(gptr<C> __restrict__ st, C* __restri
 // The two halves of a tile load for a kernel that has other work in between: NS 16-byte
 // units per thread from p (the tile's base plus the thread's offset) into registers, and
 // from there to their places in LDS.
-template <typename C, int NS, int W, int NT>
+template <typename C, int NS, int W>
 __device__ __forceinline__ void load_tile(gptr<C> p, const PassArgs& a, floatx4 (&v)[NS])
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
+    constexpr int LW = W == 2 ? 1 : 0;
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         long long o = 0;
 #pragma unroll
         for (int b = 0; (1 << b) < NS; ++b)
-            if ((j >> b) & 1) o += local_stride(a, LOGT + LW + b);
+            if ((j >> b) & 1) o += local_stride(a, kLogThreads + LW + b);
         v[j] = __builtin_nontemporal_load((const floatx4*)(p + o));
     }
 }
 
-template <typename C, int NS, int W, int NT>
+template <typename C, int NS, int W>
 __device__ __forceinline__ void put_tile(C* __restrict__ lds, const floatx4 (&v)[NS])
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8;
     int ut = swz<C>(W * (int)threadIdx.x);
     asm volatile("" : "+v"(ut));
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        const int at = ut ^ swz<C>(W * (j << LOGT));
+        const int at = ut ^ swz<C>(W * (j << kLogThreads));
         if constexpr (W == 2) {
             lds[at] = C{v[j].x, v[j].y};
             lds[at ^ 1] = C{v[j].z, v[j].w};
@@ -227,15 +225,14 @@ __device__ __forceinline__ void put_tile(C* __restrict__ lds, const floatx4 (&v)
     }
 }
 
-template <typename C, int NS, int W, int NT>
+template <typename C, int NS, int W>
 __device__ __forceinline__ void get_tile(const C* __restrict__ lds, floatx4 (&v)[NS])
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8;
     int ut = swz<C>(W * (int)threadIdx.x);
     asm volatile("" : "+v"(ut));
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        const int at = ut ^ swz<C>(W * (j << LOGT));
+        const int at = ut ^ swz<C>(W * (j << kLogThreads));
         if constexpr (W == 2) {
             const C p = lds[at], q = lds[at ^ 1];
             v[j] = floatx4{p.x, p.y, q.x, q.y};
@@ -245,50 +242,49 @@ __device__ __forceinline__ void get_tile(const C* __restrict__ lds, floatx4 (&v)
     }
 }
 
-template <typename C, int NS, int W, int NT>
+template <typename C, int NS, int W>
 __device__ __forceinline__ void store_tile(gptr<C> p, const PassArgs& a, const floatx4 (&v)[NS])
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
+    constexpr int LW = W == 2 ? 1 : 0;
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         long long o = 0;
 #pragma unroll
         for (int b = 0; (1 << b) < NS; ++b)
-            if ((j >> b) & 1) o += local_stride(a, LOGT + LW + b);
+            if ((j >> b) & 1) o += local_stride(a, kLogThreads + LW + b);
         __builtin_nontemporal_store(v[j], (floatx4*)(p + o));
     }
 }
 
-template <typename C, bool LOAD, int NT = kThreads>
+template <typename C, bool LOAD>
 __device__ __forceinline__ void move_tile(gptr<C> __restrict__ st, C* __restrict__ lds, const PassArgs& a,
                                           long long base)
 {
-    constexpr int LOGT = NT == 512 ? 9 : 8;
     const int tid = threadIdx.x;
     if constexpr (sizeof(C) == 8) {
         // complex64 pairs whenever qubit 0 is a tile qubit and a slice is full
-        if (a.L >= 1 && a.m > LOGT) {
-            const long long toff = base + local_off_bits(a, tid << 1, 1, LOGT + 1);
-            switch (a.m - LOGT - 1) {
-            case 0: move_tile_n<C, LOAD, 1, 2, NT>(st, lds, a, toff); break;
-            case 1: move_tile_n<C, LOAD, 2, 2, NT>(st, lds, a, toff); break;
-            case 2: move_tile_n<C, LOAD, 4, 2, NT>(st, lds, a, toff); break;
-            case 3: move_tile_n<C, LOAD, 8, 2, NT>(st, lds, a, toff); break;
-            default: move_tile_n<C, LOAD, 16, 2, NT>(st, lds, a, toff); break;
+        if (a.L >= 1 && a.m > kLogThreads) {
+            const long long toff = base + local_off_bits(a, tid << 1, 1, kLogThreads + 1);
+            switch (a.m - kLogThreads - 1) {
+            case 0: move_tile_n<C, LOAD, 1, 2>(st, lds, a, toff); break;
+            case 1: move_tile_n<C, LOAD, 2, 2>(st, lds, a, toff); break;
+            case 2: move_tile_n<C, LOAD, 4, 2>(st, lds, a, toff); break;
+            case 3: move_tile_n<C, LOAD, 8, 2>(st, lds, a, toff); break;
+            default: move_tile_n<C, LOAD, 16, 2>(st, lds, a, toff); break;
             }
             return;
         }
     }
-    const int lowb = a.m < LOGT ? a.m : LOGT;
+    const int lowb = a.m < kLogThreads ? a.m : kLogThreads;
     const long long toff = base + local_off_bits(a, tid, 0, lowb);
-    switch (a.m - LOGT) {
-    case 0: move_tile_n<C, LOAD, 1, 1, NT>(st, lds, a, toff); break;
-    case 1: move_tile_n<C, LOAD, 2, 1, NT>(st, lds, a, toff); break;
-    case 2: move_tile_n<C, LOAD, 4, 1, NT>(st, lds, a, toff); break;
-    case 3: move_tile_n<C, LOAD, 8, 1, NT>(st, lds, a, toff); break;
-    case 4: move_tile_n<C, LOAD, 16, 1, NT>(st, lds, a, toff); break;
-    case 5: move_tile_n<C, LOAD, 32, 1, NT>(st, lds, a, toff); break;
-    default:   // tiles smaller than one slice (whole states below NT amplitudes)
+    switch (a.m - kLogThreads) {
+    case 0: move_tile_n<C, LOAD, 1, 1>(st, lds, a, toff); break;
+    case 1: move_tile_n<C, LOAD, 2, 1>(st, lds, a, toff); break;
+    case 2: move_tile_n<C, LOAD, 4, 1>(st, lds, a, toff); break;
+    case 3: move_tile_n<C, LOAD, 8, 1>(st, lds, a, toff); break;
+    case 4: move_tile_n<C, LOAD, 16, 1>(st, lds, a, toff); break;
+    case 5: move_tile_n<C, LOAD, 32, 1>(st, lds, a, toff); break;
+    default:   // tiles smaller than one slice (whole states below 256 amplitudes)
         if (tid < (1 << a.m)) {
             if (LOAD) lds[swz<C>(tid)] = st[toff];
             else st[toff] = lds[swz<C>(tid)];
@@ -324,7 +320,7 @@ __device__ __forceinline__ int group_base(int g, const DevOp& op)
     return b;
 }
 
-template <typename C, int K, int NT = kThreads>
+template <typename C, int K>
 __device__ void op_dense(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __restrict__ M)
 {
     constexpr int D = 1 << K;
@@ -332,7 +328,7 @@ __device__ void op_dense(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __
     // LDS position of row r of group g0 + tid: swz(group_base(g0)) (uniform, scalar work)
     // ^ swz(group_base(tid)) ^ swz(row_off(r)) (per lane and per op)
     const int bt = swz<C>(group_base<K>(threadIdx.x, op));
-    for (int g0 = 0; g0 < G; g0 += NT) {
+    for (int g0 = 0; g0 < G; g0 += kThreads) {
         if (g0 + (int)threadIdx.x >= G) break;
         const int b = __builtin_amdgcn_readfirstlane(swz<C>(group_base<K>(g0, op))) ^ bt;
         C v[D];
@@ -546,7 +542,7 @@ __device__ __forceinline__ auto load_mat(const DevOp& op, cptr<float> __restrict
 }
 
 // One 4-qubit op, or a pair of them on disjoint targets (op2: the second).
-template <typename C, bool PAIR, bool LDSOP, int NT>
+template <typename C, bool PAIR, bool LDSOP>
 __device__ __forceinline__ void op_mfma4(C* __restrict__ lds, int T, const DevOp& op, const DevOp& op2,
                                          cptr<float> __restrict__ apool, const float* __restrict__ alds)
 {
@@ -557,7 +553,7 @@ __device__ __forceinline__ void op_mfma4(C* __restrict__ lds, int T, const DevOp
         return ((j & 1) ? packed16(&o.jbit, 0) : 0) ^ ((j & 2) ? packed16(&o.jbit, 1) : 0);
     };
     const int nblk = T >> 8;
-    constexpr int NW = NT / 64;
+    constexpr int NW = kThreads / 64;
     const auto m1 = load_mat<C, LDSOP>(op, apool, alds, lane);
     decltype(load_mat<C, LDSOP>(op, apool, alds, lane)) m2;
     if (PAIR) m2 = load_mat<C, LDSOP>(op2, apool, alds, lane);
@@ -621,7 +617,7 @@ __device__ __forceinline__ void op_mfma4(C* __restrict__ lds, int T, const DevOp
 // complex128 3-qubit op: its real embedding [[Re, -Im], [Im, Re]], 16 x 16, fills the
 // matrix instruction (three 8 x 8 products would not): lane (q, c) feeds two complex rows
 // of column c, 4 j + q, as four real steps and gets rows 2 q and 2 q + 1 back.
-template <bool LDSOP, int NT>
+template <bool LDSOP>
 __device__ __forceinline__ void op_mfma3(double2* __restrict__ lds, int T, const DevOp& op,
                                          cptr<float> __restrict__ apool, const float* __restrict__ alds)
 {
@@ -641,7 +637,7 @@ __device__ __forceinline__ void op_mfma3(double2* __restrict__ lds, int T, const
     const int r0 = lane_off(lane, op.lin), r1 = r0 ^ packed16(&op.jbit, 0);
     const int w0 = lane_off(lane, op.lout), w1 = w0 ^ packed16(&op.jbit, 1);
     const int nblk = T >> 7;
-    constexpr int NW = NT / 64;
+    constexpr int NW = kThreads / 64;
     for (int blk = wave; blk < nblk; blk += NW) {
         const int sb = block_off(blk, op);
         const double2 v0 = *reinterpret_cast<const double2*>(base + (sb ^ r0));
@@ -656,7 +652,7 @@ __device__ __forceinline__ void op_mfma3(double2* __restrict__ lds, int T, const
     }
 }
 
-template <typename C, int K, int NT = kThreads>
+template <typename C, int K>
 __device__ void op_perm(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __restrict__ ph,
                         cptr<int> __restrict__ src)
 {
@@ -664,7 +660,7 @@ __device__ void op_perm(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __r
     const int G = T >> K;
     const bool phased = op.flags != 0;
     const int bt = swz<C>(group_base<K>(threadIdx.x, op));
-    for (int g0 = 0; g0 < G; g0 += NT) {
+    for (int g0 = 0; g0 < G; g0 += kThreads) {
         if (g0 + (int)threadIdx.x >= G) break;
         const int b = __builtin_amdgcn_readfirstlane(swz<C>(group_base<K>(g0, op))) ^ bt;
         C v[D];
@@ -678,7 +674,7 @@ __device__ void op_perm(C* __restrict__ lds, int T, const DevOp& op, cptr<C> __r
 // Diagonal op: the table (2^k phases) is read from LDS when the planner staged it there
 // (per-lane indices; a global read here would also wait on every outstanding memory
 // operation of the pass), else from the plan pool.
-template <typename C, typename P, int NT = kThreads>
+template <typename C, typename P>
 __device__ __forceinline__ void op_diag(C* __restrict__ lds, int T, const DevOp& op, P Dg, long long base)
 {
     // targets outside the tile contribute a per-tile constant part of the table index
@@ -689,12 +685,12 @@ __device__ __forceinline__ void op_diag(C* __restrict__ lds, int T, const DevOp&
         if (j < op.k && lp[j] < 0) gfix |= (int)((base >> op.gbit[j]) & 1) << j;
     }
     const int st = swz<C>(threadIdx.x);
-    for (int e = threadIdx.x; e < T; e += NT) {
+    for (int e = threadIdx.x; e < T; e += kThreads) {
         int idx = gfix;
 #pragma unroll
         for (int j = 0; j < kMaxDiagK; ++j)
             if (lp[j] >= 0) idx |= ((e >> lp[j]) & 1) << j;
-        const int pe = swz<C>(e - (int)threadIdx.x) ^ st;   // e - tid: a multiple of NT
+        const int pe = swz<C>(e - (int)threadIdx.x) ^ st;   // e - tid: a multiple of 256
         lds[pe] = cmul(lds[pe], Dg[idx]);
     }
 }
@@ -710,9 +706,9 @@ __device__ __forceinline__ void lds_sync()
 
 // WIDE = false leaves out the register-heavy paths (VALU dense ops on 4 or 5 targets,
 // permutations on 3 or more): the caller launches that variant only for passes without
-// such ops, and its lower register count allows more resident workgroups.  NT is the
-// workgroup size.  Ends with an LDS barrier after the last op.
-template <typename C, bool WIDE, bool LDSOP, int NT = kThreads>
+// such ops, and its lower register count allows more resident workgroups.  Ends with an LDS
+// barrier after the last op.
+template <typename C, bool WIDE, bool LDSOP>
 __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp> __restrict__ ops, int op_begin,
                           int op_count, cptr<C> __restrict__ pool, cptr<int> __restrict__ ipool,
                           cptr<float> __restrict__ apool, const float* __restrict__ alds, long long base)
@@ -724,11 +720,11 @@ __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp
             // matrix cores: a pair, one 4-qubit op, or (complex128 only) a 3-qubit op
             if (op.flags) {
                 ++oi;
-                op_mfma4<C, true, LDSOP, NT>(lds, T, op, ops[op_begin + oi], apool, alds);
+                op_mfma4<C, true, LDSOP>(lds, T, op, ops[op_begin + oi], apool, alds);
             } else if (sizeof(C) == 8 || op.k == 4) {   // (complex64 3-qubit ops: widened operands)
-                op_mfma4<C, false, LDSOP, NT>(lds, T, op, op, apool, alds);
+                op_mfma4<C, false, LDSOP>(lds, T, op, op, apool, alds);
             } else {
-                if constexpr (sizeof(C) == 16) op_mfma3<LDSOP, NT>(lds, T, op, apool, alds);
+                if constexpr (sizeof(C) == 16) op_mfma3<LDSOP>(lds, T, op, apool, alds);
             }
             // the next op's waves read only what the same waves wrote: LDS keeps a wave's order
             if (op.nosync) asm volatile("" ::: "memory");
@@ -737,25 +733,25 @@ __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp
         }
         if (op.kind == OP_DENSE) {
             switch (op.k) {
-            case 1: op_dense<C, 1, NT>(lds, T, op, M); break;
-            case 2: op_dense<C, 2, NT>(lds, T, op, M); break;
-            case 3: op_dense<C, 3, NT>(lds, T, op, M); break;
-            case 4: if constexpr (WIDE) op_dense<C, 4, NT>(lds, T, op, M); break;
-            default: if constexpr (WIDE) op_dense<C, 5, NT>(lds, T, op, M); break;
+            case 1: op_dense<C, 1>(lds, T, op, M); break;
+            case 2: op_dense<C, 2>(lds, T, op, M); break;
+            case 3: op_dense<C, 3>(lds, T, op, M); break;
+            case 4: if constexpr (WIDE) op_dense<C, 4>(lds, T, op, M); break;
+            default: if constexpr (WIDE) op_dense<C, 5>(lds, T, op, M); break;
             }
         } else if (op.kind == OP_PERM) {
             cptr<int> S = ipool + op.ioff;
             switch (op.k) {
-            case 1: op_perm<C, 1, NT>(lds, T, op, M, S); break;
-            case 2: op_perm<C, 2, NT>(lds, T, op, M, S); break;
-            case 3: if constexpr (WIDE) op_perm<C, 3, NT>(lds, T, op, M, S); break;
-            case 4: if constexpr (WIDE) op_perm<C, 4, NT>(lds, T, op, M, S); break;
-            default: if constexpr (WIDE) op_perm<C, 5, NT>(lds, T, op, M, S); break;
+            case 1: op_perm<C, 1>(lds, T, op, M, S); break;
+            case 2: op_perm<C, 2>(lds, T, op, M, S); break;
+            case 3: if constexpr (WIDE) op_perm<C, 3>(lds, T, op, M, S); break;
+            case 4: if constexpr (WIDE) op_perm<C, 4>(lds, T, op, M, S); break;
+            default: if constexpr (WIDE) op_perm<C, 5>(lds, T, op, M, S); break;
             }
         } else if (op.aoff >= 0) {
-            op_diag<C, const C*, NT>(lds, T, op, reinterpret_cast<const C*>(alds + op.aoff), base);
+            op_diag<C, const C*>(lds, T, op, reinterpret_cast<const C*>(alds + op.aoff), base);
         } else {
-            op_diag<C, cptr<C>, NT>(lds, T, op, M, base);
+            op_diag<C, cptr<C>>(lds, T, op, M, base);
         }
         lds_sync();
     }
@@ -763,16 +759,15 @@ __device__ __forceinline__ void apply_ops(C* __restrict__ lds, int T, cptr<DevOp
 
 // The pass's staged block (diagonal tables, then matrix operands), global -> LDS: 16 bytes
 // per thread and step; blocks are multiples of 16 bytes.
-template <int NT = kThreads>
 __device__ __forceinline__ void stage_operands(float* __restrict__ alds, cptr<float> __restrict__ apool, int off, int len)
 {
     cptr<floatx4> src = (cptr<floatx4>)(apool + off);
     floatx4* dst = reinterpret_cast<floatx4*>(alds);
-    for (int i = threadIdx.x; i < (len >> 2); i += NT) dst[i] = src[i];
+    for (int i = threadIdx.x; i < (len >> 2); i += kThreads) dst[i] = src[i];
 }
 
 // One tile of one pass: HBM -> LDS, every op of the pass, LDS -> HBM.
-template <typename C, bool WIDE, bool LDSOP, int NT = kThreads>
+template <typename C, bool WIDE, bool LDSOP>
 __device__ __forceinline__ void run_tile(gptr<C> __restrict__ st, C* __restrict__ lds, const PassArgs& a,
                                          long long tile, cptr<DevOp> __restrict__ ops, cptr<C> __restrict__ pool,
                                          cptr<int> __restrict__ ipool, cptr<float> __restrict__ apool,
@@ -782,18 +777,18 @@ __device__ __forceinline__ void run_tile(gptr<C> __restrict__ st, C* __restrict_
     if (from_zero) {
         // the tile of |0...0> (Eq. 1): built on chip instead of read from HBM (element 0
         // keeps position 0 under the swizzle and every other element is zero)
-        for (int e = threadIdx.x; e < (1 << a.m); e += NT) {
+        for (int e = threadIdx.x; e < (1 << a.m); e += kThreads) {
             C z;
             z.x = (base == 0 && e == 0) ? 1 : 0;
             z.y = 0;
             lds[e] = z;
         }
     } else {
-        move_tile<C, true, NT>(st, lds, a, base);
+        move_tile<C, true>(st, lds, a, base);
     }
     __syncthreads();
-    apply_ops<C, WIDE, LDSOP, NT>(lds, 1 << a.m, ops, a.op_begin, a.op_count, pool, ipool, apool, alds, base);
-    move_tile<C, false, NT>(st, lds, a, base);
+    apply_ops<C, WIDE, LDSOP>(lds, 1 << a.m, ops, a.op_begin, a.op_count, pool, ipool, apool, alds, base);
+    move_tile<C, false>(st, lds, a, base);
 }
 
 // One work-list entry of a pass launch: the state it belongs to and its tile.  Consecutive
@@ -818,8 +813,8 @@ __device__ __forceinline__ long long xcd_tile(long long t, unsigned grid, long l
 // workgroups a CU holds (four complex64, two complex128) overlap them only in part; with the
 // loads ahead each counts twice: 30-qubit complex64 passes 4.28 -> 4.00 ms (moves alone
 // 3.46), 28-qubit complex128 2.71 -> 2.43 ms (moves alone 1.72, ops alone 2.03).
-template <typename C, bool WIDE, bool PF, int NT>
-__global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restrict__ st, C* __restrict__ st2,
+template <typename C, bool WIDE, bool PF>
+__global__ __launch_bounds__(kThreads, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restrict__ st, C* __restrict__ st2,
                                                                      const PassArgs a, long long ntiles,
                                                                      int from_zero, const DevOp* __restrict__ ops,
                                                                      const C* __restrict__ pool,
@@ -833,13 +828,13 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restri
     extern __shared__ __align__(16) unsigned char smem[];
     C* lds = reinterpret_cast<C*>(smem);
     float* alds = reinterpret_cast<float*>(smem + (sizeof(C) << a.m));
-    stage_operands<NT>(alds, (cptr<float>)apool, a.a_off, PF ? a.a_len : a.d_len);
+    stage_operands(alds, (cptr<float>)apool, a.a_off, PF ? a.a_len : a.d_len);
     __syncthreads();
     const long long total = st2 ? 2 * ntiles : ntiles;
     if constexpr (PF) {
-        constexpr int W = sizeof(C) == 8 ? 2 : 1, NS = 4096 / (NT * W);
-        constexpr int LOGT = NT == 512 ? 9 : 8, LW = W == 2 ? 1 : 0;
-        const long long tl = local_off_bits(a, (int)threadIdx.x << LW, LW, LOGT + LW);
+        constexpr int W = sizeof(C) == 8 ? 2 : 1, NS = 4096 / (kThreads * W);
+        constexpr int LW = W == 2 ? 1 : 0;
+        const long long tl = local_off_bits(a, (int)threadIdx.x << LW, LW, kLogThreads + LW);
         auto at = [&](long long t, gptr<C>& s) {   // the state of entry t and its tile's base
             const bool second = t >= ntiles;
             s = (gptr<C>)(second ? st2 : st);
@@ -849,8 +844,8 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restri
         long long t = blockIdx.x;
         gptr<C> s;
         long long base = at(t, s);
-        load_tile<C, NS, W, NT>(s + base + tl, a, v);
-        put_tile<C, NS, W, NT>(lds, v);
+        load_tile<C, NS, W>(s + base + tl, a, v);
+        put_tile<C, NS, W>(lds, v);
         lds_sync();
         for (;;) {
             const long long tn = t + gridDim.x;
@@ -858,21 +853,21 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restri
             long long bn = 0;
             if (tn < total) {
                 bn = at(tn, sn);
-                load_tile<C, NS, W, NT>(sn + bn + tl, a, v);
+                load_tile<C, NS, W>(sn + bn + tl, a, v);
             }
-            apply_ops<C, WIDE, true, NT>(lds, 4096, (cptr<DevOp>)ops, a.op_begin, a.op_count, (cptr<C>)pool,
+            apply_ops<C, WIDE, true>(lds, 4096, (cptr<DevOp>)ops, a.op_begin, a.op_count, (cptr<C>)pool,
                                          (cptr<int>)ipool, (cptr<float>)apool, alds, base);
             if (tn >= total) {
-                move_tile_n<C, false, NS, W, NT>(s, lds, a, base + tl);
+                move_tile_n<C, false, NS, W>(s, lds, a, base + tl);
                 break;
             }
             // the tile to registers, the next one into its place, then the stores: the wait
             // for the next tile's loads then has no stores behind it to wait for
             floatx4 r[NS];
-            get_tile<C, NS, W, NT>(lds, r);
+            get_tile<C, NS, W>(lds, r);
             lds_sync();
-            put_tile<C, NS, W, NT>(lds, v);
-            store_tile<C, NS, W, NT>(s + base + tl, a, r);
+            put_tile<C, NS, W>(lds, v);
+            store_tile<C, NS, W>(s + base + tl, a, r);
             lds_sync();
             t = tn;
             s = sn;
@@ -881,7 +876,7 @@ __global__ __launch_bounds__(NT, sizeof(C) == 8 ? 4 : 2) void k_pass(C* __restri
     } else {
         for (long long t = blockIdx.x; t < total; t += gridDim.x) {
             const bool second = t >= ntiles;
-            run_tile<C, WIDE, false, NT>((gptr<C>)(second ? st2 : st), lds, a,
+            run_tile<C, WIDE, false>((gptr<C>)(second ? st2 : st), lds, a,
                                         xcd_tile(second ? t - ntiles : t, gridDim.x, ntiles), (cptr<DevOp>)ops,
                                         (cptr<C>)pool, (cptr<int>)ipool, (cptr<float>)apool, alds, from_zero != 0);
             __syncthreads();
@@ -1307,15 +1302,15 @@ __global__ __launch_bounds__(kThreads) void k_expval_r(const C* __restrict__ sa,
     floatx4 va[NS], vb[TWO ? NS : 1];
     auto load = [&](long long tile) {
         const long long o = tile_base(a, tile) + tl;
-        load_tile<C, NS, W, kThreads>(ga + o, a, va);
-        if constexpr (TWO) load_tile<C, NS, W, kThreads>(gb + o, a, vb);
+        load_tile<C, NS, W>(ga + o, a, va);
+        if constexpr (TWO) load_tile<C, NS, W>(gb + o, a, vb);
     };
     load(blockIdx.x);
     __syncthreads();
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const long long base = tile_base(a, tile);
-        put_tile<C, NS, W, kThreads>(la, va);
-        if constexpr (TWO) put_tile<C, NS, W, kThreads>(lb, vb);
+        put_tile<C, NS, W>(la, va);
+        if constexpr (TWO) put_tile<C, NS, W>(lb, vb);
         lds_sync();
         if (tile + gridDim.x < ntiles) load(tile + gridDim.x);
         int i = 0;
@@ -2043,14 +2038,14 @@ hipError_t launch_pass_t(void* st, void* st2, const PassArgs& a, long long ntile
     const long long total = st2 ? 2 * ntiles : ntiles;
     // a 64 KiB complex128 tile plus its operand block exceeds the 64 KiB default
     static std::atomic<unsigned long long> raised{0};
-    const hipError_t e = raise_lds_limit(raised, 163840, k_pass<C, WIDE, PF, kThreads>);
+    const hipError_t e = raise_lds_limit(raised, 163840, k_pass<C, WIDE, PF>);
     if (e != hipSuccess) return e;
     const size_t lds = (sizeof(C) << a.m) + sizeof(float) * (size_t)(PF ? a.a_len : a.d_len);
     // at most 64 workgroups per CU, each striding over tiles: the operand block is staged
     // once per workgroup rather than once per tile (measured on 2^18-tile passes: 6 %
     // faster for complex64, 10 % for complex128 than one workgroup per tile)
     const long long grid = std::min<long long>(PF ? total / 2 : total, 64ll * device_cus());
-    hipLaunchKernelGGL((k_pass<C, WIDE, PF, kThreads>), dim3((unsigned)grid), dim3(kThreads), lds, s, (C*)st, (C*)st2, a,
+    hipLaunchKernelGGL((k_pass<C, WIDE, PF>), dim3((unsigned)grid), dim3(kThreads), lds, s, (C*)st, (C*)st2, a,
                        ntiles, from_zero ? 1 : 0, ops, (const C*)pool, ipool, apool);
     return hipGetLastError();
 }
@@ -2074,7 +2069,7 @@ hipError_t prepare_batch_pass()
 hipError_t launch_batch_pass(int dtype, const BatchItem* table, const BatchList* list, int grid, int tile_qubits,
                              hipStream_t s, bool wide)
 {
-    // tile + the per-pass operand block (MFMA matrices, diagonal tables) of either dtype
+    // tile and the pass's diagonal tables of either dtype (matrix operands come through L2)
     const size_t lds = ((dtype == 0 ? sizeof(float2) : sizeof(double2)) << tile_qubits) +
                        sizeof(float) * kServeOperandFloats;
     if (dtype == 0)
