@@ -1,10 +1,11 @@
 """Facts of the planner's results that end results alone would not show (no GPU): memory of a
-plan being made, what its passes stage, launch limits per device."""
+plan being made, what its passes stage, the tables of matrix-core steps, launch limits per device."""
 import ctypes
 import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 from paper_2604_03816_amd import build as qsv_build
@@ -135,3 +136,34 @@ def test_a_gradient_call_reserves_what_its_plans_take(facts, forward, undo, plan
     facts.reserved_slots.argtypes = [ctypes.c_size_t] * 3 + [ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]
     got = facts.reserved_slots(forward, undo, plans, 8, ctypes.byref(b))
     assert (got, b.value) == want
+
+
+def random_dense(n, count, seed):
+    rng = np.random.default_rng(seed)
+    ops = []
+    for _ in range(count):
+        k = int(rng.choice([2, 3, 3, 4, 4, 4]))
+        ops.append(C.Op("U", tuple(int(q) for q in rng.permutation(n)[:k]), matrix=C.haar_unitary(rng, 1 << k)))
+    return ops
+
+
+@pytest.mark.parametrize("dtype,tol", [("c64", 1e-5), ("c128", 1e-13)])
+@pytest.mark.parametrize("tile,n", [(8, 8), (8, 14), (9, 9), (10, 10), (10, 16), (11, 16), (12, 12), (12, 20), (13, 15)])
+def test_matrix_core_steps_from_their_tables(facts, tile, n, dtype, tol):
+    """Operand and offset tables walked lane by lane: every tile slot read and written once by
+    one wave, no barrier left out where a wave would read another's slots, and the product the
+    gates' own (entries rounded to the state's precision: 2^-24 of sums of 16 terms of size 1.4,
+    twice in a pair, stays under 1e-5; FP64 under 1e-13)."""
+    if dtype == "c128" and tile > 12:
+        pytest.skip("13-qubit tiles fit LDS only in complex64")
+    facts.check_steps.argtypes = [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int,
+                                                       ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int)]
+    free = 0
+    for seed in range(4):
+        for ops in (random_dense(n, 40, seed), circuit("hea", n, 4, seed), circuit("brickwork", n, 6, seed)):
+            g, worst, nosync = qsv.GateList(ops), ctypes.c_double(), ctypes.c_int()
+            steps = facts.check_steps(n, 0 if dtype == "c64" else 1, tile, g.arr, g.n, seed < 2, ctypes.byref(worst),
+                                      ctypes.byref(nosync))
+            assert steps > 0 and worst.value <= tol, (seed, steps, worst.value)
+            free += nosync.value
+    assert (free > 0) == (tile >= 10)
