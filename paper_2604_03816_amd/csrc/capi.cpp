@@ -1228,7 +1228,10 @@ qsv_status qsv_probs(qsv_state s, const int* qubits, int m, void* out, int out_o
     }
     MargBlocks a{};
     a.m = m;
-    a.cb = std::min(n, kMargBlockBits);
+    // many outputs of at most 16 blocks of 2^12 amplitudes: blocks of 2^8, a workgroup each
+    // (the 12 lowest of 15 qubits: 37 us a call with 2^12, 34 so; from 18 qubits on slower: the
+    // 14 highest of 20 48 and 68-80)
+    a.cb = std::min(n, m >= 11 && n <= 16 ? kLogThreads : kMargBlockBits);
     unsigned long long Q = 0;
     for (int j = 0; j < m; ++j) {
         const int q = qubits ? qubits[j] : j;
